@@ -49,34 +49,88 @@ struct FusedVariant {
     int flags;
 };
 
-// Does candidate c eliminate the victim?  !EX: the default measure (MODE kExBoundary = the
-// division-free form of nms_pair.h, else the literal division).  EX: the variants.
+// The float32 that a candidate carries in FusedCandidate::T when the threshold has a boundary form.
+// The default measure and the outranking-area variants: the value that decides (nms_pair.h).
+// Intersection over union: the value below which a pair is a certain miss whatever the victim -- the
+// float32 at or below boundary * area * (1 - 2^-21), by the argument at map_tile_ex_kernel's c_T1;
+// where that is not positive (a candidate without area) nothing is a certain miss.  A variant's value
+// that is not positive becomes -infinity: every intersection, none included, reaches it.
+template <bool EX, bool IOU>
+__device__ __forceinline__ float fused_threshold(float area, double boundary)
+{
+    if (!IOU) {
+        const float t = nms_pair_threshold(area, boundary);
+        return !EX || t > 0.0f ? t : -INFINITY;
+    }
+    const double t = boundary * (double)area * (1.0 - 0x1p-21);
+    float t1 = (float)t;
+    if ((double)t1 > t) t1 = __uint_as_float(__float_as_uint(t1) - 1u);  // next float32 down (t > 0)
+    return t1 > 0.0f ? t1 : -INFINITY;
+}
+
+// First test of a pair, decisive but for IoU in boundary form, where a hit only means "maybe", and
+// for the scores and labels of AUX in boundary form.  One floor is enough there: a negative width
+// times a floored height reaches no positive T, and T = -infinity passes everything on.
 template <bool EX, bool IOU, int MODE, bool AUX>
-__device__ __forceinline__ bool fused_hit(const float4 v, float v_area, float v_score, int v_label,
-                                          const FusedCandidate &c, float theta, const FusedVariant &o)
+__device__ __forceinline__ bool fused_first(const float4 v, float v_area, float v_score, int v_label,
+                                            const FusedCandidate &c, float theta, const FusedVariant &o)
 {
     if (!EX) {
         if (MODE == kExBoundary) return nms_eliminates_fast(v.x, v.y, v.z, v.w, c.x1, c.y1, c.x2, c.y2, c.T);
         return nms_eliminates_exact(v.x, v.y, v.z, v.w, c.x1, c.y1, c.x2, c.y2, c.area, theta);
     }
-    const float iw = fmaxf(0.0f, (fminf(v.z, c.x2) - fmaxf(v.x, c.x1)) + o.offset);
+    float iw = (fminf(v.z, c.x2) - fmaxf(v.x, c.x1)) + o.offset;
+    if (MODE != kExBoundary) iw = fmaxf(0.0f, iw);
     const float ih = fmaxf(0.0f, (fminf(v.w, c.y2) - fmaxf(v.y, c.y1)) + o.offset);
     const float inter = iw * ih;
+    if (MODE == kExBoundary) return inter >= c.T;
     const float denom = IOU ? (v_area + c.area) - inter : c.area;
-    bool hit;
-    if (MODE == kExBoundary && !IOU)
-        hit = inter >= c.T;
-    else if (MODE == kExBoundary)
-        hit = (double)inter >= o.boundary * (double)denom;
-    else if (MODE == kExDivideGe)
-        hit = !(inter / denom < theta);
-    else
-        hit = inter / denom > theta;
+    bool hit = MODE == kExDivideGe ? !(inter / denom < theta) : inter / denom > theta;
     if (AUX) {
         hit = hit && ((o.flags & kExTiesIgnore) == 0 || c.score > v_score);
         hit = hit && ((o.flags & kExClasses) == 0 || c.label == v_label);
     }
     return hit;
+}
+
+// Is there anything to decide after fused_first?
+template <bool EX, bool IOU, int MODE, bool AUX>
+constexpr bool kFusedSecond = EX && MODE == kExBoundary && (IOU || AUX);
+
+// What is left to decide for the lanes of `word` (not 0) that fused_first let through.
+template <bool IOU, bool AUX>
+__device__ __forceinline__ unsigned long long fused_second(unsigned long long word, const float4 v, float v_area, float v_score,
+                                                           int v_label, const FusedCandidate &c, const FusedVariant &o)
+{
+    if (AUX) {
+        if (o.flags & kExTiesIgnore) word &= __ballot(c.score > v_score);
+        if (o.flags & kExClasses) word &= __ballot(c.label == v_label);
+    }
+    if (IOU && word != 0) {
+        const float iw = fmaxf(0.0f, (fminf(v.z, c.x2) - fmaxf(v.x, c.x1)) + o.offset);
+        const float ih = fmaxf(0.0f, (fminf(v.w, c.y2) - fmaxf(v.y, c.y1)) + o.offset);
+        const float inter = iw * ih;
+        const float denom = (v_area + c.area) - inter;
+        word &= __ballot((double)inter >= o.boundary * (double)denom);
+    }
+    return word;
+}
+
+// Does candidate c eliminate the victim?  The lane mask over the lanes of `open` (the others do not
+// matter).  !EX: the default measure (MODE kExBoundary = the division-free form of nms_pair.h, else the
+// literal division).  EX: the variants.  Few rows pass the first test, so what follows it -- the
+// float64 compare of IoU, scores, labels -- sits behind a wave-uniform branch (every pair through the
+// float64 compare: 128 frames of 3000 boxes, IoU, 20 labels, 874 us for the call; so: 749).
+template <bool EX, bool IOU, int MODE, bool AUX>
+__device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_score,
+                                                         int v_label, const FusedCandidate &c, float theta, const FusedVariant &o)
+{
+    unsigned long long word = __ballot(fused_first<EX, IOU, MODE, AUX>(v, v_area, v_score, v_label, c, theta, o)) & open;
+    if (kFusedSecond<EX, IOU, MODE, AUX> && word != 0) {
+        asm volatile("" ::: "memory");  // keeps this a branch
+        word = fused_second<IOU, AUX>(word, v, v_area, v_score, v_label, c, o);
+    }
+    return word;
 }
 
 // Bitwise OR over each row of 16 lanes, in the row's last lane.
@@ -98,10 +152,13 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                     const int32_t *__restrict__ counts, int n_max, int n_pad, NmsThetaConst th, FusedVariant opt,
                     uint8_t *__restrict__ keep_out)
 {
-    constexpr bool kUseT = MODE == kExBoundary && !IOU;  // the list carries T, else the area
+    constexpr bool kUseT = MODE == kExBoundary;          // the list carries T, else the area
+    constexpr bool kUseArea = kUseT && IOU;              // ... and the area as well
+    constexpr bool kSecond = kFusedSecond<EX, IOU, MODE, AUX>;
     constexpr int kTileBuf = kWalkLists;                 // one more buffer of the same layout: the rows of the tile being settled
     __shared__ float4 box_s[kWalkLists + 1][kTile];      // list t in buffer t % kWalkLists
     __shared__ float aux_s[kWalkLists + 1][kTile];
+    __shared__ float area_s[kWalkLists + 1][kTile];
     __shared__ float score_s[kWalkLists + 1][kTile];
     __shared__ int label_s[kWalkLists + 1][kTile];
     __shared__ int count_s[kWalkLists];
@@ -148,7 +205,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
             FusedCandidate me;
             me.x1 = vb[i].x, me.y1 = vb[i].y, me.x2 = vb[i].z, me.y2 = vb[i].w;
             me.area = EX ? ((vb[i].z - vb[i].x) + opt.offset) * ((vb[i].w - vb[i].y) + opt.offset) : area[r];
-            me.T = MODE == kExBoundary ? nms_pair_threshold(me.area, EX ? opt.boundary : th.m) : 0.0f;
+            me.T = MODE == kExBoundary ? fused_threshold<EX, IOU>(me.area, EX ? opt.boundary : th.m) : 0.0f;
             me.score = AUX ? opt.ranked_score[(size_t)f * n_pad + r] : 0.0f;
             me.label = (AUX && (opt.flags & kExClasses)) ? opt.ranked_label[(size_t)f * n_pad + r] : 0;
             self[i] = me;
@@ -165,9 +222,20 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
         const float4 b = box_s[buf][k];
         c.x1 = b.x, c.y1 = b.y, c.x2 = b.z, c.y2 = b.w;
         c.T = kUseT ? aux_s[buf][k] : 0.0f;
-        c.area = kUseT ? 0.0f : aux_s[buf][k];
+        c.area = kUseArea ? area_s[buf][k] : (kUseT ? 0.0f : aux_s[buf][k]);
         c.score = AUX ? score_s[buf][k] : 0.0f;
         c.label = AUX ? label_s[buf][k] : 0;
+        return c;
+    };
+    // What fused_first needs of it: where a second test follows, area, score and label are only read there.
+    auto first_entry = [&](int buf, int k) __attribute__((always_inline)) {
+        if (!kSecond) return entry(buf, k);
+        FusedCandidate c;
+        const float4 b = box_s[buf][k];
+        c.x1 = b.x, c.y1 = b.y, c.x2 = b.z, c.y2 = b.w;
+        c.T = aux_s[buf][k];
+        c.area = c.score = 0.0f;
+        c.label = 0;
         return c;
     };
     // The list in buffer `buf` against the tiles in slots 0 .. N-1.  Survivors are fetched four
@@ -179,27 +247,39 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
         if (count == 0) return;
         auto fetch = [&](FusedCandidate (&c)[kWalkChunk], int k0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < kWalkChunk; ++u) c[u] = entry(buf, k0 + u < count ? k0 + u : count - 1);
+            for (int u = 0; u < kWalkChunk; ++u) c[u] = first_entry(buf, k0 + u < count ? k0 + u : count - 1);
+        };
+        // survivor c (entry k) against the N tiles
+        auto test_one = [&](const FusedCandidate &c, int k) __attribute__((always_inline)) {
+            unsigned long long word[N];
+            unsigned long long any = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                word[i] = __ballot(fused_first<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].score, self[i].label, c, th.theta, opt));
+                if (kSecond) {
+                    word[i] &= ~out[i];
+                    any |= word[i];
+                } else {
+                    out[i] |= word[i];
+                }
+            }
+            if (kSecond && any != 0) {
+                asm volatile("" ::: "memory");  // keeps this a branch
+                const FusedCandidate full = entry(buf, k);
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    if (word[i] != 0)
+                        out[i] |= fused_second<IOU, AUX>(word[i], vb[i], self[i].area, self[i].score, self[i].label, full, opt);
+            }
         };
         auto test = [&](const FusedCandidate (&c)[kWalkChunk], int k0) __attribute__((always_inline)) {
             if (k0 + kWalkChunk <= count) {
 #pragma unroll
-                for (int u = 0; u < kWalkChunk; ++u) {
-#pragma unroll
-                    for (int i = 0; i < N; ++i)
-                        out[i] |= __ballot(fused_hit<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].score, self[i].label,
-                                                                          c[u], th.theta, opt));
-                }
+                for (int u = 0; u < kWalkChunk; ++u) test_one(c[u], k0 + u);
             } else {
 #pragma unroll
-                for (int u = 0; u < kWalkChunk - 1; ++u) {
-                    if (k0 + u < count) {  // wave-uniform
-#pragma unroll
-                        for (int i = 0; i < N; ++i)
-                            out[i] |= __ballot(fused_hit<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].score,
-                                                                              self[i].label, c[u], th.theta, opt));
-                    }
-                }
+                for (int u = 0; u < kWalkChunk - 1; ++u)
+                    if (k0 + u < count) test_one(c[u], k0 + u);  // wave-uniform
             }
         };
         FusedCandidate even[kWalkChunk], odd[kWalkChunk];
@@ -224,6 +304,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
     auto post_tile = [&]() __attribute__((always_inline)) {
         box_s[kTileBuf][lane] = vb[0];
         aux_s[kTileBuf][lane] = kUseT ? self[0].T : self[0].area;
+        if (kUseArea) area_s[kTileBuf][lane] = self[0].area;
         if (AUX) score_s[kTileBuf][lane] = self[0].score;
         if (AUX) label_s[kTileBuf][lane] = self[0].label;
     };
@@ -245,8 +326,8 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                 const int count = g > 0 ? __builtin_amdgcn_readfirstlane(count_s[pending]) : 0;
                 unsigned long long part = 0;
                 for (int k = wave; k < count; k += kFusedWaves)
-                    part |= __ballot(fused_hit<EX, IOU, MODE, AUX>(row_box, row.area, row.score, row.label, entry(pending, k),
-                                                                    th.theta, opt));
+                    part |= fused_word<EX, IOU, MODE, AUX>(~part, row_box, row.area, row.score, row.label, entry(pending, k),
+                                                           th.theta, opt);
                 if (lane == 0) part_s[wave] = part;
                 FusedCandidate victim[kTile / kFusedWaves];
 #pragma unroll
@@ -254,11 +335,9 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
 #pragma unroll
                 for (int j = 0; j < kTile / kFusedWaves; ++j) {
                     const int r = wave + kFusedWaves * j;
-                    const bool hit = fused_hit<EX, IOU, MODE, AUX>(make_float4(victim[j].x1, victim[j].y1, victim[j].x2, victim[j].y2),
-                                                                   victim[j].area, victim[j].score, victim[j].label, row,
-                                                                   th.theta, opt) &&
-                                     lane < r;
-                    const unsigned long long hitters = __ballot(hit);
+                    const unsigned long long hitters = fused_word<EX, IOU, MODE, AUX>(
+                        (1ull << r) - 1ull, make_float4(victim[j].x1, victim[j].y1, victim[j].x2, victim[j].y2), victim[j].area,
+                        victim[j].score, victim[j].label, row, th.theta, opt);
                     if (lane == 0) hitters_s[r] = hitters;
                 }
             }
@@ -289,6 +368,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                     const int k = __builtin_popcountll(kept & ((1ull << lane) - 1ull));
                     box_s[into][k] = v;
                     aux_s[into][k] = kUseT ? mine.T : mine.area;
+                    if (kUseArea) area_s[into][k] = mine.area;
                     if (AUX) score_s[into][k] = mine.score;
                     if (AUX) label_s[into][k] = mine.label;
                 }
