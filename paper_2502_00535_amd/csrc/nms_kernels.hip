@@ -524,9 +524,9 @@ int nms_reduce_greedy_batched(const uint64_t *mask, const int32_t *order, const 
     for (int t0 = 0; t0 < T; t0 += kSweepTiles) {
         begin_launch();
         if (t0 == 0)
-            greedy_sweep_kernel<true><<<dim3(frames), dim3(256), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
+            greedy_sweep_kernel<true><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
         else
-            greedy_sweep_kernel<false><<<dim3(frames), dim3(256), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
+            greedy_sweep_kernel<false><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
         st = launch_status();
         if (st != NMS_OK) return st;
         const int later = T - (t0 + kSweepTiles);  // tile rows after this block
