@@ -86,6 +86,24 @@ NMS_HD NmsRunLayout nms_run_layout(int n_max, int n_pad, int frames, int sort_ch
     return l;
 }
 
+// ---- rank step ----------------------------------------------------------------------------------
+// Ranks by counting (n compares per box over the whole chip) instead of a sort of one workgroup per
+// frame, whose time hardly depends on the number of frames.  Measured, the rank step alone, counted
+// against sorted: 1 x 4096 4.9 us against 15.4, 8 x 4096 12.5 / 15.9, 16 x 4096 20.5 / 16.0; 8 x 3000
+// 9.7 / 17.4, 16 x 2048 8.0 / 10.1, 24 x 2048 10.7 / 10.2, 32 x 1000 5.8 / 8.3, 64 x 1000 9.3 / 8.3, 64 x 500
+// 4.7 / 6.9, 128 x 500 7.3 / 7.0, 128 x 256 3.9 / 6.3: the line is a number of boxes.
+NMS_HD bool nms_use_count_rank(int n_max, int frames, int sort_chunk)
+{
+    return n_max <= sort_chunk && (long long)frames * n_max <= 32768;
+}
+
+// Elements per workgroup there: the most that leave two workgroups for every compute unit.
+NMS_HD int nms_count_rank_elements(int n_max, int frames)
+{
+    const long long boxes = (long long)frames * n_max;
+    return boxes >= 512 * 128 ? 128 : (boxes >= 256 * 64 ? 64 : 16);
+}
+
 // ---- which kernels a whole-path call runs ------------------------------------------------------
 // All four routes return the same keep vector (the paper's rule, section "Algorithm Correctness");
 // they differ in what they launch.  Values of nms_route() in the C ABI.

@@ -47,6 +47,7 @@ __device__ __forceinline__ int frame_count(const int32_t *counts, int f, int n_m
 }
 
 #include "kernels/rank.h"
+#include "kernels/rank_count.h"
 #include "kernels/map.h"
 #include "kernels/direct.h"
 #include "kernels/reduce.h"
@@ -105,10 +106,32 @@ inline int launch_status()
     return NMS_ERR_LAUNCH;
 }
 
+// The rank step by counting (nms_use_count_rank).
+int count_rank_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                      int32_t *order, float *sorted5, uint8_t *keep_preset, const RankExtras &extras, hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    // elements per workgroup: as many as leave a workgroup for every compute unit
+    const int elems = nms_count_rank_elements(n_max, frames);
+    const dim3 grid((n_pad + elems - 1) / elems, frames);
+    begin_launch();
+#define NMS_LAUNCH_COUNT(E_)                                                                                           \
+    rank_count_kernel<E_><<<grid, dim3(kCountThreads), 0, stream>>>(boxes, scores, counts, n_max, n_pad, order, sorted5, \
+                                                                    keep_preset, extras)
+    if (elems == 16) NMS_LAUNCH_COUNT(16);
+    else if (elems == 64) NMS_LAUNCH_COUNT(64);
+    else NMS_LAUNCH_COUNT(128);
+#undef NMS_LAUNCH_COUNT
+    return launch_status();
+}
+
 int rank_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
                 int32_t *order, float *sorted5, void *workspace, uint8_t *keep_preset, float4 *ysc, unsigned *ytile,
                 hipStream_t stream, float *tsc = nullptr, double m = 0.0)
 {
+    if (ysc == nullptr && ytile == nullptr && tsc == nullptr && nms_use_count_rank(n_max, frames, kChunk))
+        return count_rank_launch(boxes, scores, counts, n_max, frames, order, sorted5, keep_preset,
+                                 {nullptr, nullptr, nullptr, nullptr, 0.0f}, stream);
     const int n_pad = nms_padded_n(n_max);
     // one chunk up to kChunk boxes; beyond that, chunks of kMergeChunk (more workgroups, shorter sorts) and a merge
     const int n_chunks = n_max <= kChunk ? 1 : (n_max + kMergeChunk - 1) / kMergeChunk;
@@ -672,9 +695,13 @@ int nms_run_greedy_batched(const float *boxes, const float *scores, const int32_
     int32_t *order = w.order;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, nullptr, w.ysc, w.ytile, s);
+    // counted ranks come without the y-scaled table: the map step then takes its late-scaled form
+    const bool counted = nms_use_count_rank(n_max, frames, kChunk);
+    float4 *ysc = counted ? nullptr : w.ysc;
+    unsigned *ytile = counted ? nullptr : w.ytile;
+    st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, nullptr, ysc, ytile, s);
     if (st != NMS_OK) return st;
-    st = map_launch<true>(w.sorted5, counts, n_max, frames, threshold, mask, nullptr, nullptr, w.ysc, w.ytile, s);
+    st = map_launch<true>(w.sorted5, counts, n_max, frames, threshold, mask, nullptr, nullptr, ysc, ytile, s);
     if (st != NMS_OK) return st;
     return nms_reduce_greedy_batched(reinterpret_cast<const uint64_t *>(mask), order, counts, n_max, frames, keep_out,
                                      stream);
@@ -725,15 +752,21 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     hipStream_t s = static_cast<hipStream_t>(stream);
     // under the paper's rule the row reduction is folded into the map kernel: keep_out starts at 1
     const bool fold = opt.rule == NMS_RULE_PAPER;
-    st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
-                     nullptr, s);
-    if (st != NMS_OK) return st;
-    begin_launch();
-    gather_ranked_kernel<<<dim3((n_pad + 255) / 256, frames), dim3(256), 0, s>>>(
-        w.order, scores, opt.classes, counts, w.sorted5, opt.pixel_offset, n_max, n_pad, ranked_score, ranked_class,
-        ranked_area);
-    st = launch_status();
-    if (st != NMS_OK) return st;
+    if (nms_use_count_rank(n_max, frames, kChunk)) {  // one launch for ranks and what follows them
+        st = count_rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, fold ? keep_out : nullptr,
+                               {opt.classes, ranked_score, ranked_class, ranked_area, opt.pixel_offset}, s);
+        if (st != NMS_OK) return st;
+    } else {
+        st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
+                         nullptr, s);
+        if (st != NMS_OK) return st;
+        begin_launch();
+        gather_ranked_kernel<<<dim3((n_pad + 255) / 256, frames), dim3(256), 0, s>>>(
+            w.order, scores, opt.classes, counts, w.sorted5, opt.pixel_offset, n_max, n_pad, ranked_score, ranked_class,
+            ranked_area);
+        st = launch_status();
+        if (st != NMS_OK) return st;
+    }
 
     // work units and grid as in map_launch
     const int T = n_pad / kTile;
