@@ -1,0 +1,223 @@
+// Part of nms_kernels.hip (included there, inside its anonymous namespace): greedy rule with class labels: every class by a wavefront of its own.
+#pragma once
+
+// ----------------------------------------------------------------------------- greedy rule, class by class
+
+// With labels a box eliminates boxes of its own label only, so the sequential rule falls apart into
+// one short procedure per label.  A workgroup puts the ranked boxes of its frame into 256 bins by
+// label (one more pass of the rank step's stable radix sort, so a bin stays in rank order) and each
+// wavefront settles whole bins, without a barrier: 64 rows at a time, the bin's survivors so far
+// against them, then the rows among themselves in rank order.  Twenty labels leave a twentieth of the
+// pairs, and the bins of a frame run side by side where the walk of greedy_fused_kernel is one chain
+// through all tiles (128 ragged frames of 3000 boxes, IoU, 20 labels, the whole call: 749 -> 91 us).
+//
+// A bin is found by a hash of the label, so one bin may hold several labels: the label test stays, and
+// any labels give the same result.  A bin is one wavefront's work and grows with the square of its
+// size; a frame with a bin of more than kClassBin rows is left to the walk (todo[f] = 1).
+//
+// LDS: a bin's survivors are kept, packed, at the front of its own stretch of the tables; the tile in
+// work sits right behind them (survivors + rows of the tile never exceed the rows seen so far).
+constexpr int kClassBins = 256;
+constexpr int kClassBin = 1024;
+
+__device__ __forceinline__ unsigned class_bin(int label)
+{
+    unsigned x = (unsigned)label;
+    x ^= x >> 16;
+    x ^= x >> 8;
+    return x & (kClassBins - 1);
+}
+
+template <int W>
+struct ClassSort {
+    unsigned long long keys[256 * W];
+    unsigned long long match[512 * W];
+    unsigned hist[256 * W];
+    unsigned wbase[256 * W];
+    unsigned tot[256];
+};
+
+template <int W>
+struct ClassTables {
+    float4 box[256 * W];
+    float T[256 * W];
+    int label[256 * W];
+    uint16_t rank[256 * W];
+};
+
+// W: wavefronts of the workgroup; frames of at most 256 W boxes.  Grid: frames * parts workgroups; each
+// takes every parts-th bin of its frame.
+template <bool IOU, int W>
+__global__ void __launch_bounds__(W * 64)
+greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ order, const int32_t *__restrict__ counts,
+                      int n_max, int n_pad, int parts, FusedVariant opt, unsigned *__restrict__ todo, uint8_t *__restrict__ keep_out)
+{
+    constexpr int kThreads = W * 64;
+    constexpr size_t kBytes = sizeof(ClassSort<W>) > sizeof(ClassTables<W>) ? sizeof(ClassSort<W>) : sizeof(ClassTables<W>);
+    __shared__ __align__(16) unsigned char raw[kBytes];
+    ClassSort<W> &so = *reinterpret_cast<ClassSort<W> *>(raw);
+    ClassTables<W> &tb = *reinterpret_cast<ClassTables<W> *>(raw);
+    __shared__ uint16_t ids[256 * W];  // ranks, bin by bin
+    __shared__ int start[kClassBins + 1];
+    __shared__ int next_bin;
+    const int f = blockIdx.x / parts;
+    const int part = blockIdx.x % parts;
+    const int tid = (int)threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_f = frame_count(counts, f, n_max);
+    const float4 *box4 = reinterpret_cast<const float4 *>(sorted5 + (size_t)f * 5 * n_pad);
+    const int32_t *order_f = order + (size_t)f * n_max;
+    const int32_t *label_f = opt.ranked_label + (size_t)f * n_pad;
+    const float *score_f = opt.ranked_score + (size_t)f * n_pad;
+    uint8_t *keep_f = keep_out + (size_t)f * n_max;
+    const bool ties_ignore = (opt.flags & kExTiesIgnore) != 0;
+
+    {
+        int e[4];
+        unsigned key[4], index[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            e[q] = wave * 256 + q * 64 + lane;
+            key[q] = e[q] < n_f ? class_bin(label_f[e[q]]) : kClassBins - 1u;  // (places behind the count stay behind every box of the last bin)
+            index[q] = (unsigned)e[q];
+        }
+        radix_rank_large<W, 1>(key, index, e, so.keys, so.hist, so.tot, so.wbase, so.match);  // ends with a barrier
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ids[tid + kThreads * q] = (uint16_t)so.keys[tid + kThreads * q];
+    if (wave == 0) {
+        const uint4 all = reinterpret_cast<const uint4 *>(so.tot)[lane];
+        const int sum = (int)(all.x + all.y + all.z + all.w);
+        const int before = (int)wave_inclusive_sum((unsigned)sum) - sum;
+        start[4 * lane] = before;
+        start[4 * lane + 1] = before + (int)all.x;
+        start[4 * lane + 2] = before + (int)(all.x + all.y);
+        start[4 * lane + 3] = before + (int)(all.x + all.y + all.z);
+        if (lane == 0) {
+            start[kClassBins] = n_f;
+            next_bin = part;
+        }
+    }
+    __syncthreads();  // the sort's part of the LDS is free from here on
+    const bool oversized = __syncthreads_or(tid < kClassBins && start[tid + 1] - start[tid] > kClassBin) != 0;
+    if (part == 0) {
+        if (tid == 0) todo[f] = oversized ? 1u : 0u;
+        if (!oversized)
+            for (int i = n_f + tid; i < n_max; i += kThreads) keep_f[i] = 0;
+    }
+    if (oversized) return;
+
+    for (;;) {
+        int bin = 0;
+        if (lane == 0) bin = __hip_atomic_fetch_add(&next_bin, parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        bin = __builtin_amdgcn_readfirstlane(bin);
+        if (bin >= kClassBins) break;
+        const int first = __builtin_amdgcn_readfirstlane(start[bin]);
+        const int size = __builtin_amdgcn_readfirstlane(start[bin + 1]) - first;
+        if (size <= 0) continue;
+
+        // a lane's row of the next tile, fetched a tile ahead
+        float4 row_box;
+        int row_rank, row_index, row_label;
+        float row_score;
+        auto fetch = [&](int t0) __attribute__((always_inline)) {
+            row_rank = ids[first + (t0 + lane < size ? t0 + lane : size - 1)];
+            row_box = box4[row_rank];
+            row_index = order_f[row_rank];
+            row_label = label_f[row_rank];
+            row_score = ties_ignore ? score_f[row_rank] : 0.0f;
+        };
+        // entry `at` of the tables as an outranking box: what the first test needs, and the rest
+        auto first_entry = [&](int at) __attribute__((always_inline)) {
+            const float4 b = tb.box[at];
+            FusedCandidate c;
+            c.x1 = b.x, c.y1 = b.y, c.x2 = b.z, c.y2 = b.w;
+            c.T = tb.T[at];
+            c.area = c.score = 0.0f;
+            c.label = 0;
+            return c;
+        };
+        auto complete = [&](FusedCandidate &c, int at) __attribute__((always_inline)) {
+            c.area = ((c.x2 - c.x1) + opt.offset) * ((c.y2 - c.y1) + opt.offset);
+            c.label = tb.label[at];
+            if (ties_ignore) c.score = score_f[tb.rank[at]];
+        };
+        fetch(0);
+        int kept_rows = 0;  // the bin's survivors so far
+        for (int t0 = 0; t0 < size; t0 += kTile) {
+            const int rows = size - t0 < kTile ? size - t0 : kTile;
+            const bool real = lane < rows;
+            const float4 v = row_box;
+            const int v_rank = row_rank, v_index = row_index, v_label = row_label;
+            const float v_score = row_score;
+            const float v_area = ((v.z - v.x) + opt.offset) * ((v.w - v.y) + opt.offset);
+            const float v_T = fused_threshold<true, IOU>(v_area, opt.boundary);
+            if (t0 + kTile < size) fetch(t0 + kTile);
+            unsigned long long open = rows == kTile ? ~0ull : (1ull << rows) - 1ull;  // rows that no survivor has eliminated
+            const int tile_at = first + kept_rows;
+            // a wavefront's LDS instructions execute in order: the fences only keep the compiler from moving them
+            if (real) {
+                tb.box[tile_at + lane] = v;
+                tb.T[tile_at + lane] = v_T;
+                tb.label[tile_at + lane] = v_label;
+                tb.rank[tile_at + lane] = (uint16_t)v_rank;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // the survivors so far, four at a time (the last one again where the count ends)
+            for (int j = 0; j < kept_rows && open != 0; j += 4) {
+                FusedCandidate c[4];
+                unsigned long long word[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) c[k] = first_entry(first + (j + k < kept_rows ? j + k : kept_rows - 1));
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_score, v_label, c[k], 0.0f, opt));
+                if (((word[0] | word[1] | word[2] | word[3]) & open) != 0) {
+                    asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        word[k] &= open;
+                        if (word[k] != 0) {
+                            complete(c[k], first + (j + k < kept_rows ? j + k : kept_rows - 1));
+                            open &= ~fused_second<IOU, true>(word[k], v, v_area, v_score, v_label, c[k], opt);
+                        }
+                    }
+                }
+            }
+            // the rows among themselves: the first tests of four rows side by side, then in rank order
+            for (int j = 0; j < rows; j += 4) {
+                if (((open >> j) & 15ull) == 0) continue;
+                FusedCandidate c[4];
+                unsigned long long word[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) c[k] = first_entry(tile_at + (j + k < rows ? j + k : rows - 1));
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_score, v_label, c[k], 0.0f, opt));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = j + k;  // < 64; a row at or beyond `rows` is not open
+                    word[k] &= open & (r == kTile - 1 ? 0ull : ~0ull << (r + 1));
+                    if (((open >> r) & 1ull) != 0 && word[k] != 0) {
+                        asm volatile("" ::: "memory");  // keeps this a branch
+                        complete(c[k], tile_at + (r < rows ? r : rows - 1));
+                        open &= ~fused_second<IOU, true>(word[k], v, v_area, v_score, v_label, c[k], opt);
+                    }
+                }
+            }
+            const bool kept = ((open >> lane) & 1ull) != 0;
+            if (real) keep_f[v_index] = kept ? 1 : 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (kept) {
+                const int at = tile_at + __builtin_popcountll(open & ((1ull << lane) - 1ull));
+                tb.box[at] = v;
+                tb.T[at] = v_T;
+                tb.label[at] = v_label;
+                tb.rank[at] = (uint16_t)v_rank;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            kept_rows += __builtin_popcountll(open);
+        }
+    }
+}

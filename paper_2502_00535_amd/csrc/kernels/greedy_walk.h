@@ -150,7 +150,7 @@ template <bool EX, bool IOU, int MODE, bool AUX>
 __global__ void __launch_bounds__(kFusedWaves * 64)
 greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ order,
                     const int32_t *__restrict__ counts, int n_max, int n_pad, NmsThetaConst th, FusedVariant opt,
-                    uint8_t *__restrict__ keep_out)
+                    const unsigned *__restrict__ todo, uint8_t *__restrict__ keep_out)
 {
     constexpr bool kUseT = MODE == kExBoundary;          // the list carries T, else the area
     constexpr bool kUseArea = kUseT && IOU;              // ... and the area as well
@@ -167,6 +167,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
     __shared__ int alive_s[NMS_SORT_CHUNK / kTile];  // compaction: rows alive per tile
     __shared__ int ids_s[NMS_SORT_CHUNK];            // compaction: rank numbers of the rows left
     const int f = blockIdx.x;
+    if (todo != nullptr && todo[f] == 0) return;  // greedy_classes_kernel has settled this frame
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n_f = frame_count(counts, f, n_max);

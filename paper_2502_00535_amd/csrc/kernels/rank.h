@@ -183,7 +183,8 @@ __device__ __forceinline__ void radix_rank_small(unsigned (&key)[4], unsigned (&
 // (one 16-byte read per lane, a DPP scan) and added to its own histogram row, so that the scatter
 // follows without a third barrier: three per pass instead of four.
 // match: W x 2 x 256 lane masks; hist, wbase: W x 256 counters each; tot: 256.
-template <int W>
+// PASSES: 4 sorts by the whole key, fewer by its lowest digits only; tot[] is left with the last pass's digit counts.
+template <int W, int PASSES = 4>
 __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&idx)[4], const int (&e)[4],
                                                  unsigned long long *buf, unsigned *hist, unsigned *tot, unsigned *wbase,
                                                  unsigned long long *match)
@@ -213,7 +214,7 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
         }
     };
 #pragma unroll 1
-    for (int shift = 0; shift < 32; shift += 8) {
+    for (int shift = 0; shift < 8 * PASSES; shift += 8) {
         reinterpret_cast<uint4 *>(myhist)[lane] = make_uint4(0u, 0u, 0u, 0u);
         unsigned d[4], place[4];
 #pragma unroll
@@ -280,7 +281,7 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
             buf[dest] = ((unsigned long long)key[q] << 32) | idx[q];
         }
         __syncthreads();
-        if (shift < 24) {
+        if (shift < 8 * (PASSES - 1)) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const unsigned long long v = buf[e[q]];

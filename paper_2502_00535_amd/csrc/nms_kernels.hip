@@ -53,6 +53,7 @@ __device__ __forceinline__ int frame_count(const int32_t *counts, int f, int n_m
 #include "kernels/reduce.h"
 #include "kernels/greedy_sweep.h"
 #include "kernels/greedy_walk.h"
+#include "kernels/greedy_classes.h"
 #include "kernels/variants.h"
 #include "kernels/early_exit.h"
 #include "kernels/staged.h"
@@ -591,10 +592,10 @@ static int run_greedy_fused(const float *boxes, const float *scores, const int32
     const FusedVariant none = {nullptr, nullptr, 0.0, 1.0f, 0};
     if (th.fast)
         greedy_fused_kernel<false, false, kExBoundary, false><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(
-            w.sorted5, w.order, counts, n_max, n_pad, th, none, keep_out);
+            w.sorted5, w.order, counts, n_max, n_pad, th, none, nullptr, keep_out);
     else
         greedy_fused_kernel<false, false, kExDivideGe, false><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(
-            w.sorted5, w.order, counts, n_max, n_pad, th, none, keep_out);
+            w.sorted5, w.order, counts, n_max, n_pad, th, none, nullptr, keep_out);
     return launch_status();
 }
 
@@ -802,10 +803,31 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         // large batches under the greedy rule: the mask-free walk, one workgroup per frame
         const NmsThetaConst th = nms_make_theta_const(threshold);
         const FusedVariant v = {ranked_score, ranked_class, boundary, opt.pixel_offset, flags};
+        // With labels: class by class; the walk then takes the frames with a class too large for that.
+        // (The tile flags' place in the workspace is free here.)
+        unsigned *todo = nullptr;
+        if (opt.classes && mode == kExBoundary) {
+            todo = w.ytile;
+            int parts = 1;  // workgroups per frame (each sorts the frame's labels): up to four while every one has a compute unit
+            while (parts < 4 && frames * parts * 2 <= 256) parts *= 2;
+            const dim3 classes_grid((unsigned)(frames * parts));
+            begin_launch();
+#define NMS_LAUNCH_CLASSES(IOU_, W_)                                                       \
+    greedy_classes_kernel<IOU_, W_><<<classes_grid, dim3(W_ * 64), 0, s>>>(                \
+        w.sorted5, w.order, counts, n_max, n_pad, parts, v, todo, keep_out)
+            if (n_max <= 1024) {
+                if (iou) NMS_LAUNCH_CLASSES(true, 4); else NMS_LAUNCH_CLASSES(false, 4);
+            } else {
+                if (iou) NMS_LAUNCH_CLASSES(true, 16); else NMS_LAUNCH_CLASSES(false, 16);
+            }
+#undef NMS_LAUNCH_CLASSES
+            st = launch_status();
+            if (st != NMS_OK) return st;
+        }
         begin_launch();
 #define NMS_LAUNCH_WALK(IOU_, MODE_, AUX_)                                                          \
     greedy_fused_kernel<true, IOU_, MODE_, AUX_><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(   \
-        w.sorted5, w.order, counts, n_max, n_pad, th, v, keep_out)
+        w.sorted5, w.order, counts, n_max, n_pad, th, v, todo, keep_out)
 #define NMS_LAUNCH_WALK_MODE(IOU_, AUX_)                                                  \
     do {                                                                                  \
         if (mode == kExBoundary) NMS_LAUNCH_WALK(IOU_, kExBoundary, AUX_);                \
