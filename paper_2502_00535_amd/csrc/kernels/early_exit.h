@@ -438,7 +438,7 @@ early_exit_ranked_kernel(const float *__restrict__ boxes, const float *__restric
         index[q] = (unsigned)key;
         mine[q] = e[q] < n_f ? boxes_f[e[q]] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    radix_rank_large<kEarlyWaves>(key32, index, e, rk.keys, rk.hist, rk.tot, rk.wbase, reinterpret_cast<unsigned long long *>(rk.stage));  // ends with a barrier
+    radix_rank_large<kEarlyWaves>(key32, index, e, n_f, rk.keys, rk.hist, rk.tot, rk.wbase, reinterpret_cast<unsigned long long *>(rk.stage));  // ends with a barrier
 #pragma unroll
     for (int q = 0; q < 4; ++q) rk.stage[e[q]] = mine[q];
     __syncthreads();

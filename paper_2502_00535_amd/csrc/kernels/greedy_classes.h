@@ -9,7 +9,7 @@
 // wavefront settles whole bins, without a barrier: 64 rows at a time, the bin's survivors so far
 // against them, then the rows among themselves in rank order.  Twenty labels leave a twentieth of the
 // pairs, and the bins of a frame run side by side where the walk of greedy_fused_kernel is one chain
-// through all tiles (128 ragged frames of 3000 boxes, IoU, 20 labels, the whole call: 749 -> 91 us).
+// through all tiles (128 ragged frames of 3000 boxes, IoU, 20 labels, the whole call: 749 -> 69 us).
 //
 // A bin is found by a hash of the label, so one bin may hold several labels: the label test stays, and
 // any labels give the same result.  A bin is one wavefront's work and grows with the square of its
@@ -79,10 +79,10 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             e[q] = wave * 256 + q * 64 + lane;
-            key[q] = e[q] < n_f ? class_bin(label_f[e[q]]) : kClassBins - 1u;  // (places behind the count stay behind every box of the last bin)
+            key[q] = e[q] < n_f ? class_bin(label_f[e[q]]) : 0u;
             index[q] = (unsigned)e[q];
         }
-        radix_rank_large<W, 1>(key, index, e, so.keys, so.hist, so.tot, so.wbase, so.match);  // ends with a barrier
+        radix_rank_large<W, 1>(key, index, e, n_f, so.keys, so.hist, so.tot, so.wbase, so.match);  // ends with a barrier
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) ids[tid + kThreads * q] = (uint16_t)so.keys[tid + kThreads * q];

@@ -182,10 +182,14 @@ __device__ __forceinline__ void radix_rank_small(unsigned (&key)[4], unsigned (&
 // per digit, all its reads issued together); the prefix sum over the 256 totals is then done by every wavefront for itself
 // (one 16-byte read per lane, a DPP scan) and added to its own histogram row, so that the scatter
 // follows without a third barrier: three per pass instead of four.
+// Places without an element (e >= cnt) take no part: the elements always stand in the first cnt places.
+// (As keys above all others they had one digit in common, and a wavefront's 64 atomics on one address
+// take turns: 24 frames of 3000 boxes 17.6 -> 13.7 us, full frames unchanged.  radix_rank_small, whose
+// frames are a few wavefronts, gains nothing by it.)
 // match: W x 2 x 256 lane masks; hist, wbase: W x 256 counters each; tot: 256.
 // PASSES: 4 sorts by the whole key, fewer by its lowest digits only; tot[] is left with the last pass's digit counts.
 template <int W, int PASSES = 4>
-__device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&idx)[4], const int (&e)[4],
+__device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&idx)[4], const int (&e)[4], int cnt,
                                                  unsigned long long *buf, unsigned *hist, unsigned *tot, unsigned *wbase,
                                                  unsigned long long *match)
 {
@@ -207,8 +211,8 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
         return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
     };
     // the first lane of a mask adds its population to the histogram and clears the entry
-    auto settle = [&](unsigned long long *t, unsigned d, unsigned long long m, unsigned below) __attribute__((always_inline)) {
-        if (below == 0) {
+    auto settle = [&](unsigned long long *t, unsigned d, unsigned long long m, unsigned below, bool real) __attribute__((always_inline)) {
+        if (below == 0 && real) {
             __hip_atomic_fetch_add(&myhist[d], (unsigned)__popcll(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             __hip_atomic_store(&t[d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
@@ -220,8 +224,8 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
 #pragma unroll
         for (int q = 0; q < 4; ++q) d[q] = (key[q] >> shift) & 255u;
         // (the fences only keep the compiler from reordering: a wavefront's LDS instructions execute in order)
-        or_bit(tab0, d[0]);
-        or_bit(tab1, d[1]);
+        if (e[0] < cnt) or_bit(tab0, d[0]);
+        if (e[1] < cnt) or_bit(tab1, d[1]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         {
             const unsigned long long m0 = load_mask(tab0, d[0]);
@@ -231,12 +235,12 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
             const unsigned b0 = below_in(m0), b1 = below_in(m1);
             place[0] = b0;
             place[1] = (unsigned)__popcll(m01) + b1;
-            settle(tab0, d[0], m0, b0);
-            settle(tab1, d[1], m1, b1);
+            settle(tab0, d[0], m0, b0, e[0] < cnt);
+            settle(tab1, d[1], m1, b1, e[1] < cnt);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        or_bit(tab0, d[2]);
-        or_bit(tab1, d[3]);
+        if (e[2] < cnt) or_bit(tab0, d[2]);
+        if (e[3] < cnt) or_bit(tab1, d[3]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         {
             const unsigned h2 = __hip_atomic_load(&myhist[d[2]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -248,8 +252,8 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
             const unsigned b2 = below_in(m2), b3 = below_in(m3);
             place[2] = h2 + b2;
             place[3] = h3 + (unsigned)__popcll(m23) + b3;
-            settle(tab0, d[2], m2, b2);
-            settle(tab1, d[3], m3, b3);
+            settle(tab0, d[2], m2, b2, e[2] < cnt);
+            settle(tab1, d[3], m3, b3, e[3] < cnt);
         }
         __syncthreads();
         if (tid < 256) {
@@ -278,7 +282,7 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const unsigned dest = __hip_atomic_load(&mybase[d[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + place[q];
-            buf[dest] = ((unsigned long long)key[q] << 32) | idx[q];
+            if (e[q] < cnt) buf[dest] = ((unsigned long long)key[q] << 32) | idx[q];
         }
         __syncthreads();
         if (shift < 8 * (PASSES - 1)) {
@@ -345,7 +349,7 @@ rank_chunk_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
     if constexpr (kSmall)
         radix_rank_small<P / 256>(key32, index, e, keys, hist, wbase, reinterpret_cast<unsigned long long *>(stage));
     else
-        radix_rank_large<P / 256>(key32, index, e, keys, hist, tot, wbase, reinterpret_cast<unsigned long long *>(stage));
+        radix_rank_large<P / 256>(key32, index, e, cnt, keys, hist, tot, wbase, reinterpret_cast<unsigned long long *>(stage));
     // both end with a barrier; keys[] is sorted
 
     int32_t *order_f = order + (size_t)f * n_max;
