@@ -172,7 +172,7 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
                 for (int k = 0; k < 4; ++k) c[k] = first_entry(first + (j + k < kept_rows ? j + k : kept_rows - 1));
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_score, v_label, c[k], 0.0f, opt));
+                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_T, v_score, v_label, c[k], 0.0f, opt));
                 if (((word[0] | word[1] | word[2] | word[3]) & open) != 0) {
                     asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
@@ -194,7 +194,7 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
                 for (int k = 0; k < 4; ++k) c[k] = first_entry(tile_at + (j + k < rows ? j + k : rows - 1));
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_score, v_label, c[k], 0.0f, opt));
+                    word[k] = __ballot(fused_first<true, IOU, kExBoundary, true>(v, v_area, v_T, v_score, v_label, c[k], 0.0f, opt));
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int r = j + k;  // < 64; a row at or beyond `rows` is not open

@@ -70,9 +70,11 @@ __device__ __forceinline__ float fused_threshold(float area, double boundary)
 
 // First test of a pair, decisive but for IoU in boundary form, where a hit only means "maybe", and
 // for the scores and labels of AUX in boundary form.  One floor is enough there: a negative width
-// times a floored height reaches no positive T, and T = -infinity passes everything on.
+// times a floored height reaches no positive T, and T = -infinity passes everything on.  The union of
+// IoU is no smaller than either box, so the victim's own T (v_T) bounds the intersection too: with the
+// candidate's alone every box that contains the candidate is a "maybe".
 template <bool EX, bool IOU, int MODE, bool AUX>
-__device__ __forceinline__ bool fused_first(const float4 v, float v_area, float v_score, int v_label,
+__device__ __forceinline__ bool fused_first(const float4 v, float v_area, float v_T, float v_score, int v_label,
                                             const FusedCandidate &c, float theta, const FusedVariant &o)
 {
     if (!EX) {
@@ -83,7 +85,7 @@ __device__ __forceinline__ bool fused_first(const float4 v, float v_area, float 
     if (MODE != kExBoundary) iw = fmaxf(0.0f, iw);
     const float ih = fmaxf(0.0f, (fminf(v.w, c.y2) - fmaxf(v.y, c.y1)) + o.offset);
     const float inter = iw * ih;
-    if (MODE == kExBoundary) return inter >= c.T;
+    if (MODE == kExBoundary) return inter >= (IOU ? fmaxf(c.T, v_T) : c.T);
     const float denom = IOU ? (v_area + c.area) - inter : c.area;
     bool hit = MODE == kExDivideGe ? !(inter / denom < theta) : inter / denom > theta;
     if (AUX) {
@@ -122,10 +124,10 @@ __device__ __forceinline__ unsigned long long fused_second(unsigned long long wo
 // float64 compare of IoU, scores, labels -- sits behind a wave-uniform branch (every pair through the
 // float64 compare: 128 frames of 3000 boxes, IoU, 20 labels, 874 us for the call; so: 749).
 template <bool EX, bool IOU, int MODE, bool AUX>
-__device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_score,
-                                                         int v_label, const FusedCandidate &c, float theta, const FusedVariant &o)
+__device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_T,
+                                                         float v_score, int v_label, const FusedCandidate &c, float theta, const FusedVariant &o)
 {
-    unsigned long long word = __ballot(fused_first<EX, IOU, MODE, AUX>(v, v_area, v_score, v_label, c, theta, o)) & open;
+    unsigned long long word = __ballot(fused_first<EX, IOU, MODE, AUX>(v, v_area, v_T, v_score, v_label, c, theta, o)) & open;
     if (kFusedSecond<EX, IOU, MODE, AUX> && word != 0) {
         asm volatile("" ::: "memory");  // keeps this a branch
         word = fused_second<IOU, AUX>(word, v, v_area, v_score, v_label, c, o);
@@ -256,7 +258,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
             unsigned long long any = 0;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                word[i] = __ballot(fused_first<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].score, self[i].label, c, th.theta, opt));
+                word[i] = __ballot(fused_first<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].T, self[i].score, self[i].label, c, th.theta, opt));
                 if (kSecond) {
                     word[i] &= ~out[i];
                     any |= word[i];
@@ -327,7 +329,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                 const int count = g > 0 ? __builtin_amdgcn_readfirstlane(count_s[pending]) : 0;
                 unsigned long long part = 0;
                 for (int k = wave; k < count; k += kFusedWaves)
-                    part |= fused_word<EX, IOU, MODE, AUX>(~part, row_box, row.area, row.score, row.label, entry(pending, k),
+                    part |= fused_word<EX, IOU, MODE, AUX>(~part, row_box, row.area, row.T, row.score, row.label, entry(pending, k),
                                                            th.theta, opt);
                 if (lane == 0) part_s[wave] = part;
                 FusedCandidate victim[kTile / kFusedWaves];
@@ -338,7 +340,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                     const int r = wave + kFusedWaves * j;
                     const unsigned long long hitters = fused_word<EX, IOU, MODE, AUX>(
                         (1ull << r) - 1ull, make_float4(victim[j].x1, victim[j].y1, victim[j].x2, victim[j].y2), victim[j].area,
-                        victim[j].score, victim[j].label, row, th.theta, opt);
+                        victim[j].T, victim[j].score, victim[j].label, row, th.theta, opt);
                     if (lane == 0) hitters_s[r] = hitters;
                 }
             }
