@@ -9,6 +9,11 @@ from __future__ import annotations
 import ctypes
 import os
 
+# torch first: its wheel carries its own HIP runtime (soname libamdhip64.so.7).  Once
+# that copy is in the process the loader binds the library below to it; loaded the other
+# way round, the system runtime would come in as a second, unusable instance.
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libnms_mi355x.so")
 
@@ -56,11 +61,6 @@ def library_path() -> str:
 
 
 def _load() -> ctypes.CDLL:
-    # torch first: its wheel carries its own HIP runtime (soname libamdhip64.so.7).  Once
-    # that copy is in the process the loader binds this library to it; loaded the other
-    # way round, the system runtime would come in as a second, unusable instance.
-    import torch  # noqa: F401
-
     if not os.path.exists(_LIB_PATH):
         raise ImportError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2502_00535_amd.build` "
@@ -147,6 +147,12 @@ def _on_device(t) -> bool:
     return t.is_cuda
 
 
+# A call on a small frame is as long as its marshalling (10 us of it at 360 boxes before the helpers below
+# compared dtypes as objects, passed addresses as plain integers and asked for the raw stream): they
+# build nothing that the call does not need.
+_DTYPES = {"float32": torch.float32, "int32": torch.int32, "int64": torch.int64, "uint8": torch.uint8}
+
+
 def _ptr(t, dtype_name: str | None, what: str, need: int = 0):
     """Device pointer of a contiguous CUDA/HIP tensor (None -> NULL).  `need` is the number
     of elements the library will read or write there: the C ABI takes bare pointers and
@@ -154,8 +160,6 @@ def _ptr(t, dtype_name: str | None, what: str, need: int = 0):
     kernel could run past its end."""
     if t is None:
         return None
-    import torch
-
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{what}: expected a torch tensor")
     if t.numel() < need:
@@ -164,9 +168,15 @@ def _ptr(t, dtype_name: str | None, what: str, need: int = 0):
         raise ValueError(f"{what}: tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{what}: tensor must be contiguous")
-    if dtype_name is not None and str(t.dtype) != f"torch.{dtype_name}":
+    if dtype_name is not None and t.dtype != _DTYPES[dtype_name]:
         raise TypeError(f"{what}: expected dtype {dtype_name}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _boxes(n_max, frames):
+    """frames * n_max, the element count of the per-box buffers; 0 when the library will refuse the sizes anyway."""
+    n_max, frames = int(n_max), int(frames)
+    return frames * n_max if n_max >= 0 and frames >= 0 else 0
 
 
 def _sizes(n_max, frames):
@@ -185,11 +195,9 @@ def _ws(t):
 
 
 def _stream(stream):
-    import torch
-
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _check(status: int, where: str):
@@ -279,7 +287,7 @@ def nms_reduce_batched(mask, order, counts, n_max, frames, keep_out, stream=None
 
 
 def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n, 1)
+    fn_ = _boxes(n, 1)
     w, wb = _ws(workspace)
     _check(lib.nms_run_ws(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_), int(n),
                           float(threshold), _ptr(keep_out, "uint8", "keep_out", fn_), w, wb, _stream(stream)),
@@ -287,7 +295,7 @@ def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
 
 
 def nms_run_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
@@ -313,7 +321,7 @@ class RunPlan:
         self._entry = entry
         self._keepalive = (boxes, scores, counts, keep_out, workspace)
         w, wb = _ws(workspace)
-        fn_, _, _ = _sizes(n_max, frames)
+        fn_ = _boxes(n_max, frames)
         self._args = (_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                       _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
                       _ptr(keep_out, "uint8", "keep_out", fn_), w, wb, _stream(stream))
@@ -326,7 +334,7 @@ class RunPlan:
 
 
 def nms_run_ranked_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_ranked_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                       _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
@@ -335,7 +343,7 @@ def nms_run_ranked_batched(boxes, scores, counts, n_max, frames, threshold, keep
 
 
 def nms_run_direct_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     _check(lib.nms_run_direct_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                       _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
                                       _ptr(keep_out, "uint8", "keep_out", fn_), _stream(stream)),
@@ -343,7 +351,7 @@ def nms_run_direct_batched(boxes, scores, counts, n_max, frames, threshold, keep
 
 
 def nms_run_batched_profiled(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, events, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     """events: three raw hipEvent_t handles (ints) or None entries."""
     w, wb = _ws(workspace)
     ev = (ctypes.c_void_p * 3)(*[ctypes.c_void_p(e) if e else None for e in events])
@@ -372,7 +380,7 @@ def nms_greedy_workspace_bytes(n_max: int, frames: int) -> int:
 
 
 def nms_run_greedy_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_greedy_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                       _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
@@ -381,7 +389,7 @@ def nms_run_greedy_batched(boxes, scores, counts, n_max, frames, threshold, keep
 
 
 def nms_run_early_exit_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_early_exit_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                           _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
@@ -390,7 +398,7 @@ def nms_run_early_exit_batched(boxes, scores, counts, n_max, frames, threshold, 
 
 
 def nms_run_greedy_fused_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_greedy_fused_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                             _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
@@ -419,11 +427,11 @@ def nms_ex_workspace_bytes(n_max: int, frames: int) -> int:
 def nms_run_ex_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, rule="paper",
                        measure="outranking_area", compare="ge", ties="index", pixel_offset=1.0, classes=None,
                        stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     cls = _ptr(classes, "int32", "classes", fn_)
     opt = NmsOptions(RULES[rule], MEASURES[measure], COMPARES[compare], TIES[ties], float(pixel_offset), 0,
-                     cls.value if cls is not None else None)
+                     cls)
     _check(lib.nms_run_ex_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                   _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
                                   ctypes.byref(opt), _ptr(keep_out, "uint8", "keep_out", fn_), w, wb, _stream(stream)),
@@ -440,7 +448,7 @@ def nms_shutdown():
 
 
 def nms_run(boxes, scores, n, threshold, keep_out, stream=None):
-    fn_, fp_, fm_ = _sizes(n, 1)
+    fn_ = _boxes(n, 1)
     _check(lib.nms_run(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_), int(n),
                        float(threshold), _ptr(keep_out, "uint8", "keep_out", fn_), _stream(stream)), "nms_run")
 
@@ -449,7 +457,7 @@ NMS_STATIC_SCRATCH_BYTES = 4194304
 
 
 def nms_run_static_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, stream=None):
-    fn_, fp_, fm_ = _sizes(n_max, frames)
+    fn_ = _boxes(n_max, frames)
     _check(lib.nms_run_static_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
                                       _ptr(counts, "int32", "counts", int(frames)), int(n_max), int(frames), float(threshold),
                                       _ptr(keep_out, "uint8", "keep_out", fn_), _stream(stream)),
