@@ -296,6 +296,15 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
     }
 }
 
+// What the variants need in rank order besides the box table (null pointers: not wanted).
+struct RankExtras {
+    const int32_t *classes;
+    float *score;
+    int32_t *label;
+    float *area;
+    float offset;
+};
+
 // One workgroup ranks one chunk of up to kChunk boxes of one frame: P = 4 * blockDim.x
 // elements (P a multiple of 256, 256..4096), four per thread, sorted by radix_rank_small or radix_rank_large.
 // With a single chunk the kernel also writes order / sorted5 (and, for the fused path,
@@ -310,7 +319,7 @@ rank_chunk_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
                   const int32_t *__restrict__ counts, int n_max, int n_pad, int n_chunks,
                   int32_t *__restrict__ order, float *__restrict__ sorted5,
                   unsigned long long *__restrict__ keys_ws, uint8_t *__restrict__ keep_preset,
-                  float4 *__restrict__ ysc, unsigned *__restrict__ ytile, float *__restrict__ tsc, double m)
+                  float4 *__restrict__ ysc, unsigned *__restrict__ ytile, float *__restrict__ tsc, double m, RankExtras ex)
 {
     __shared__ unsigned long long keys[P];
     __shared__ __align__(16) unsigned hist[(P / 256) * 256];  // one row of 256 digit counts per wavefront
@@ -380,6 +389,15 @@ rank_chunk_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
                     regular = emit_ranked_box(b[q], idx[q], r, n_pad, order_f, sorted_f, ysc_f, tsc_f, m);
                 else
                     emit_padding_row(r, n_pad, sorted_f, ysc_f, tsc_f);
+                if (ex.score != nullptr) {
+                    // (a launch of its own for these: 5 us at 128 x 3000 boxes)
+                    const bool real = idx[q] >= 0;
+                    const float4 bb = real ? b[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const size_t at = (size_t)f * n_pad + r;
+                    ex.score[at] = real ? scores_f[idx[q]] : -INFINITY;
+                    if (ex.classes != nullptr) ex.label[at] = real ? ex.classes[(size_t)f * n_max + idx[q]] : 0;
+                    ex.area[at] = ((bb.z - bb.x) + ex.offset) * ((bb.w - bb.y) + ex.offset);
+                }
                 if (ytile_f != nullptr) {
                     const unsigned long long irregular = __ballot(!regular);
                     if (lane == 0) ytile_f[r / kTile] = irregular == 0 ? 1u : 0u;

@@ -21,15 +21,6 @@
 constexpr int kCountThreads = 1024;
 constexpr int kCountWaves = kCountThreads / 64;
 
-// What the variants need in rank order besides the box table (null pointers: not wanted).
-struct RankExtras {
-    const int32_t *classes;
-    float *score;
-    int32_t *label;
-    float *area;
-    float offset;
-};
-
 template <int kElems>
 __global__ void __launch_bounds__(kCountThreads)
 rank_count_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,

@@ -128,11 +128,11 @@ int count_rank_launch(const float *boxes, const float *scores, const int32_t *co
 
 int rank_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
                 int32_t *order, float *sorted5, void *workspace, uint8_t *keep_preset, float4 *ysc, unsigned *ytile,
-                hipStream_t stream, float *tsc = nullptr, double m = 0.0)
+                hipStream_t stream, float *tsc = nullptr, double m = 0.0,
+                const RankExtras &extras = {nullptr, nullptr, nullptr, nullptr, 0.0f})  // extras: frames of one chunk only
 {
     if (ysc == nullptr && ytile == nullptr && tsc == nullptr && nms_use_count_rank(n_max, frames, kChunk))
-        return count_rank_launch(boxes, scores, counts, n_max, frames, order, sorted5, keep_preset,
-                                 {nullptr, nullptr, nullptr, nullptr, 0.0f}, stream);
+        return count_rank_launch(boxes, scores, counts, n_max, frames, order, sorted5, keep_preset, extras, stream);
     const int n_pad = nms_padded_n(n_max);
     // one chunk up to kChunk boxes; beyond that, chunks of kMergeChunk (more workgroups, shorter sorts) and a merge
     const int n_chunks = n_max <= kChunk ? 1 : (n_max + kMergeChunk - 1) / kMergeChunk;
@@ -143,7 +143,8 @@ int rank_launch(const float *boxes, const float *scores, const int32_t *counts, 
     begin_launch();
 #define NMS_LAUNCH_RANK(P_, STAGE_)                                                                    \
     rank_chunk_kernel<P_, STAGE_><<<dim3(n_chunks, frames), dim3(P_ / 4), 0, stream>>>(                \
-        boxes, scores, counts, n_max, n_pad, n_chunks, order, sorted5, keys_ws, keep_preset, ysc, ytile, tsc, m)
+        boxes, scores, counts, n_max, n_pad, n_chunks, order, sorted5, keys_ws, keep_preset, ysc, ytile, tsc, m, \
+        extras)
     if (n_chunks > 1) NMS_LAUNCH_RANK(kMergeChunk, false);
     else if (threads == 64) NMS_LAUNCH_RANK(256, true);
     else if (threads == 128) NMS_LAUNCH_RANK(512, true);
@@ -753,14 +754,10 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     hipStream_t s = static_cast<hipStream_t>(stream);
     // under the paper's rule the row reduction is folded into the map kernel: keep_out starts at 1
     const bool fold = opt.rule == NMS_RULE_PAPER;
-    if (nms_use_count_rank(n_max, frames, kChunk)) {  // one launch for ranks and what follows them
-        st = count_rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, fold ? keep_out : nullptr,
-                               {opt.classes, ranked_score, ranked_class, ranked_area, opt.pixel_offset}, s);
-        if (st != NMS_OK) return st;
-    } else {
-        st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
-                         nullptr, s);
-        if (st != NMS_OK) return st;
+    st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
+                     nullptr, s, nullptr, 0.0, {opt.classes, ranked_score, ranked_class, ranked_area, opt.pixel_offset});
+    if (st != NMS_OK) return st;
+    if (n_max > kChunk) {  // several chunks: the merged ranks' scores, labels and areas by a launch of their own
         begin_launch();
         gather_ranked_kernel<<<dim3((n_pad + 255) / 256, frames), dim3(256), 0, s>>>(
             w.order, scores, opt.classes, counts, w.sorted5, opt.pixel_offset, n_max, n_pad, ranked_score, ranked_class,
