@@ -68,8 +68,8 @@ __device__ __forceinline__ float fused_threshold(float area, double boundary)
     return t1 > 0.0f ? t1 : -INFINITY;
 }
 
-// First test of a pair, decisive but for IoU in boundary form, where a hit only means "maybe", and
-// for the scores and labels of AUX in boundary form.  One floor is enough there: a negative width
+// First test of a pair, decisive but for AUX in boundary form, where scores and labels are still to be
+// looked at and a hit under IoU only means "maybe".  One floor is enough there: a negative width
 // times a floored height reaches no positive T, and T = -infinity passes everything on.  The union of
 // IoU is no smaller than either box, so the victim's own T (v_T) bounds the intersection too: with the
 // candidate's alone every box that contains the candidate is a "maybe".
@@ -82,11 +82,12 @@ __device__ __forceinline__ bool fused_first(const float4 v, float v_area, float 
         return nms_eliminates_exact(v.x, v.y, v.z, v.w, c.x1, c.y1, c.x2, c.y2, c.area, theta);
     }
     float iw = (fminf(v.z, c.x2) - fmaxf(v.x, c.x1)) + o.offset;
-    if (MODE != kExBoundary) iw = fmaxf(0.0f, iw);
+    if (MODE != kExBoundary || (IOU && !AUX)) iw = fmaxf(0.0f, iw);
     const float ih = fmaxf(0.0f, (fminf(v.w, c.y2) - fmaxf(v.y, c.y1)) + o.offset);
     const float inter = iw * ih;
-    if (MODE == kExBoundary) return inter >= (IOU ? fmaxf(c.T, v_T) : c.T);
     const float denom = IOU ? (v_area + c.area) - inter : c.area;
+    if (MODE == kExBoundary && IOU && !AUX) return (double)inter >= o.boundary * (double)denom;
+    if (MODE == kExBoundary) return inter >= (IOU ? fmaxf(c.T, v_T) : c.T);
     bool hit = MODE == kExDivideGe ? !(inter / denom < theta) : inter / denom > theta;
     if (AUX) {
         hit = hit && ((o.flags & kExTiesIgnore) == 0 || c.score > v_score);
@@ -97,7 +98,7 @@ __device__ __forceinline__ bool fused_first(const float4 v, float v_area, float 
 
 // Is there anything to decide after fused_first?
 template <bool EX, bool IOU, int MODE, bool AUX>
-constexpr bool kFusedSecond = EX && MODE == kExBoundary && (IOU || AUX);
+constexpr bool kFusedSecond = EX && MODE == kExBoundary && AUX;
 
 // What is left to decide for the lanes of `word` (not 0) that fused_first let through.
 template <bool IOU, bool AUX>
@@ -120,9 +121,10 @@ __device__ __forceinline__ unsigned long long fused_second(unsigned long long wo
 
 // Does candidate c eliminate the victim?  The lane mask over the lanes of `open` (the others do not
 // matter).  !EX: the default measure (MODE kExBoundary = the division-free form of nms_pair.h, else the
-// literal division).  EX: the variants.  Few rows pass the first test, so what follows it -- the
-// float64 compare of IoU, scores, labels -- sits behind a wave-uniform branch (every pair through the
-// float64 compare: 128 frames of 3000 boxes, IoU, 20 labels, 874 us for the call; so: 749).
+// literal division).  EX: the variants.  With scores or labels to look at, what follows the first test sits
+// behind a wave-uniform branch (40 frames of 4096 boxes, IoU, 5 labels, the whole call: 1284 -> 444 us, the
+// binning of greedy_classes_kernel included).  IoU alone takes the float64 compare for every pair: the branch gains 1 % where
+// few pairs hit (64 x 2100) and costs 5 to 9 % where many do (300 x 600: 52 -> 57 us).
 template <bool EX, bool IOU, int MODE, bool AUX>
 __device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_T,
                                                          float v_score, int v_label, const FusedCandidate &c, float theta, const FusedVariant &o)
@@ -154,7 +156,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                     const int32_t *__restrict__ counts, int n_max, int n_pad, NmsThetaConst th, FusedVariant opt,
                     const unsigned *__restrict__ todo, uint8_t *__restrict__ keep_out)
 {
-    constexpr bool kUseT = MODE == kExBoundary;          // the list carries T, else the area
+    constexpr bool kUseT = MODE == kExBoundary && (!IOU || AUX);  // the list carries T, else the area
     constexpr bool kUseArea = kUseT && IOU;              // ... and the area as well
     constexpr bool kSecond = kFusedSecond<EX, IOU, MODE, AUX>;
     constexpr int kTileBuf = kWalkLists;                 // one more buffer of the same layout: the rows of the tile being settled
@@ -208,7 +210,7 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
             FusedCandidate me;
             me.x1 = vb[i].x, me.y1 = vb[i].y, me.x2 = vb[i].z, me.y2 = vb[i].w;
             me.area = EX ? ((vb[i].z - vb[i].x) + opt.offset) * ((vb[i].w - vb[i].y) + opt.offset) : area[r];
-            me.T = MODE == kExBoundary ? fused_threshold<EX, IOU>(me.area, EX ? opt.boundary : th.m) : 0.0f;
+            me.T = kUseT ? fused_threshold<EX, IOU>(me.area, EX ? opt.boundary : th.m) : 0.0f;
             me.score = AUX ? opt.ranked_score[(size_t)f * n_pad + r] : 0.0f;
             me.label = (AUX && (opt.flags & kExClasses)) ? opt.ranked_label[(size_t)f * n_pad + r] : 0;
             self[i] = me;
