@@ -13,12 +13,11 @@
 //
 // A bin is found by a hash of the label, so one bin may hold several labels: the label test stays, and
 // any labels give the same result.  A bin is one wavefront's work and grows with the square of its
-// size; a frame with a bin of more than kClassBin rows is left to the walk (todo[f] = 1).
+// size; a frame with a bin of more than nms_class_bin_limit() rows is left to the walk (todo[f] = 1).
 //
 // LDS: a bin's survivors are kept, packed, at the front of its own stretch of the tables; the tile in
 // work sits right behind them (survivors + rows of the tile never exceed the rows seen so far).
 constexpr int kClassBins = 256;
-constexpr int kClassBin = 1024;
 
 __device__ __forceinline__ unsigned class_bin(int label)
 {
@@ -100,7 +99,7 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
         }
     }
     __syncthreads();  // the sort's part of the LDS is free from here on
-    const bool oversized = __syncthreads_or(tid < kClassBins && start[tid + 1] - start[tid] > kClassBin) != 0;
+    const bool oversized = __syncthreads_or(tid < kClassBins && start[tid + 1] - start[tid] > nms_class_bin_limit(n_f)) != 0;
     if (part == 0) {
         if (tid == 0) todo[f] = oversized ? 1u : 0u;
         if (!oversized)

@@ -104,6 +104,30 @@ NMS_HD int nms_count_rank_elements(int n_max, int frames)
     return boxes >= 512 * 128 ? 128 : (boxes >= 256 * 64 ? 64 : 16);
 }
 
+// ---- greedy rule with labels ----------------------------------------------------------------------
+// Large batches under the greedy rule with labels: class by class (greedy_classes_kernel) for frames
+// of more than two tiles.  Shorter frames are one or two rounds of the walk, and its launch would follow
+// anyway (IoU, whole call, walk alone against class by class: 2048 x 64, 20 labels 42 us / 60; 1024 x 128,
+// 20 labels 33 / 38, 80 labels 33 / 49; 820 x 160, 20 labels 70 / 40).
+NMS_HD bool nms_use_class_route(int n_max)
+{
+    return n_max > 128;
+}
+
+// The largest bin of labels that is settled there, in a frame of n_f boxes; a frame with a larger one is
+// left to the walk.  A bin is one wavefront's chain and grows with the square of its rows, the walk
+// has sixteen wavefronts on the whole frame: the line is a share of the frame.  Class by class against
+// the walk behind the launch that finds nothing to settle, IoU, whole call, scenes where much / little is
+// eliminated: 128 x 3000 in bins of 1000 502 / 1045 us against 207 / 527, of 600 221 / 309 against 283 /
+// 550; 128 x 1024 in bins of 1024 190 / 541 against 61 / 129, of 205 60 / 68 against 95 / 136.  In short frames
+// bins beyond a quarter still pay: 263 x 500 in bins of 167 43 / 58 against 77 / 115, of 500 78 / 191 against
+// 59 / 113; 342 x 384 in bins of 384 59 / 128 against 50 / 85; 1024 x 256 in bins of 256 48 / 100 against 65 / 95.
+NMS_HD int nms_class_bin_limit(int n_f)
+{
+    const int quarter = n_f / 4;
+    return quarter > 288 ? quarter : 288;
+}
+
 // ---- which kernels a whole-path call runs ------------------------------------------------------
 // All four routes return the same keep vector (the paper's rule, section "Algorithm Correctness");
 // they differ in what they launch.  Values of nms_route() in the C ABI.

@@ -800,10 +800,11 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         // large batches under the greedy rule: the mask-free walk, one workgroup per frame
         const NmsThetaConst th = nms_make_theta_const(threshold);
         const FusedVariant v = {ranked_score, ranked_class, boundary, opt.pixel_offset, flags};
-        // With labels: class by class; the walk then takes the frames with a class too large for that.
+        // With labels: class by class; the walk then takes the frames with a class too large for that
+        // (a launch of 4 us that often finds nothing to do, but only the device knows the labels).
         // (The tile flags' place in the workspace is free here.)
         unsigned *todo = nullptr;
-        if (opt.classes && mode == kExBoundary) {
+        if (opt.classes && mode == kExBoundary && nms_use_class_route(n_max)) {
             todo = w.ytile;
             int parts = 1;  // workgroups per frame (each sorts the frame's labels): up to four while every one has a compute unit
             while (parts < 4 && frames * parts * 2 <= 256) parts *= 2;

@@ -83,6 +83,12 @@ int main(int argc, char **argv)
         printf("taken %lld bad %lld\n", taken, bad);
         return 0;
     }
+    if (!strcmp(argv[1], "classes")) {
+        // largest bin of labels that one wavefront settles, for every frame length given on stdin
+        int n;
+        while (scanf("%d", &n) == 1) printf("%d %d\n", nms_use_class_route(n) ? 1 : 0, nms_class_bin_limit(n));
+        return 0;
+    }
     if (!strcmp(argv[1], "layout")) {
         int n_max, frames, chunk;
         while (scanf("%d %d %d", &n_max, &frames, &chunk) == 3) {

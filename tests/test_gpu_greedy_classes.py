@@ -1,5 +1,5 @@
 """The greedy rule with labels on large batches: every class by a wavefront of its own, frames with a
-class beyond 1024 boxes by the walk, against the oracle.  Bar: 0 differing keep bits."""
+class beyond 288 boxes and a quarter of the frame by the walk, against the oracle.  Bar: 0 differing keep bits."""
 import numpy as np
 import pytest
 
@@ -15,7 +15,7 @@ def labels_of(kind, rng, n):
         return rng.integers(0, 20, n)
     if kind == "one":
         return np.zeros(n, np.int64)
-    if kind == "largest_bin":  # 1024 boxes of one label: the most that a wavefront takes
+    if kind == "largest_bin":  # 1024 boxes of one label: the most that a wavefront takes, in a frame of 4096
         return rng.permutation(np.where(np.arange(n) < 1024, 3, 4 + np.arange(n) % 90))
     if kind == "one_more":
         return rng.permutation(np.where(np.arange(n) < 1025, 3, 4 + np.arange(n) % 90))
@@ -49,3 +49,62 @@ def test_labels(nms, oracle, n_max, frames):  # noqa: F811
             want = oracle_ex(oracle, boxes, scores, classes, 0.45, opts, counts if ragged else None, workers=8)[which]
             got = dev.run(0.45, opts)
             assert np.array_equal(got, want), f"{opts}: {(got != want).sum()} differing keep bits"
+
+
+def largest_bin(n):
+    return max(288, n // 4)  # the rule swept in tests/test_host_logic.py
+
+
+# both sides of the shortest frame taken class by class; frames that are one bin, at its bound and one beyond; bins
+# at the bound and one beyond in frames of 1024 boxes and where the bound begins to follow the frame's length
+@pytest.mark.parametrize("n_max,frames", [(128, 1024), (129, 1017), (288, 456), (289, 454), (1024, 128), (1152, 114), (1160, 113)])
+def test_bins_at_the_bound(nms, oracle, n_max, frames):  # noqa: F811
+    rng = np.random.default_rng(n_max)
+    distinct = 6
+    boxes = np.zeros((distinct, n_max, 4), np.float32)
+    scores = np.zeros((distinct, n_max), np.float32)
+    classes = np.zeros((distinct, n_max), np.int32)
+    counts = np.array([n_max, n_max, n_max, n_max - 1, n_max // 2, 63], np.int32)
+    for f in range(distinct):
+        boxes[f], scores[f] = random_frame(31 * n_max + f, n_max, extent=250 + 50 * f, max_side=120, integer=f % 2 == 0,
+                                           score_levels=(0, 40)[f % 2])
+        rows = min(n_max, largest_bin(int(counts[f])) + f % 2)
+        classes[f, : counts[f]] = rng.permutation(np.where(np.arange(counts[f]) < rows, 7, 8 + np.arange(counts[f]) % 60))
+    which = np.arange(frames) % distinct
+    dev = ExFrames(nms, boxes[which], scores[which], classes[which], counts[which])
+    for measure, compare, ties, offset in (("iou", "gt", "index", 0.0), ("outranking_area", "ge", "ignore", 1.0)):
+        opts = dict(rule="greedy", measure=measure, compare=compare, ties=ties, pixel_offset=offset, labelled=True)
+        print(f"case n_max={n_max} frames={frames} {opts}", flush=True)
+        want = oracle_ex(oracle, boxes, scores, classes, 0.45, opts, counts, workers=8)[which]
+        got = dev.run(0.45, opts)
+        assert np.array_equal(got, want), f"{opts}: {(got != want).sum()} differing keep bits"
+
+
+@pytest.mark.parametrize("n,frames", [(640, 205), (1024, 128)])
+def test_one_label_costs_little_more_than_none(nms, n, frames):  # noqa: F811
+    """All boxes of one label are one bin: as one wavefront's chain 3 to 5 times the unlabelled call, through the
+    walk 1.2 to 1.4 times.  The bound lies between, well beyond what a run's times differ."""
+    import torch
+
+    dev = torch.device("cuda:0")
+    frame = random_frame(3, n, extent=2000, max_side=120, integer=False, score_levels=0)
+    boxes = torch.from_numpy(np.tile(frame[0], (frames, 1, 1))).to(dev)
+    scores = torch.from_numpy(np.tile(frame[1], (frames, 1))).to(dev)
+    keep = torch.empty((2, frames, n), dtype=torch.uint8, device=dev)
+    ws = torch.empty(nms.nms_ex_workspace_bytes(n, frames), dtype=torch.uint8, device=dev)
+    ones = torch.ones((frames, n), dtype=torch.int32, device=dev)
+    times = [[], []]
+    for _ in range(6):
+        for i, classes in enumerate((None, ones)):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(20):
+                nms.nms_run_ex_batched(boxes, scores, None, n, frames, 0.5, keep[i], ws, rule="greedy", measure="iou",
+                                       compare="gt", pixel_offset=0.0, classes=classes)
+            end.record()
+            end.synchronize()
+            times[i].append(begin.elapsed_time(end) / 20)
+    assert torch.equal(keep[0], keep[1])
+    plain, labelled = (min(t) for t in times)
+    print(f"n={n} frames={frames}: {1e3 * plain:.1f} us without labels, {1e3 * labelled:.1f} us with one", flush=True)
+    assert labelled < 2.0 * plain

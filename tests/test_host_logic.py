@@ -56,6 +56,17 @@ def test_small_frames_shares_fit_the_kernels(driver):
     assert taken > 100000
 
 
+def test_large_bins_of_labels_are_left_to_the_walk(driver):
+    """Greedy rule with labels: a bin is one wavefront's chain, so its bound is a share of the frame and no
+    bin of a long frame beyond a quarter of it is settled that way; frames of up to two tiles never are."""
+    lengths = list(range(1, 4097))
+    rows = [list(map(int, r.split())) for r in run(driver, "classes", stdin="\n".join(map(str, lengths))).split("\n") if r]
+    limits = dict(zip(lengths, (r[1] for r in rows)))
+    assert [n for n, r in zip(lengths, rows) if r[0]] == lengths[128:]
+    assert all(limits[n] == max(288, n // 4) for n in lengths)
+    assert limits[1024] < 1024 // 3 and limits[3000] < 3000 // 3
+
+
 def test_workspace_layout_matches_the_size_helper(driver):
     import paper_2502_00535_amd.binding as nms
 
