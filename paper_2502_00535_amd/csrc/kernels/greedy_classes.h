@@ -5,15 +5,19 @@
 
 // With labels a box eliminates boxes of its own label only, so the sequential rule falls apart into
 // one short procedure per label.  A workgroup puts the ranked boxes of its frame into 256 bins by
-// label (one more pass of the rank step's stable radix sort, so a bin stays in rank order) and each
+// label (one pass of a stable counting sort, so a bin stays in rank order) and each
 // wavefront settles whole bins, without a barrier: 64 rows at a time, the bin's survivors so far
 // against them, then the rows among themselves in rank order.  Twenty labels leave a twentieth of the
 // pairs, and the bins of a frame run side by side where the walk of greedy_fused_kernel is one chain
-// through all tiles (128 ragged frames of 3000 boxes, IoU, 20 labels, the whole call: 749 -> 69 us).
+// through all tiles (128 ragged frames of 3000 boxes, IoU, 20 labels, the whole call: 749 -> 69 us, and
+// 65 once the rank step writes the labels in rank order).
 //
 // A bin is found by a hash of the label, so one bin may hold several labels: the label test stays, and
 // any labels give the same result.  A bin is one wavefront's work and grows with the square of its
-// size; a frame with a bin of more than nms_class_bin_limit() rows is left to the walk (todo[f] = 1).
+// size; a frame with a bin of more than nms_class_bin_limit() rows is walked instead, here and at once:
+// in a launch of its own the walk starts when the last bin of the batch is done, and costs its 4 us also when
+// there is nothing to do (171 x 768, three labels, frames of both kinds: 106 / 167 us, here 60 / 83;
+// 128 x 3000, 20 labels 75 / 72, here 73 / 71).
 //
 // LDS: a bin's survivors are kept, packed, at the front of its own stretch of the tables; the tile in
 // work sits right behind them (survivors + rows of the tile never exceed the rows seen so far).
@@ -27,36 +31,42 @@ __device__ __forceinline__ unsigned class_bin(int label)
     return x & (kClassBins - 1);
 }
 
+// Putting the ranks of a frame into bins by W wavefronts.
 template <int W>
 struct ClassSort {
-    unsigned long long keys[256 * W];
-    unsigned long long match[512 * W];
-    unsigned hist[256 * W];
-    unsigned wbase[256 * W];
-    unsigned tot[256];
+    unsigned long long match[256 * W];   // a wavefront's lane masks by bin
+    unsigned hist[256 * W];              // its counts by bin, then the boxes of the bin in the wavefronts before
+    __align__(16) unsigned tot[256];
 };
 
-template <int W>
+template <int N>
 struct ClassTables {
-    float4 box[256 * W];
-    float T[256 * W];
-    int label[256 * W];
-    uint16_t rank[256 * W];
+    float4 box[N];
+    float T[N];
+    int label[N];
+    uint16_t rank[N];
 };
 
-// W: wavefronts of the workgroup; frames of at most 256 W boxes.  Grid: frames * parts workgroups; each
-// takes every parts-th bin of its frame.
-template <bool IOU, int W>
-__global__ void __launch_bounds__(W * 64)
+template <int W, int N>
+union ClassShared {
+    ClassSort<W> sort;
+    ClassTables<N> tables;
+    WalkShared<W, N> walk;
+};
+
+// W: wavefronts of the workgroup; frames of at most N boxes, N = 64, 128 or 256 W.  Grid: frames * parts workgroups;
+// each takes every parts-th bin of its frame.
+template <bool IOU, int W, int N>
+__global__ void __launch_bounds__(W * 64, 4)  // (a fourth wavefront per SIMD costs W = 4, N = 1024 a register spilled)
 greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ order, const int32_t *__restrict__ counts,
-                      int n_max, int n_pad, int parts, FusedVariant opt, unsigned *__restrict__ todo, uint8_t *__restrict__ keep_out)
+                      int n_max, int n_pad, int parts, NmsThetaConst th, FusedVariant opt, uint8_t *__restrict__ keep_out)
 {
     constexpr int kThreads = W * 64;
-    constexpr size_t kBytes = sizeof(ClassSort<W>) > sizeof(ClassTables<W>) ? sizeof(ClassSort<W>) : sizeof(ClassTables<W>);
-    __shared__ __align__(16) unsigned char raw[kBytes];
-    ClassSort<W> &so = *reinterpret_cast<ClassSort<W> *>(raw);
-    ClassTables<W> &tb = *reinterpret_cast<ClassTables<W> *>(raw);
-    __shared__ uint16_t ids[256 * W];  // ranks, bin by bin
+    static_assert(kThreads >= kClassBins, "a thread per bin");
+    __shared__ __align__(16) unsigned char raw[sizeof(ClassShared<W, N>)];
+    ClassSort<W> &so = reinterpret_cast<ClassShared<W, N> *>(raw)->sort;
+    ClassTables<N> &tb = reinterpret_cast<ClassShared<W, N> *>(raw)->tables;
+    __shared__ uint16_t ids[N];  // ranks, bin by bin
     __shared__ int start[kClassBins + 1];
     __shared__ int next_bin;
     const int f = blockIdx.x / parts;
@@ -72,19 +82,52 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
     uint8_t *keep_f = keep_out + (size_t)f * n_max;
     const bool ties_ignore = (opt.flags & kExTiesIgnore) != 0;
 
+    // a box's place in its bin: the boxes of the bin in the wavefronts before, in this wavefront's registers before, in the lanes before
+    constexpr int kPer = N / kThreads;
+    unsigned bin_of[kPer], place[kPer];
     {
-        int e[4];
-        unsigned key[4], index[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            e[q] = wave * 256 + q * 64 + lane;
-            key[q] = e[q] < n_f ? class_bin(label_f[e[q]]) : 0u;
-            index[q] = (unsigned)e[q];
+        unsigned long long *tab = so.match + wave * 256;
+        unsigned *mine = so.hist + wave * 256;
+        for (int i = lane; i < 256; i += 64) {
+            tab[i] = 0ull;
+            mine[i] = 0u;
         }
-        radix_rank_large<W, 1>(key, index, e, n_f, so.keys, so.hist, so.tot, so.wbase, so.match);  // ends with a barrier
-    }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) ids[tid + kThreads * q] = (uint16_t)so.keys[tid + kThreads * q];
+        for (int q = 0; q < kPer; ++q) {
+            const int e = (wave * kPer + q) * 64 + lane;
+            bin_of[q] = e < n_f ? class_bin(label_f[e]) : (unsigned)kClassBins;  // (no box)
+        }
+        // (the fences only keep the compiler from reordering: a wavefront's LDS instructions execute in order)
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const bool real = bin_of[q] < kClassBins;
+            const unsigned b = bin_of[q] & (kClassBins - 1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (real) __hip_atomic_fetch_or(&tab[b], 1ull << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const unsigned long long same = __hip_atomic_load(&tab[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            const unsigned before = __hip_atomic_load(&mine[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const unsigned below = (unsigned)__builtin_popcountll(same & ((1ull << lane) - 1ull));
+            place[q] = before + below;
+            if (real && below == 0) {
+                __hip_atomic_store(&mine[b], before + (unsigned)__builtin_popcountll(same), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                __hip_atomic_store(&tab[b], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid < kClassBins) {
+        unsigned run = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const unsigned t = so.hist[w * 256 + tid];
+            so.hist[w * 256 + tid] = run;
+            run += t;
+        }
+        so.tot[tid] = run;
+    }
+    __syncthreads();
     if (wave == 0) {
         const uint4 all = reinterpret_cast<const uint4 *>(so.tot)[lane];
         const int sum = (int)(all.x + all.y + all.z + all.w);
@@ -98,14 +141,22 @@ greedy_classes_kernel(const float *__restrict__ sorted5, const int32_t *__restri
             next_bin = part;
         }
     }
-    __syncthreads();  // the sort's part of the LDS is free from here on
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (bin_of[q] < kClassBins)
+            ids[start[bin_of[q]] + (int)(so.hist[wave * 256 + bin_of[q]] + place[q])] = (uint16_t)((wave * kPer + q) * 64 + lane);
+    __syncthreads();
+    // (a barrier: the sort's part of the LDS is free from here on)
     const bool oversized = __syncthreads_or(tid < kClassBins && start[tid + 1] - start[tid] > nms_class_bin_limit(n_f)) != 0;
-    if (part == 0) {
-        if (tid == 0) todo[f] = oversized ? 1u : 0u;
-        if (!oversized)
-            for (int i = n_f + tid; i < n_max; i += kThreads) keep_f[i] = 0;
+    if (oversized) {
+        if (part == 0)
+            walk_frame<true, IOU, kExBoundary, true>(reinterpret_cast<ClassShared<W, N> *>(raw)->walk, sorted5 + (size_t)f * 5 * n_pad, order_f,
+                                                     score_f, label_f, n_f, n_max, n_pad, th, opt, keep_f);
+        return;
     }
-    if (oversized) return;
+    if (part == 0)
+        for (int i = n_f + tid; i < n_max; i += kThreads) keep_f[i] = 0;
 
     for (;;) {
         int bin = 0;

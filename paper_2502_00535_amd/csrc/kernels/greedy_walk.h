@@ -27,8 +27,8 @@
 // runs in stages of 2, 4, 8, ... tiles; after a stage the rows still alive are compacted (their
 // rank numbers through LDS, their boxes gathered again from the table) into fewer tiles and
 // the walk starts over on them.  The last stage begins once 16 tiles or fewer are left.
+// (With W wavefronts: greedy_classes_kernel walks frames of up to 1024 boxes with 4 or 8.)
 constexpr int kFusedWaves = 16;
-constexpr int kFusedOwned = NMS_SORT_CHUNK / kTile / kFusedWaves;  // 4
 constexpr long long kGreedyFusedBoxes = 32ll * 4096;  // nms_run_greedy_batched takes this route from frames * n_max boxes on
 
 struct FusedCandidate {  // a survivor as an outranking box (fields a variant does not use are never read)
@@ -122,8 +122,8 @@ __device__ __forceinline__ unsigned long long fused_second(unsigned long long wo
 // Does candidate c eliminate the victim?  The lane mask over the lanes of `open` (the others do not
 // matter).  !EX: the default measure (MODE kExBoundary = the division-free form of nms_pair.h, else the
 // literal division).  EX: the variants.  With scores or labels to look at, what follows the first test sits
-// behind a wave-uniform branch (40 frames of 4096 boxes, IoU, 5 labels, the whole call: 1284 -> 444 us, the
-// binning of greedy_classes_kernel included).  IoU alone takes the float64 compare for every pair: the branch gains 1 % where
+// behind a wave-uniform branch (40 frames of 4096 boxes of one label, which are walked, IoU, the whole call: 191 -> 172 us
+// where much is eliminated, 833 -> 573 where little is).  IoU alone takes the float64 compare for every pair: the branch gains 1 % where
 // few pairs hit (64 x 2100) and costs 5 to 9 % where many do (300 x 600: 52 -> 57 us).
 template <bool EX, bool IOU, int MODE, bool AUX>
 __device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_T,
@@ -150,69 +150,70 @@ __device__ __forceinline__ unsigned row_or16(unsigned x)
 constexpr int kWalkChunk = 4;  // survivors fetched from LDS at a time
 constexpr int kWalkLists = 2;  // lists kept in LDS: the one being written and the one being applied
 
-template <bool EX, bool IOU, int MODE, bool AUX>
-__global__ void __launch_bounds__(kFusedWaves * 64)
-greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ order,
-                    const int32_t *__restrict__ counts, int n_max, int n_pad, NmsThetaConst th, FusedVariant opt,
-                    const unsigned *__restrict__ todo, uint8_t *__restrict__ keep_out)
+// W: wavefronts of the workgroup; N: the longest frame, of W, 2 W or 4 W tiles.
+template <int W, int N>
+struct WalkShared {
+    float4 box[kWalkLists + 1][kTile];      // list t in buffer t % kWalkLists
+    float aux[kWalkLists + 1][kTile];
+    float area[kWalkLists + 1][kTile];
+    float score[kWalkLists + 1][kTile];
+    int label[kWalkLists + 1][kTile];
+    int count[kWalkLists];
+    unsigned long long part[W];             // rows of the tile being settled that a wavefront's share of the list before eliminates
+    unsigned long long hitters[kTile];      // per row of that tile: the better-ranked rows of the tile that eliminate it
+    int alive[N / kTile];                   // compaction: rows alive per tile
+    int ids[N / kTile > W ? N : 1];         // compaction: rank numbers of the rows left
+};
+
+// One frame, by all wavefronts of the workgroup.
+template <bool EX, bool IOU, int MODE, bool AUX, int W, int N>
+__device__ __forceinline__ void walk_frame(WalkShared<W, N> &sh, const float *__restrict__ sorted_f, const int32_t *__restrict__ order_f,
+                                           const float *__restrict__ score_f, const int32_t *__restrict__ label_f, int n_f, int n_max,
+                                           int n_pad, const NmsThetaConst th, const FusedVariant opt, uint8_t *__restrict__ keep_f)
 {
+    constexpr int kOwned = N / kTile / W;
+    static_assert(kOwned == 1 || kOwned == 2 || kOwned == 4, "apply() dispatches on up to four slots");
     constexpr bool kUseT = MODE == kExBoundary && (!IOU || AUX);  // the list carries T, else the area
     constexpr bool kUseArea = kUseT && IOU;              // ... and the area as well
     constexpr bool kSecond = kFusedSecond<EX, IOU, MODE, AUX>;
     constexpr int kTileBuf = kWalkLists;                 // one more buffer of the same layout: the rows of the tile being settled
-    __shared__ float4 box_s[kWalkLists + 1][kTile];      // list t in buffer t % kWalkLists
-    __shared__ float aux_s[kWalkLists + 1][kTile];
-    __shared__ float area_s[kWalkLists + 1][kTile];
-    __shared__ float score_s[kWalkLists + 1][kTile];
-    __shared__ int label_s[kWalkLists + 1][kTile];
-    __shared__ int count_s[kWalkLists];
-    __shared__ unsigned long long part_s[kFusedWaves];   // rows of the tile being settled that a wavefront's share of the list before eliminates
-    __shared__ unsigned long long hitters_s[kTile];      // per row of that tile: the better-ranked rows of the tile that eliminate it
-    __shared__ int alive_s[NMS_SORT_CHUNK / kTile];  // compaction: rows alive per tile
-    __shared__ int ids_s[NMS_SORT_CHUNK];            // compaction: rank numbers of the rows left
-    const int f = blockIdx.x;
-    if (todo != nullptr && todo[f] == 0) return;  // greedy_classes_kernel has settled this frame
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int n_f = frame_count(counts, f, n_max);
-    const float *sorted_f = sorted5 + (size_t)f * 5 * n_pad;
     const float4 *box4 = reinterpret_cast<const float4 *>(sorted_f);
     const float *area = sorted_f + 4 * (size_t)n_pad;
-    uint8_t *keep_f = keep_out + (size_t)f * n_max;
-    const int32_t *order_f = order + (size_t)f * n_max;
 
-    for (int i = (int)threadIdx.x; i < n_max; i += blockDim.x) keep_f[i] = 0;  // survivors are marked as they are found
+    for (int i = (int)threadIdx.x; i < n_max; i += W * 64) keep_f[i] = 0;  // survivors are marked as they are found
 
     // The owned tiles that are not settled yet, the next one to settle in slot 0 (after a tile is
     // settled the others move down one slot).
-    float4 vb[kFusedOwned];
-    FusedCandidate self[kFusedOwned];     // the same rows in their role as outranking boxes
-    int rank_of[kFusedOwned];             // rank number of the lane's row
-    unsigned long long out[kFusedOwned];  // wave-uniform; bit r: row r is eliminated or does not exist
+    float4 vb[kOwned];
+    FusedCandidate self[kOwned];     // the same rows in their role as outranking boxes
+    int rank_of[kOwned];             // rank number of the lane's row
+    unsigned long long out[kOwned];  // wave-uniform; bit r: row r is eliminated or does not exist
     int left = 0;                         // owned tiles not settled yet
-    int tn = 0;                           // number of the tile in slot 0 (the others follow in steps of 16)
+    int tn = 0;                           // number of the tile in slot 0 (the others follow in steps of W)
     int n_cur = n_f;                      // rows in the current numbering
 
-    // (re)load the owned tiles of the current numbering; `compacted`: rank numbers come from ids_s
+    // (re)load the owned tiles of the current numbering; `compacted`: rank numbers come from sh.ids
     auto load_tiles = [&](bool compacted) __attribute__((always_inline)) {
         left = 0;
         tn = wave;
 #pragma unroll
-        for (int i = 0; i < kFusedOwned; ++i) {
-            const int first = (wave + kFusedWaves * i) * kTile;
+        for (int i = 0; i < kOwned; ++i) {
+            const int first = (wave + W * i) * kTile;
             const bool has = first < n_cur;
             left += has ? 1 : 0;
             const int q = first + lane;
             const bool real = q < n_cur;
-            const int r = real ? (compacted ? ids_s[q] : q) : 0;  // rows that do not exist read row 0 and are marked out
+            const int r = real ? (compacted ? sh.ids[q] : q) : 0;  // rows that do not exist read row 0 and are marked out
             rank_of[i] = r;
             vb[i] = box4[r];
             FusedCandidate me;
             me.x1 = vb[i].x, me.y1 = vb[i].y, me.x2 = vb[i].z, me.y2 = vb[i].w;
             me.area = EX ? ((vb[i].z - vb[i].x) + opt.offset) * ((vb[i].w - vb[i].y) + opt.offset) : area[r];
             me.T = kUseT ? fused_threshold<EX, IOU>(me.area, EX ? opt.boundary : th.m) : 0.0f;
-            me.score = AUX ? opt.ranked_score[(size_t)f * n_pad + r] : 0.0f;
-            me.label = (AUX && (opt.flags & kExClasses)) ? opt.ranked_label[(size_t)f * n_pad + r] : 0;
+            me.score = AUX ? score_f[r] : 0.0f;
+            me.label = (AUX && (opt.flags & kExClasses)) ? label_f[r] : 0;
             self[i] = me;
             out[i] = !has ? ~0ull : (first + kTile <= n_cur ? 0ull : ~0ull << (n_cur - first));
         }
@@ -224,42 +225,42 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
     // wave-uniform k every lane gets the same entry (a broadcast read); with k = lane, its own.
     auto entry = [&](int buf, int k) __attribute__((always_inline)) {
         FusedCandidate c;
-        const float4 b = box_s[buf][k];
+        const float4 b = sh.box[buf][k];
         c.x1 = b.x, c.y1 = b.y, c.x2 = b.z, c.y2 = b.w;
-        c.T = kUseT ? aux_s[buf][k] : 0.0f;
-        c.area = kUseArea ? area_s[buf][k] : (kUseT ? 0.0f : aux_s[buf][k]);
-        c.score = AUX ? score_s[buf][k] : 0.0f;
-        c.label = AUX ? label_s[buf][k] : 0;
+        c.T = kUseT ? sh.aux[buf][k] : 0.0f;
+        c.area = kUseArea ? sh.area[buf][k] : (kUseT ? 0.0f : sh.aux[buf][k]);
+        c.score = AUX ? sh.score[buf][k] : 0.0f;
+        c.label = AUX ? sh.label[buf][k] : 0;
         return c;
     };
-    // What fused_first needs of it: where a second test follows, area, score and label are only read there.
+    // What fused_first needs of it, and under IoU the label: where a second test follows, its other fields are only fetched or made there.
     auto first_entry = [&](int buf, int k) __attribute__((always_inline)) {
         if (!kSecond) return entry(buf, k);
         FusedCandidate c;
-        const float4 b = box_s[buf][k];
+        const float4 b = sh.box[buf][k];
         c.x1 = b.x, c.y1 = b.y, c.x2 = b.z, c.y2 = b.w;
-        c.T = aux_s[buf][k];
+        c.T = sh.aux[buf][k];
         c.area = c.score = 0.0f;
-        c.label = 0;
+        c.label = IOU ? sh.label[buf][k] : 0;
         return c;
     };
-    // The list in buffer `buf` against the tiles in slots 0 .. N-1.  Survivors are fetched four
+    // The list in buffer `buf` against the tiles in slots 0 .. S-1.  Survivors are fetched four
     // at a time into two sets of registers in turn, the next four while the current four are
     // tested; a full chunk has no branch inside.
     auto apply_slots = [&](auto slots, int buf) __attribute__((always_inline)) {
-        constexpr int N = decltype(slots)::value;
-        const int count = __builtin_amdgcn_readfirstlane(count_s[buf]);
+        constexpr int S = decltype(slots)::value;
+        const int count = __builtin_amdgcn_readfirstlane(sh.count[buf]);
         if (count == 0) return;
         auto fetch = [&](FusedCandidate (&c)[kWalkChunk], int k0) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kWalkChunk; ++u) c[u] = first_entry(buf, k0 + u < count ? k0 + u : count - 1);
         };
-        // survivor c (entry k) against the N tiles
+        // survivor c (entry k) against the S tiles
         auto test_one = [&](const FusedCandidate &c, int k) __attribute__((always_inline)) {
-            unsigned long long word[N];
+            unsigned long long word[S];
             unsigned long long any = 0;
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
+            for (int i = 0; i < S; ++i) {
                 word[i] = __ballot(fused_first<EX, IOU, MODE, AUX>(vb[i], self[i].area, self[i].T, self[i].score, self[i].label, c, th.theta, opt));
                 if (kSecond) {
                     word[i] &= ~out[i];
@@ -270,9 +271,15 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
             }
             if (kSecond && any != 0) {
                 asm volatile("" ::: "memory");  // keeps this a branch
-                const FusedCandidate full = entry(buf, k);
+                FusedCandidate full = c;
+                if (IOU) {  // no second round trip to LDS: where much is eliminated, most survivors come this way
+                    full.area = ((c.x2 - c.x1) + opt.offset) * ((c.y2 - c.y1) + opt.offset);
+                    if (opt.flags & kExTiesIgnore) full.score = sh.score[buf][k];
+                } else {
+                    full = entry(buf, k);
+                }
 #pragma unroll
-                for (int i = 0; i < N; ++i)
+                for (int i = 0; i < S; ++i)
                     if (word[i] != 0)
                         out[i] |= fused_second<IOU, AUX>(word[i], vb[i], self[i].area, self[i].score, self[i].label, full, opt);
             }
@@ -299,25 +306,28 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
     };
     auto apply = [&](int slots, int buf) __attribute__((always_inline)) {  // the same for a number of slots known at run time
         if (slots == 1) apply_slots(std::integral_constant<int, 1>(), buf);
-        else if (slots == 2) apply_slots(std::integral_constant<int, 2>(), buf);
-        else if (slots == 3) apply_slots(std::integral_constant<int, 3>(), buf);
-        else if (slots >= 4) apply_slots(std::integral_constant<int, 4>(), buf);
+        if constexpr (kOwned >= 2) {
+            if (slots == 2) apply_slots(std::integral_constant<int, 2>(), buf);
+        }
+        if constexpr (kOwned == 4) {
+            if (slots == 3) apply_slots(std::integral_constant<int, 3>(), buf);
+            else if (slots >= 4) apply_slots(std::integral_constant<int, 4>(), buf);
+        }
     };
-    static_assert(kFusedOwned == 4, "apply() dispatches on up to four slots");
 
     // the rows of slot 0 into LDS for the round that settles them
     auto post_tile = [&]() __attribute__((always_inline)) {
-        box_s[kTileBuf][lane] = vb[0];
-        aux_s[kTileBuf][lane] = kUseT ? self[0].T : self[0].area;
-        if (kUseArea) area_s[kTileBuf][lane] = self[0].area;
-        if (AUX) score_s[kTileBuf][lane] = self[0].score;
-        if (AUX) label_s[kTileBuf][lane] = self[0].label;
+        sh.box[kTileBuf][lane] = vb[0];
+        sh.aux[kTileBuf][lane] = kUseT ? self[0].T : self[0].area;
+        if (kUseArea) sh.area[kTileBuf][lane] = self[0].area;
+        if (AUX) sh.score[kTileBuf][lane] = self[0].score;
+        if (AUX) sh.label[kTileBuf][lane] = self[0].label;
     };
 
     int g = 0;          // rounds so far over all stages: round g writes list g, into buffer g % kWalkLists
     for (int stage_tiles = 2;; stage_tiles *= 2) {
         const int tiles_cur = (n_cur + kTile - 1) / kTile;
-        const int rounds = (tiles_cur <= kFusedWaves || stage_tiles >= tiles_cur) ? tiles_cur : stage_tiles;
+        const int rounds = (tiles_cur <= W || stage_tiles >= tiles_cur) ? tiles_cur : stage_tiles;
         if (wave == 0) post_tile();  // tile 0 of this numbering
         lds_barrier();
         for (int t = 0; t < rounds; ++t, ++g) {
@@ -328,36 +338,39 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
             {
                 const FusedCandidate row = entry(kTileBuf, lane);
                 const float4 row_box = make_float4(row.x1, row.y1, row.x2, row.y2);
-                const int count = g > 0 ? __builtin_amdgcn_readfirstlane(count_s[pending]) : 0;
+                const int count = g > 0 ? __builtin_amdgcn_readfirstlane(sh.count[pending]) : 0;
                 unsigned long long part = 0;
-                for (int k = wave; k < count; k += kFusedWaves)
+                for (int k = wave; k < count; k += W)
                     part |= fused_word<EX, IOU, MODE, AUX>(~part, row_box, row.area, row.T, row.score, row.label, entry(pending, k),
                                                            th.theta, opt);
-                if (lane == 0) part_s[wave] = part;
-                FusedCandidate victim[kTile / kFusedWaves];
+                if (lane == 0) sh.part[wave] = part;
+#pragma unroll 1
+                for (int j0 = 0; j0 < kTile / W; j0 += 4) {
+                    FusedCandidate victim[4];
 #pragma unroll
-                for (int j = 0; j < kTile / kFusedWaves; ++j) victim[j] = entry(kTileBuf, wave + kFusedWaves * j);
+                    for (int j = 0; j < 4; ++j) victim[j] = entry(kTileBuf, wave + W * (j0 + j));
 #pragma unroll
-                for (int j = 0; j < kTile / kFusedWaves; ++j) {
-                    const int r = wave + kFusedWaves * j;
-                    const unsigned long long hitters = fused_word<EX, IOU, MODE, AUX>(
-                        (1ull << r) - 1ull, make_float4(victim[j].x1, victim[j].y1, victim[j].x2, victim[j].y2), victim[j].area,
-                        victim[j].T, victim[j].score, victim[j].label, row, th.theta, opt);
-                    if (lane == 0) hitters_s[r] = hitters;
+                    for (int j = 0; j < 4; ++j) {
+                        const int r = wave + W * (j0 + j);
+                        const unsigned long long hitters = fused_word<EX, IOU, MODE, AUX>(
+                            (1ull << r) - 1ull, make_float4(victim[j].x1, victim[j].y1, victim[j].x2, victim[j].y2), victim[j].area,
+                            victim[j].T, victim[j].score, victim[j].label, row, th.theta, opt);
+                        if (lane == 0) sh.hitters[r] = hitters;
+                    }
                 }
             }
             lds_barrier();
-            if (wave == (t & (kFusedWaves - 1))) {
+            if (wave == (t & (W - 1))) {
                 // Settle tile t (slot 0).  A row survives iff it is alive and no surviving
                 // better-ranked row of the tile eliminates it; iterated from "every alive row
                 // survives" this settles one more row per pass at least, in practice a few passes.
                 __builtin_amdgcn_s_setprio(3);
-                const unsigned long long share = part_s[lane & (kFusedWaves - 1)];
+                const unsigned long long share = sh.part[lane & (W - 1)];
                 const unsigned dead_lo = row_or16((unsigned)share), dead_hi = row_or16((unsigned)(share >> 32));
                 const unsigned long long dead =
-                    out[0] | ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)dead_hi, kFusedWaves - 1) << 32) |
-                    (unsigned)__builtin_amdgcn_readlane((int)dead_lo, kFusedWaves - 1);
-                const unsigned long long hitters = hitters_s[lane];
+                    out[0] | ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)dead_hi, 15) << 32) |
+                    (unsigned)__builtin_amdgcn_readlane((int)dead_lo, 15);
+                const unsigned long long hitters = sh.hitters[lane];
                 const bool alive = ((~dead >> lane) & 1ull) != 0;
                 unsigned long long kept = ~dead;
                 for (int pass = 0; pass < kTile; ++pass) {
@@ -371,55 +384,71 @@ greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
                 const int into = g & (kWalkLists - 1);
                 if (is_kept) {  // survivor number k of the tile is entry k of the list
                     const int k = __builtin_popcountll(kept & ((1ull << lane) - 1ull));
-                    box_s[into][k] = v;
-                    aux_s[into][k] = kUseT ? mine.T : mine.area;
-                    if (kUseArea) area_s[into][k] = mine.area;
-                    if (AUX) score_s[into][k] = mine.score;
-                    if (AUX) label_s[into][k] = mine.label;
+                    sh.box[into][k] = v;
+                    sh.aux[into][k] = kUseT ? mine.T : mine.area;
+                    if (kUseArea) sh.area[into][k] = mine.area;
+                    if (AUX) sh.score[into][k] = mine.score;
+                    if (AUX) sh.label[into][k] = mine.label;
                 }
-                if (lane == 0) count_s[into] = __builtin_popcountll(kept);
+                if (lane == 0) sh.count[into] = __builtin_popcountll(kept);
                 __builtin_amdgcn_s_setprio(0);
                 if (is_kept) keep_f[order_f[rank_of[0]]] = 1;
 #pragma unroll
-                for (int i = 0; i + 1 < kFusedOwned; ++i) {
+                for (int i = 0; i + 1 < kOwned; ++i) {
                     vb[i] = vb[i + 1];
                     self[i] = self[i + 1];
                     rank_of[i] = rank_of[i + 1];
                     out[i] = out[i + 1];
                 }
                 --left;
-                tn += kFusedWaves;
-            } else if (t + 1 < rounds && wave == ((t + 1) & (kFusedWaves - 1))) {
+                tn += W;
+            } else if (t + 1 < rounds && wave == ((t + 1) & (W - 1))) {
                 post_tile();  // the next round's tile
             }
             if (g > 0) apply(left, pending);  // the list before against the tiles that are left
             lds_barrier();
         }
         if (rounds == tiles_cur) break;  // every tile is settled
+        if constexpr (kOwned > 1) {
 
-        // End of a stage: the rows still alive move together (the list just written has not been
-        // applied yet; it holds boxes, not row numbers, and is applied in the next stage's first
-        // round like any other).  Tile `rounds + j` of the old numbering reports its count in
-        // alive_s[j]; a prefix sum gives every tile its place in ids_s.
-        const int tiles_left = tiles_cur - rounds;
+            // End of a stage: the rows still alive move together (the list just written has not been
+            // applied yet; it holds boxes, not row numbers, and is applied in the next stage's first
+            // round like any other).  Tile `rounds + j` of the old numbering reports its count in
+            // sh.alive[j]; a prefix sum gives every tile its place in sh.ids.
+            const int tiles_left = tiles_cur - rounds;
 #pragma unroll
-        for (int i = 0; i < kFusedOwned; ++i) {
-            if (i < left && lane == 0) alive_s[tn - rounds + kFusedWaves * i] = __builtin_popcountll(~out[i]);
-        }
-        lds_barrier();
-        const unsigned mine_alive = lane < tiles_left ? (unsigned)alive_s[lane] : 0u;
-        const unsigned incl = wave_inclusive_sum(mine_alive);
-        const int total = __builtin_amdgcn_readlane((int)incl, 63);
-#pragma unroll
-        for (int i = 0; i < kFusedOwned; ++i) {
-            if (i < left) {  // wave-uniform
-                const int base = __builtin_amdgcn_readlane((int)(incl - mine_alive), tn - rounds + kFusedWaves * i);
-                const unsigned long long alive = ~out[i];
-                if ((alive >> lane) & 1ull) ids_s[base + __builtin_popcountll(alive & ((1ull << lane) - 1ull))] = rank_of[i];
+            for (int i = 0; i < kOwned; ++i) {
+                if (i < left && lane == 0) sh.alive[tn - rounds + W * i] = __builtin_popcountll(~out[i]);
             }
+            lds_barrier();
+            const unsigned mine_alive = lane < tiles_left ? (unsigned)sh.alive[lane] : 0u;
+            const unsigned incl = wave_inclusive_sum(mine_alive);
+            const int total = __builtin_amdgcn_readlane((int)incl, 63);
+#pragma unroll
+            for (int i = 0; i < kOwned; ++i) {
+                if (i < left) {  // wave-uniform
+                    const int base = __builtin_amdgcn_readlane((int)(incl - mine_alive), tn - rounds + W * i);
+                    const unsigned long long alive = ~out[i];
+                    if ((alive >> lane) & 1ull) sh.ids[base + __builtin_popcountll(alive & ((1ull << lane) - 1ull))] = rank_of[i];
+                }
+            }
+            lds_barrier();
+            n_cur = total;
+            load_tiles(true);
         }
-        lds_barrier();
-        n_cur = total;
-        load_tiles(true);
     }
+}
+
+template <bool EX, bool IOU, int MODE, bool AUX>
+__global__ void __launch_bounds__(kFusedWaves * 64)
+greedy_fused_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ order,
+                    const int32_t *__restrict__ counts, int n_max, int n_pad, NmsThetaConst th, FusedVariant opt,
+                    uint8_t *__restrict__ keep_out)
+{
+    __shared__ WalkShared<kFusedWaves, NMS_SORT_CHUNK> sh;
+    const int f = blockIdx.x;
+    walk_frame<EX, IOU, MODE, AUX>(sh, sorted5 + (size_t)f * 5 * n_pad, order + (size_t)f * n_max,
+                                   AUX ? opt.ranked_score + (size_t)f * n_pad : nullptr,
+                                   AUX ? opt.ranked_label + (size_t)f * n_pad : nullptr,
+                                   frame_count(counts, f, n_max), n_max, n_pad, th, opt, keep_out + (size_t)f * n_max);
 }

@@ -187,8 +187,7 @@ __device__ __forceinline__ void radix_rank_small(unsigned (&key)[4], unsigned (&
 // take turns: 24 frames of 3000 boxes 17.6 -> 13.7 us, full frames unchanged.  radix_rank_small, whose
 // frames are a few wavefronts, gains nothing by it.)
 // match: W x 2 x 256 lane masks; hist, wbase: W x 256 counters each; tot: 256.
-// PASSES: 4 sorts by the whole key, fewer by its lowest digits only; tot[] is left with the last pass's digit counts.
-template <int W, int PASSES = 4>
+template <int W>
 __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&idx)[4], const int (&e)[4], int cnt,
                                                  unsigned long long *buf, unsigned *hist, unsigned *tot, unsigned *wbase,
                                                  unsigned long long *match)
@@ -218,7 +217,7 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
         }
     };
 #pragma unroll 1
-    for (int shift = 0; shift < 8 * PASSES; shift += 8) {
+    for (int shift = 0; shift < 32; shift += 8) {
         reinterpret_cast<uint4 *>(myhist)[lane] = make_uint4(0u, 0u, 0u, 0u);
         unsigned d[4], place[4];
 #pragma unroll
@@ -285,7 +284,7 @@ __device__ __forceinline__ void radix_rank_large(unsigned (&key)[4], unsigned (&
             if (e[q] < cnt) buf[dest] = ((unsigned long long)key[q] << 32) | idx[q];
         }
         __syncthreads();
-        if (shift < 8 * (PASSES - 1)) {
+        if (shift < 24) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const unsigned long long v = buf[e[q]];

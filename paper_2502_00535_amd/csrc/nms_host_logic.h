@@ -105,27 +105,31 @@ NMS_HD int nms_count_rank_elements(int n_max, int frames)
 }
 
 // ---- greedy rule with labels ----------------------------------------------------------------------
-// Large batches under the greedy rule with labels: class by class (greedy_classes_kernel) for frames
-// of more than two tiles.  Shorter frames are one or two rounds of the walk, and its launch would follow
-// anyway (IoU, whole call, walk alone against class by class: 2048 x 64, 20 labels 42 us / 60; 1024 x 128,
-// 20 labels 33 / 38, 80 labels 33 / 49; 820 x 160, 20 labels 70 / 40).
-NMS_HD bool nms_use_class_route(int n_max)
-{
-    return n_max > 128;
-}
-
-// The largest bin of labels that is settled there, in a frame of n_f boxes; a frame with a larger one is
-// left to the walk.  A bin is one wavefront's chain and grows with the square of its rows, the walk
-// has sixteen wavefronts on the whole frame: the line is a share of the frame.  Class by class against
-// the walk behind the launch that finds nothing to settle, IoU, whole call, scenes where much / little is
-// eliminated: 128 x 3000 in bins of 1000 502 / 1045 us against 207 / 527, of 600 221 / 309 against 283 /
-// 550; 128 x 1024 in bins of 1024 190 / 541 against 61 / 129, of 205 60 / 68 against 95 / 136.  In short frames
-// bins beyond a quarter still pay: 263 x 500 in bins of 167 43 / 58 against 77 / 115, of 500 78 / 191 against
-// 59 / 113; 342 x 384 in bins of 384 59 / 128 against 50 / 85; 1024 x 256 in bins of 256 48 / 100 against 65 / 95.
+// Large batches under the greedy rule with labels (greedy_classes_kernel; a batch there holds at least
+// 131,072 boxes).  The figures: IoU, whole call, scenes where much / little is eliminated, in us.
+//
+// The largest bin of labels that one wavefront settles, in a frame of n_f boxes; a frame with a larger
+// one is walked by the whole workgroup.  A bin is a chain that grows with the square of its rows, the walk
+// shares the frame out: the line is a share of the frame.  Class by class against walked: 128 x 3000 in bins
+// of 1000 502 / 1045 against 207 / 527, of 600 221 / 300 against 280 / 545; 263 x 500 in bins of 250 51 / 90 against
+// 46 / 72, of 167 40 / 56 against 51 / 72; 300 x 1024 in bins of 512 128 / 244 against 72 / 183, of 341 90 / 138
+// against 88 / 184.  Frames of three tiles or fewer are walked whatever their labels (2048 x 64, 20 labels 51 / 51
+// against 25 / 24; 683 x 192 28 / 28 against 32 / 27).
 NMS_HD int nms_class_bin_limit(int n_f)
 {
-    const int quarter = n_f / 4;
-    return quarter > 288 ? quarter : 288;
+    if (n_f <= 192) return 0;
+    if (n_f <= 1024) return 7 * n_f / 16;
+    return n_f / 4 > 448 ? n_f / 4 : 448;
+}
+
+// Wavefronts per workgroup: enough to walk a frame quickly, few enough that the wavefronts without a bin
+// do not hold the places of other frames' when there are more frames than fit at once.  4 / 8 / 16 wavefronts, one
+// label: 512 x 640 52, 44, 68; 2048 x 64 26, 30, 47; three labels: 300 x 1024 89 / 139, 90 / 138, 93 / 138; 1024 x 500
+// 57 / 83, 71 / 98, 75 / 105; twenty: 128 x 1024 40 / 38, 34 / 32, 31 / 30.
+NMS_HD int nms_class_waves(int n_max, int frames)
+{
+    if (n_max > 1024) return 16;
+    return frames <= 768 ? 8 : 4;
 }
 
 // ---- which kernels a whole-path call runs ------------------------------------------------------

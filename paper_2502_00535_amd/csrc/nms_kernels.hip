@@ -593,10 +593,10 @@ static int run_greedy_fused(const float *boxes, const float *scores, const int32
     const FusedVariant none = {nullptr, nullptr, 0.0, 1.0f, 0};
     if (th.fast)
         greedy_fused_kernel<false, false, kExBoundary, false><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(
-            w.sorted5, w.order, counts, n_max, n_pad, th, none, nullptr, keep_out);
+            w.sorted5, w.order, counts, n_max, n_pad, th, none, keep_out);
     else
         greedy_fused_kernel<false, false, kExDivideGe, false><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(
-            w.sorted5, w.order, counts, n_max, n_pad, th, none, nullptr, keep_out);
+            w.sorted5, w.order, counts, n_max, n_pad, th, none, keep_out);
     return launch_status();
 }
 
@@ -800,32 +800,35 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         // large batches under the greedy rule: the mask-free walk, one workgroup per frame
         const NmsThetaConst th = nms_make_theta_const(threshold);
         const FusedVariant v = {ranked_score, ranked_class, boundary, opt.pixel_offset, flags};
-        // With labels: class by class; the walk then takes the frames with a class too large for that
-        // (a launch of 4 us that often finds nothing to do, but only the device knows the labels).
-        // (The tile flags' place in the workspace is free here.)
-        unsigned *todo = nullptr;
-        if (opt.classes && mode == kExBoundary && nms_use_class_route(n_max)) {
-            todo = w.ytile;
+        // With labels: class by class, or the walk by the same workgroup where a class is too large for that.
+        if (opt.classes && mode == kExBoundary) {
             int parts = 1;  // workgroups per frame (each sorts the frame's labels): up to four while every one has a compute unit
             while (parts < 4 && frames * parts * 2 <= 256) parts *= 2;
             const dim3 classes_grid((unsigned)(frames * parts));
             begin_launch();
-#define NMS_LAUNCH_CLASSES(IOU_, W_)                                                       \
-    greedy_classes_kernel<IOU_, W_><<<classes_grid, dim3(W_ * 64), 0, s>>>(                \
-        w.sorted5, w.order, counts, n_max, n_pad, parts, v, todo, keep_out)
-            if (n_max <= 1024) {
-                if (iou) NMS_LAUNCH_CLASSES(true, 4); else NMS_LAUNCH_CLASSES(false, 4);
-            } else {
-                if (iou) NMS_LAUNCH_CLASSES(true, 16); else NMS_LAUNCH_CLASSES(false, 16);
-            }
+#define NMS_LAUNCH_CLASSES(W_, N_)                                                                      \
+    do {                                                                                                \
+        if (iou)                                                                                        \
+            greedy_classes_kernel<true, W_, N_><<<classes_grid, dim3(W_ * 64), 0, s>>>(                 \
+                w.sorted5, w.order, counts, n_max, n_pad, parts, th, v, keep_out);                      \
+        else                                                                                            \
+            greedy_classes_kernel<false, W_, N_><<<classes_grid, dim3(W_ * 64), 0, s>>>(                \
+                w.sorted5, w.order, counts, n_max, n_pad, parts, th, v, keep_out);                      \
+    } while (0)
+            const int waves = nms_class_waves(n_max, frames);
+            if (waves == 4 && n_max <= 256) NMS_LAUNCH_CLASSES(4, 256);
+            else if (waves == 4 && n_max <= 512) NMS_LAUNCH_CLASSES(4, 512);
+            else if (waves == 4) NMS_LAUNCH_CLASSES(4, 1024);
+            else if (waves == 8 && n_max <= 512) NMS_LAUNCH_CLASSES(8, 512);
+            else if (waves == 8) NMS_LAUNCH_CLASSES(8, 1024);
+            else NMS_LAUNCH_CLASSES(16, 4096);
 #undef NMS_LAUNCH_CLASSES
-            st = launch_status();
-            if (st != NMS_OK) return st;
+            return launch_status();
         }
         begin_launch();
 #define NMS_LAUNCH_WALK(IOU_, MODE_, AUX_)                                                          \
     greedy_fused_kernel<true, IOU_, MODE_, AUX_><<<dim3(frames), dim3(kFusedWaves * 64), 0, s>>>(   \
-        w.sorted5, w.order, counts, n_max, n_pad, th, v, todo, keep_out)
+        w.sorted5, w.order, counts, n_max, n_pad, th, v, keep_out)
 #define NMS_LAUNCH_WALK_MODE(IOU_, AUX_)                                                  \
     do {                                                                                  \
         if (mode == kExBoundary) NMS_LAUNCH_WALK(IOU_, kExBoundary, AUX_);                \

@@ -84,9 +84,9 @@ int main(int argc, char **argv)
         return 0;
     }
     if (!strcmp(argv[1], "classes")) {
-        // largest bin of labels that one wavefront settles, for every frame length given on stdin
-        int n;
-        while (scanf("%d", &n) == 1) printf("%d %d\n", nms_use_class_route(n) ? 1 : 0, nms_class_bin_limit(n));
+        // largest bin of labels that one wavefront settles, wavefronts per workgroup in a batch of such frames
+        int n, frames;
+        while (scanf("%d %d", &n, &frames) == 2) printf("%d %d\n", nms_class_bin_limit(n), nms_class_waves(n, frames));
         return 0;
     }
     if (!strcmp(argv[1], "layout")) {

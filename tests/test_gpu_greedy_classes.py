@@ -1,11 +1,12 @@
-"""The greedy rule with labels on large batches: every class by a wavefront of its own, frames with a
-class beyond 288 boxes and a quarter of the frame by the walk, against the oracle.  Bar: 0 differing keep bits."""
+"""The greedy rule with labels on large batches: every class by a wavefront of its own, frames with a class that
+is a large share of the frame walked by the whole workgroup, against the oracle.  Bar: 0 differing keep bits."""
 import numpy as np
 import pytest
 
 from workloads import random_frame
 
 from test_gpu_variants import ExFrames, nms, oracle_ex  # noqa: F401  (nms: fixture)
+from test_host_logic import largest_bin
 
 pytestmark = pytest.mark.gpu
 
@@ -51,25 +52,23 @@ def test_labels(nms, oracle, n_max, frames):  # noqa: F811
             assert np.array_equal(got, want), f"{opts}: {(got != want).sum()} differing keep bits"
 
 
-def largest_bin(n):
-    return max(288, n // 4)  # the rule swept in tests/test_host_logic.py
-
-
-# both sides of the shortest frame taken class by class; frames that are one bin, at its bound and one beyond; bins
-# at the bound and one beyond in frames of 1024 boxes and where the bound begins to follow the frame's length
-@pytest.mark.parametrize("n_max,frames", [(128, 1024), (129, 1017), (288, 456), (289, 454), (1024, 128), (1152, 114), (1160, 113)])
+# Every kernel (4, 8 and 16 wavefronts, tables of 256 to 4096 boxes) at the ends of its range, in frames whose largest bin
+# is at the bound and one beyond, the longest that are always walked, and lengths around whole tiles.
+@pytest.mark.parametrize("n_max,frames", [(64, 2048), (192, 769), (193, 769), (256, 769), (257, 769), (512, 769), (513, 769), (1024, 769),
+                                          (171, 768), (512, 768), (513, 768), (1024, 129), (1025, 128), (1800, 80), (4096, 33)])
 def test_bins_at_the_bound(nms, oracle, n_max, frames):  # noqa: F811
     rng = np.random.default_rng(n_max)
-    distinct = 6
+    counts = np.minimum(n_max, [n_max, n_max, n_max - 1, n_max // 2, 193, 320, 65, 64, 1, 0]).astype(np.int32)
+    distinct = len(counts)
     boxes = np.zeros((distinct, n_max, 4), np.float32)
     scores = np.zeros((distinct, n_max), np.float32)
     classes = np.zeros((distinct, n_max), np.int32)
-    counts = np.array([n_max, n_max, n_max, n_max - 1, n_max // 2, 63], np.int32)
     for f in range(distinct):
         boxes[f], scores[f] = random_frame(31 * n_max + f, n_max, extent=250 + 50 * f, max_side=120, integer=f % 2 == 0,
                                            score_levels=(0, 40)[f % 2])
-        rows = min(n_max, largest_bin(int(counts[f])) + f % 2)
-        classes[f, : counts[f]] = rng.permutation(np.where(np.arange(counts[f]) < rows, 7, 8 + np.arange(counts[f]) % 60))
+        c = int(counts[f])
+        rows = largest_bin(c) + f % 2
+        classes[f, :c] = rng.permutation(np.where(np.arange(c) < rows, 7, 8 + np.arange(c) % 60))
     which = np.arange(frames) % distinct
     dev = ExFrames(nms, boxes[which], scores[which], classes[which], counts[which])
     for measure, compare, ties, offset in (("iou", "gt", "index", 0.0), ("outranking_area", "ge", "ignore", 1.0)):
@@ -82,8 +81,8 @@ def test_bins_at_the_bound(nms, oracle, n_max, frames):  # noqa: F811
 
 @pytest.mark.parametrize("n,frames", [(640, 205), (1024, 128)])
 def test_one_label_costs_little_more_than_none(nms, n, frames):  # noqa: F811
-    """All boxes of one label are one bin: as one wavefront's chain 3 to 5 times the unlabelled call, through the
-    walk 1.2 to 1.4 times.  The bound lies between, well beyond what a run's times differ."""
+    """All boxes of one label are one bin: as one wavefront's chain 3 to 5 times the unlabelled call, walked about
+    1.2 to 1.5 times.  The bound lies between, well beyond what a run's times differ."""
     import torch
 
     dev = torch.device("cuda:0")

@@ -141,7 +141,8 @@ def test_batched_ragged_with_labels(nms, oracle):
 def test_large_batch_greedy_takes_the_mask_free_walk(nms, oracle):
     """A batch large enough for the greedy rule's mask-free walk: one workgroup per frame, survivors only
     as outranking boxes.  Every measure / compare / ties / offset / labels combination, ragged
-    counts, and thresholds that take the literal division."""
+    counts, and thresholds that take the literal division.  (With labels and the other thresholds the frames
+    go class by class; test_gpu_greedy_classes.py has labelled frames that are walked.)"""
     from concurrent.futures import ThreadPoolExecutor
 
     rng = np.random.default_rng(15)

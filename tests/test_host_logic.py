@@ -56,15 +56,23 @@ def test_small_frames_shares_fit_the_kernels(driver):
     assert taken > 100000
 
 
-def test_large_bins_of_labels_are_left_to_the_walk(driver):
-    """Greedy rule with labels: a bin is one wavefront's chain, so its bound is a share of the frame and no
-    bin of a long frame beyond a quarter of it is settled that way; frames of up to two tiles never are."""
-    lengths = list(range(1, 4097))
-    rows = [list(map(int, r.split())) for r in run(driver, "classes", stdin="\n".join(map(str, lengths))).split("\n") if r]
-    limits = dict(zip(lengths, (r[1] for r in rows)))
-    assert [n for n, r in zip(lengths, rows) if r[0]] == lengths[128:]
-    assert all(limits[n] == max(288, n // 4) for n in lengths)
-    assert limits[1024] < 1024 // 3 and limits[3000] < 3000 // 3
+def test_large_bins_of_labels_are_walked(driver):
+    """Greedy rule with labels: a bin is one wavefront's chain, so its bound is a share of the frame: no bin of half a
+    frame is settled that way, none of a third of a long frame.  Wavefronts per workgroup: a table of up to 4096 boxes
+    takes 16, no batch takes more wavefronts than its frames have tiles for."""
+    lengths = list(range(0, 4097))
+    for frames in (1, 768, 769, 65535):
+        out = run(driver, "classes", stdin="\n".join(f"{n} {frames}" for n in lengths)).split()
+        limits, waves = list(map(int, out[0::2])), list(map(int, out[1::2]))
+        assert all(2 * m < n or m == n == 0 for n, m in zip(lengths, limits))
+        assert all(3 * m < n for n, m in zip(lengths, limits) if n > 1344)
+        assert all((m == 0) == (n <= 192) for n, m in zip(lengths, limits))
+        assert limits == [largest_bin(n) for n in lengths]
+        assert waves == [16 if n > 1024 else (8 if frames <= 768 else 4) for n in lengths]
+
+
+def largest_bin(n):
+    return 0 if n <= 192 else (7 * n // 16 if n <= 1024 else max(448, n // 4))
 
 
 def test_workspace_layout_matches_the_size_helper(driver):
