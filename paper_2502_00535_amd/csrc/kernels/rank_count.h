@@ -4,7 +4,7 @@
 // ----------------------------------------------------------------------------- rank by counting
 
 // The rank of a box is the number of boxes that outrank it.  A sort of one chunk is the work of one
-// workgroup -- a chain of sixteen barriers, 20 us at 4096 boxes however few frames there are --, whereas
+// workgroup -- a chain of thirteen barriers, 16 us at 4096 boxes however few frames there are --, whereas
 // counting is n compares per box that depend on nothing: two VALU instructions per pair (compare, add
 // with carry), spread over as many workgroups as the chip holds.  It wins until the pairs take longer
 // than the chain: see nms_use_count_rank.
@@ -12,9 +12,9 @@
 // A workgroup stages the keys of its whole frame in LDS and ranks kElems neighbouring elements of the
 // input.  lane = (element, group); wavefronts and groups share the other keys out in units of four
 // (one 16-byte LDS read, the same address for all lanes of a group), and their counts meet in LDS.
-// Wide workgroups hold two elements per lane, so that a read serves eight compares per lane and not
-// four (at four the LDS reads and the compares take equally long); a batch of few boxes takes sixteen elements per
-// workgroup and four groups, to put one on every compute unit.
+// kElems: 64, or 16 and four groups (nms_count_rank_elements).  Two elements per lane (128), which a read
+// serves eight compares instead of four, gain only where the sort is as quick (120 x 500 boxes 5.7 us
+// against 6.8 with 64 elements, sorted 6.8; 64 x 500 4.3 against 4.5; 8 x 3000 9.8 against 9.6).
 // Equal keys: the lower index first, so the keys before the workgroup's elements count when they are
 // not larger, the keys behind them when they are smaller, and only its own elements need the index.
 // Integer keys: ranks are a permutation whatever the bits of the scores are.
@@ -27,9 +27,8 @@ rank_count_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
                   int n_max, int n_pad, int32_t *__restrict__ order, float *__restrict__ sorted5,
                   uint8_t *__restrict__ keep_preset, RankExtras ex)
 {
-    constexpr int kLanes = kElems < 64 ? kElems : 64;  // lanes that hold different elements
-    constexpr int kGroups = 64 / kLanes;
-    constexpr int kPer = kElems / kLanes;               // elements per lane
+    static_assert(kElems <= 64, "one element per lane");
+    constexpr int kGroups = 64 / kElems;
     __shared__ uint4 keys4[kChunk / 4];
     __shared__ int partial[kCountWaves][kElems];
     unsigned *keys = reinterpret_cast<unsigned *>(keys4);
@@ -59,57 +58,39 @@ rank_count_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
         for (int i = tid; i < 4 * units; i += kCountThreads)
             keys[i] = i < n_f ? (unsigned)(nms_rank_key(scores_f[i], (unsigned)i) >> 32) : ~0u;  // (behind the last element: smaller than none)
         __syncthreads();
-        unsigned mine[kPer];
-        int before[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = e0 + 64 * q + lane % kLanes;
-            mine[q] = keys[e < n_f ? e : e0];
-            before[q] = 0;
-        }
-        const int first = wave * kGroups + lane / kLanes;  // this lane's first unit
+        const int e = e0 + lane % kElems;
+        const unsigned mine = keys[e < n_f ? e : e0];
+        int before = 0;
+        const int first = wave * kGroups + lane / kElems;  // this lane's first unit
         constexpr int kStride = kCountWaves * kGroups;
         const int own = e0 / 4;                            // units [own, own_end): the workgroup's own elements
         const int own_end = own + kElems / 4 < units ? own + kElems / 4 : units;
 #pragma unroll 2
         for (int u = first; u < own; u += kStride) {
             const uint4 k = keys4[u];
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                before[q] += k.x <= mine[q];
-                before[q] += k.y <= mine[q];
-                before[q] += k.z <= mine[q];
-                before[q] += k.w <= mine[q];
-            }
+            before += k.x <= mine;
+            before += k.y <= mine;
+            before += k.z <= mine;
+            before += k.w <= mine;
         }
         for (int u = own + first; u < own_end; u += kStride) {
             const uint4 k = keys4[u];
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int e = e0 + 64 * q + lane % kLanes;
-                before[q] += k.x < mine[q] || (k.x == mine[q] && 4 * u < e);
-                before[q] += k.y < mine[q] || (k.y == mine[q] && 4 * u + 1 < e);
-                before[q] += k.z < mine[q] || (k.z == mine[q] && 4 * u + 2 < e);
-                before[q] += k.w < mine[q] || (k.w == mine[q] && 4 * u + 3 < e);
-            }
+            before += k.x < mine || (k.x == mine && 4 * u < e);
+            before += k.y < mine || (k.y == mine && 4 * u + 1 < e);
+            before += k.z < mine || (k.z == mine && 4 * u + 2 < e);
+            before += k.w < mine || (k.w == mine && 4 * u + 3 < e);
         }
 #pragma unroll 2
         for (int u = own_end + first; u < units; u += kStride) {
             const uint4 k = keys4[u];
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                before[q] += k.x < mine[q];
-                before[q] += k.y < mine[q];
-                before[q] += k.z < mine[q];
-                before[q] += k.w < mine[q];
-            }
+            before += k.x < mine;
+            before += k.y < mine;
+            before += k.z < mine;
+            before += k.w < mine;
         }
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-#pragma unroll
-            for (int step = kLanes; step < 64; step <<= 1) before[q] += __shfl_xor(before[q], step);
-            if (lane < kLanes) partial[wave][64 * q + lane] = before[q];
-        }
+        for (int step = kElems; step < 64; step <<= 1) before += __shfl_xor(before, step);
+        if (lane < kElems) partial[wave][lane] = before;
         __syncthreads();
     }
     if (tid >= kElems || e_mine >= n_pad) return;

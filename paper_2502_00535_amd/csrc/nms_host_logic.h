@@ -97,11 +97,10 @@ NMS_HD bool nms_use_count_rank(int n_max, int frames, int sort_chunk)
     return n_max <= sort_chunk && (long long)frames * n_max <= 32768;
 }
 
-// Elements per workgroup there: the most that leave two workgroups for every compute unit.
+// Elements per workgroup there.
 NMS_HD int nms_count_rank_elements(int n_max, int frames)
 {
-    const long long boxes = (long long)frames * n_max;
-    return boxes >= 512 * 128 ? 128 : (boxes >= 256 * 64 ? 64 : 16);
+    return (long long)frames * n_max >= 16384 ? 64 : 16;
 }
 
 // ---- greedy rule with labels ----------------------------------------------------------------------

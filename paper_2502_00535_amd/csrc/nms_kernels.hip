@@ -112,7 +112,6 @@ int count_rank_launch(const float *boxes, const float *scores, const int32_t *co
                       int32_t *order, float *sorted5, uint8_t *keep_preset, const RankExtras &extras, hipStream_t stream)
 {
     const int n_pad = nms_padded_n(n_max);
-    // elements per workgroup: as many as leave a workgroup for every compute unit
     const int elems = nms_count_rank_elements(n_max, frames);
     const dim3 grid((n_pad + elems - 1) / elems, frames);
     begin_launch();
@@ -120,8 +119,7 @@ int count_rank_launch(const float *boxes, const float *scores, const int32_t *co
     rank_count_kernel<E_><<<grid, dim3(kCountThreads), 0, stream>>>(boxes, scores, counts, n_max, n_pad, order, sorted5, \
                                                                     keep_preset, extras)
     if (elems == 16) NMS_LAUNCH_COUNT(16);
-    else if (elems == 64) NMS_LAUNCH_COUNT(64);
-    else NMS_LAUNCH_COUNT(128);
+    else NMS_LAUNCH_COUNT(64);
 #undef NMS_LAUNCH_COUNT
     return launch_status();
 }

@@ -83,6 +83,13 @@ int main(int argc, char **argv)
         printf("taken %lld bad %lld\n", taken, bad);
         return 0;
     }
+    if (!strcmp(argv[1], "count_rank")) {
+        // elements per workgroup of the counting rank step (0: the batch sorts), for every batch shape given on stdin
+        int n, frames;
+        while (scanf("%d %d", &n, &frames) == 2)
+            printf("%d\n", nms_use_count_rank(n, frames, 4096) ? nms_count_rank_elements(n, frames) : 0);
+        return 0;
+    }
     if (!strcmp(argv[1], "classes")) {
         // largest bin of labels that one wavefront settles, wavefronts per workgroup in a batch of such frames
         int n, frames;

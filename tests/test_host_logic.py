@@ -4,6 +4,7 @@ hold), the unit counts, the sort keys on every kind of score, the workspace layo
 nms_workspace_bytes, and the pair test compiled by a plain host compiler -- all built from
 the same headers the kernels include, with g++ and with the sanitizers on."""
 import os
+import re
 import subprocess
 from fractions import Fraction
 
@@ -54,6 +55,21 @@ def test_small_frames_shares_fit_the_kernels(driver):
     taken, bad = int(out[-1].split()[1]), int(out[-1].split()[3])
     assert bad == 0, out
     assert taken > 100000
+
+
+def count_rank_elements(driver, shapes):
+    return list(map(int, run(driver, "count_rank", stdin="\n".join(f"{n} {f}" for n, f in shapes)).split()))
+
+
+def test_every_form_of_the_counting_rank_step_is_reached(driver):
+    """Batches of up to 32,768 boxes in frames of up to 4096 count; the forms the launch code names are those that some
+    such batch takes."""
+    shapes = [(n, f) for n in (*range(1, 200), *range(200, 4300, 41), 4095, 4096, 4097) for f in (1, 2, 3, 5, 8, 13, 30, 70, 200, 1000, 32768 // n, 32768 // n + 1)
+              if f > 0]
+    got = count_rank_elements(driver, shapes)
+    assert [e > 0 for e in got] == [n <= 4096 and n * f <= 32768 for n, f in shapes]
+    hip = open(os.path.join(ROOT, "paper_2502_00535_amd", "csrc", "nms_kernels.hip")).read()
+    assert {e for e in got if e} == {int(e) for e in re.findall(r"NMS_LAUNCH_COUNT\((\d+)\);", hip)}
 
 
 def test_large_bins_of_labels_are_walked(driver):
