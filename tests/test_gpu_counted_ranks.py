@@ -32,12 +32,25 @@ def rank(nms, boxes, scores, counts):
     return order.cpu().numpy(), table.cpu().numpy()
 
 
-# frames of the small batch: 16, 64 and 128 elements per workgroup, the last batch that counts (32,768 boxes)
+def oracle_rank(boxes, scores, n_pad):
+    """Order and box table of one frame, from a stable sort on the host."""
+    c = len(scores)
+    order = np.argsort(-scores.astype(np.float64), kind="stable")
+    rows = np.zeros((n_pad, 4), np.float32)
+    rows[:c] = boxes[order]
+    one = np.float32(1)
+    areas = ((rows[:, 2] - rows[:, 0]) + one) * ((rows[:, 3] - rows[:, 1]) + one)
+    return order, np.concatenate([rows.reshape(-1), areas])
+
+
+# The small batch counts, with 16 or 64 elements per workgroup (both occur below; the last that counts has 32,768
+# boxes), the large one sorts.
 @pytest.mark.parametrize("n,few", [(1, 1), (63, 1), (64, 300), (65, 1), (129, 130), (1000, 17), (1000, 32), (1025, 3), (2048, 16),
                                    (4095, 1), (4095, 4), (4096, 1), (4096, 5), (4096, 8)])
 def test_counted_ranks_equal_sorted_ranks(nms, n, few):
     print(f"case n={n} frames={few}", flush=True)
     many = max(few, 32768 // n + 1)  # a batch that sorts
+    assert n * few <= 32768 < n * many  # the bound that test_host_logic.py pins
     rng = np.random.default_rng(n + few)
     boxes = np.zeros((many, n, 4), np.float32)
     scores = np.zeros((many, n), np.float32)
@@ -54,6 +67,8 @@ def test_counted_ranks_equal_sorted_ranks(nms, n, few):
         order, table = rank(nms, boxes[:few], scores[:few], None if counts is None else counts[:few])
         assert np.array_equal(order, want_order[:few])
         assert np.array_equal(table.view(np.uint32), want_table[:few].view(np.uint32))
-        f = few - 1
-        c = n if counts is None else int(np.clip(counts[f], 0, n))
-        assert np.array_equal(order[f, :c], np.argsort(-scores[f, :c].astype(np.float64), kind="stable"))
+        for f in range(few):
+            c = n if counts is None else int(np.clip(counts[f], 0, n))
+            host_order, host_table = oracle_rank(boxes[f, :c], scores[f, :c], nms.nms_padded_n(n))
+            assert np.array_equal(order[f, :c], host_order), f"frame {f}"
+            assert np.array_equal(table[f].view(np.uint32), host_table.view(np.uint32)), f"frame {f}"
