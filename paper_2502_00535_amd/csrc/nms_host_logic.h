@@ -89,18 +89,22 @@ NMS_HD NmsRunLayout nms_run_layout(int n_max, int n_pad, int frames, int sort_ch
 // ---- rank step ----------------------------------------------------------------------------------
 // Ranks by counting (n compares per box over the whole chip) instead of a sort of one workgroup per
 // frame, whose time hardly depends on the number of frames.  Measured, the rank step alone, counted
-// against sorted: 1 x 4096 4.9 us against 15.4, 8 x 4096 12.5 / 15.9, 16 x 4096 20.5 / 16.0; 8 x 3000
-// 9.7 / 17.4, 16 x 2048 8.0 / 10.1, 24 x 2048 10.7 / 10.2, 32 x 1000 5.8 / 8.3, 64 x 1000 9.3 / 8.3, 64 x 500
-// 4.7 / 6.9, 128 x 500 7.3 / 7.0, 128 x 256 3.9 / 6.3: the line is a number of boxes.
+// against sorted, us: 1 x 4096 4.8 / 16.2, 4 x 4096 8.3 / 16.4, 8 x 4096 12.2 / 16.5, 10 x 4096 16.8 / 16.6; 8 x 3000 9.6 / 14.0,
+// 14 x 3000 13.2 / 14.1; 16 x 2048 7.9 / 10.5, 24 x 2048 10.4 / 10.5; 32 x 1000 5.6 / 8.1, 64 x 1000 9.0 / 8.2; 64 x 500
+// 4.5 / 6.8, 120 x 500 6.8 / 6.8; 128 x 256 3.7 / 6.2; 512 x 64 3.0 / 6.6: the line is a number of boxes.
 NMS_HD bool nms_use_count_rank(int n_max, int frames, int sort_chunk)
 {
     return n_max <= sort_chunk && (long long)frames * n_max <= 32768;
 }
 
-// Elements per workgroup there.
+// Elements per workgroup there.  Every workgroup stages its whole frame, so sixteen only pay while that
+// puts one workgroup, or two of longer frames, on a compute unit that sixty-four would leave idle.  16 against 64
+// elements, us: 1 x 4096 4.8 / 7.8, 2 x 4096 6.5 / 8.0, 3 x 4096 8.7 / 8.1; 3 x 2500 5.1 / 5.9, 4 x 2500 6.7 / 6.0; 6 x 1300 4.2 / 4.4,
+// 7 x 1300 5.3 / 4.4; 4 x 1000 3.3 / 3.7, 5 x 1000 3.9 / 3.8, 16 x 1000 6.2 / 4.1; 8 x 500 3.1 / 3.2, 10 x 500 3.4 / 3.2; 1 x 360 2.8 / 2.8,
+// 17 x 360 3.3 / 3.0; 64 x 64 2.9 / 2.4.
 NMS_HD int nms_count_rank_elements(int n_max, int frames)
 {
-    return (long long)frames * n_max >= 16384 ? 64 : 16;
+    return n_max > 384 && (long long)frames * n_max <= (n_max > 1024 ? 8192 : 4096) ? 16 : 64;
 }
 
 // ---- greedy rule with labels ----------------------------------------------------------------------

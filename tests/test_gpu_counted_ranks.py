@@ -45,8 +45,8 @@ def oracle_rank(boxes, scores, n_pad):
 
 # The small batch counts, with 16 or 64 elements per workgroup (both occur below; the last that counts has 32,768
 # boxes), the large one sorts.
-@pytest.mark.parametrize("n,few", [(1, 1), (63, 1), (64, 300), (65, 1), (129, 130), (1000, 17), (1000, 32), (1025, 3), (2048, 16),
-                                   (4095, 1), (4095, 4), (4096, 1), (4096, 5), (4096, 8)])
+@pytest.mark.parametrize("n,few", [(1, 1), (63, 1), (64, 300), (65, 1), (129, 130), (384, 1), (385, 1), (1000, 4), (1000, 17), (1000, 32),
+                                   (1025, 3), (2048, 4), (2048, 16), (4095, 1), (4095, 4), (4096, 1), (4096, 2), (4096, 5), (4096, 8)])
 def test_counted_ranks_equal_sorted_ranks(nms, n, few):
     print(f"case n={n} frames={few}", flush=True)
     many = max(few, 32768 // n + 1)  # a batch that sorts

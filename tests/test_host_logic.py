@@ -72,6 +72,16 @@ def test_every_form_of_the_counting_rank_step_is_reached(driver):
     assert {e for e in got if e} == {int(e) for e in re.findall(r"NMS_LAUNCH_COUNT\((\d+)\);", hip)}
 
 
+def test_counting_rank_step_takes_the_measured_form(driver):
+    """The quicker form of the rank step at shapes either side of the lines, where the two differ by 3 % or more."""
+    quicker = {16: [(4096, 1), (4096, 2), (3500, 2), (3000, 2), (2500, 3), (2048, 4), (1777, 4), (1300, 3), (1000, 1), (1000, 4), (768, 5), (640, 6),
+                    (500, 1), (500, 6)],
+               64: [(4096, 3), (4096, 8), (3500, 3), (3000, 3), (2500, 4), (2048, 5), (2048, 16), (1777, 5), (1777, 16), (1300, 7), (1000, 9),
+                    (1000, 16), (1000, 32), (768, 8), (640, 9), (500, 10), (500, 32), (360, 17), (256, 16), (128, 32), (64, 1), (64, 64)]}
+    for elements, shapes in quicker.items():
+        assert count_rank_elements(driver, shapes) == [elements] * len(shapes)
+
+
 def test_large_bins_of_labels_are_walked(driver):
     """Greedy rule with labels: a bin is one wavefront's chain, so its bound is a share of the frame: no bin of half a
     frame is settled that way, none of a third of a long frame.  Wavefronts per workgroup: a table of up to 4096 boxes
