@@ -194,10 +194,17 @@ def _ws(t):
     return _ptr(t, None, "workspace"), t.numel() * t.element_size()
 
 
+# The current stream's handle without a Stream object around it, where this torch has that (it is not part of
+# torch's public interface, so another version may lack it).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(status: int, where: str):

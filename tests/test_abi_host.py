@@ -4,6 +4,8 @@ error is reported before anything is launched.  No compute call is made here."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -358,3 +360,13 @@ def test_binding_refuses_undersized_tensors(nms, monkeypatch):
         nms.nms_run_ws(ok["boxes"], ok["scores"], F * n + 1, 0.5, ok["keep"], ws)
     with pytest.raises(ValueError, match="elements, the call needs"):
         nms.nms_run(ok["boxes"], ok["scores"], n, 0.5, torch.zeros(n - 1, dtype=torch.uint8))
+
+
+def test_binding_on_a_torch_without_the_raw_stream(nms):
+    """torch._C._cuda_getCurrentRawStream is not public: without it the binding loads and asks the public function."""
+    code = ("import torch; del torch._C._cuda_getCurrentRawStream\n"
+            "import paper_2502_00535_amd.binding as nms\n"
+            "torch.cuda.current_stream = lambda: type('S', (), {'cuda_stream': 4660})()\n"
+            "assert nms._stream(None) == 4660 and nms._stream(type('S', (), {'cuda_stream': 7})()) == 7\n")
+    proc = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert proc.returncode == 0, proc.stderr[-2000:]

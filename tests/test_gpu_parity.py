@@ -424,3 +424,18 @@ def test_calls_can_be_captured_in_a_hip_graph(nms, oracle):
         assert np.array_equal(keep_e.cpu().numpy(), want), f"replay {rep}: paper rule, early-exit route"
         assert np.array_equal(keep_g.cpu().numpy(), want_g), f"replay {rep}: greedy rule"
         assert np.array_equal(keep_x.cpu().numpy(), want_x), f"replay {rep}: variants"
+
+
+def test_current_stream_handle_is_torchs(nms):
+    """Without a stream argument a call goes to torch's current stream, by either way the binding has to find it."""
+    import torch
+
+    side = torch.cuda.Stream()
+    raw = nms._raw_stream
+    try:
+        for nms._raw_stream in (raw, None):
+            assert (nms._stream(None) or 0) == torch.cuda.current_stream().cuda_stream
+            with torch.cuda.stream(side):
+                assert nms._stream(None) == side.cuda_stream == nms._stream(side)
+    finally:
+        nms._raw_stream = raw
