@@ -686,7 +686,6 @@ int nms_run_greedy_batched(const float *boxes, const float *scores, const int32_
     if (!workspace || ws_bytes < nms_greedy_workspace_bytes(n_max, frames) || ((uintptr_t)workspace & 255))
         return NMS_ERR_WORKSPACE;
     // batches with a few dozen frames or more: one workgroup walks each frame, no mask
-    // (measured crossover against rank + mask + sweep: 32 frames of 4096 boxes, 64 of 2048)
     if (n_max <= kChunk && (long long)frames * n_max >= kGreedyFusedBoxes)
         return run_greedy_fused(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace,
                                 static_cast<hipStream_t>(stream));
