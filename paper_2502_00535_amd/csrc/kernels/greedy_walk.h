@@ -129,7 +129,7 @@ __device__ __forceinline__ unsigned long long fused_second(unsigned long long wo
 // matter).  !EX: the default measure (MODE kExBoundary = the division-free form of nms_pair.h, else the
 // literal division).  EX: the variants.  With scores or labels to look at, what follows the first test sits
 // behind a wave-uniform branch (40 frames of 4096 boxes of one label, which are walked, IoU, the whole call: 191 -> 172 us
-// where much is eliminated, 833 -> 573 where little is).  IoU alone takes the float64 compare for every pair: the branch gains 1 % where
+// where much is eliminated, 833 -> 578 where little is).  IoU alone takes the float64 compare for every pair: the branch gains 1 % where
 // few pairs hit (64 x 2100) and costs 5 to 9 % where many do (300 x 600: 52 -> 57 us).
 template <bool EX, bool IOU, int MODE, bool AUX>
 __device__ __forceinline__ unsigned long long fused_word(unsigned long long open, const float4 v, float v_area, float v_T,
