@@ -433,13 +433,14 @@ small_frames_kernel(const float *__restrict__ boxes, const float *__restrict__ s
     small_frames_body<FAST, 1, kSmallWaves>(boxes, scores, counts, n_max, parts, th, keep_out);
 }
 
-// Frames of at most 1024 E boxes, E = 2 or 4; a workgroup's share is at most 1024 victims (parts >= tiles / 16).
-template <bool FAST, int E>
+// Frames of at most 1024 E boxes, E = 2 or 4, thresholds that take the literal division; a workgroup's share is at most 1024
+// victims (parts >= tiles / 16).
+template <int E>
 __global__ void __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 mid_frames_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,
                   int n_max, int parts, NmsThetaConst th, uint8_t *__restrict__ keep_out)
 {
-    small_frames_body<FAST, E, kSmallWaves>(boxes, scores, counts, n_max, parts, th, keep_out);
+    small_frames_body<false, E, kSmallWaves>(boxes, scores, counts, n_max, parts, th, keep_out);
 }
 
 // Frames of at most 512 boxes: workgroups of eight wavefronts, up to four of them on a compute unit.

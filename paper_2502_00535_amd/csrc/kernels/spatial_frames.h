@@ -1,0 +1,457 @@
+// Part of nms_kernels.hip (included there, inside its anonymous namespace): the paper's rule on frames of up to 4096 boxes, boxes in order of place, one launch.
+#pragma once
+
+// ----------------------------------------------------------------------------- frames in order of place
+
+// Two boxes that do not touch decide nothing, and of the pairs of a picture few touch: 159 of 4096 boxes
+// touch a given one on regressed anchors, 103 on clustered detections.  Algorithm 1 asks of a pair only which
+// box is ranked first, one compare of the rank keys, so nothing has to be sorted by score.  Here the boxes are
+// put in order of PLACE, and the pairs that are far apart are left out.  A workgroup per frame (or several,
+// which build the same tables and share the victims), everything in LDS:
+//
+//   cells     a grid over the centres, in four classes of box size (a large box among small ones would stretch
+//             the hull of its tile); boxes are counted per cell, and a prefix sum over the cells, a Hilbert curve
+//             per class, gives every cell its rows of the table;
+//   tiles     64 rows: their hull (the smallest box around them), smallest threshold T and best rank;
+//   stage 1   lane = victim, against the best-ranked box of each of the nine cells around it, in its own size
+//             class and in the next smaller one (a box is eliminated by what it covers).  This settles seven
+//             victims of eight: 504 of 4096 are left on anchors, of which 362 survive;
+//   stage 2   the victims left, four neighbours at a time, lane = outranking box, against the tiles that can
+//             eliminate one of them (five to six of the 64): min, max, rounded subtraction, addition and
+//             multiplication are all monotone, so the victim's float32 intersection with a tile's hull is no
+//             smaller than with any box of the tile, and where it stays below the tile's smallest T no pair
+//             test of the tile can succeed.
+//
+// The pair test itself is that of the other routes, and a pair is left out only when it is certain to fail or its
+// victim has an eliminator: the same keep vector, bit for bit.  For thresholds with a division-free form (T > 0).
+// The order of boxes inside a cell and the boxes of stage 1 are whatever the atomics make them; no result
+// depends on them.
+//
+// What bounds it: on large batches VALU issue and LDS bandwidth of stage 2 (of 93 k cycles at 256 x 4096 anchors 17 k are
+// the tables, 20 k stage 1, 55 k stage 2); on small ones the chain of seven barriers (256 x 1024: 18 k cycles).
+// Measured, whole call, us, against the kernels that took these batches before (rank order, early exit):
+// 256 x 4096 anchors 45.5 / 145, clustered 33.0 / 99; 48 ragged frames of 1777 boxes 10.0 / 29.3; 64 x 1024 8.5 / 11.7;
+// 512 x 1024 anchors 45 / 133.
+constexpr int kPlaceWaves = 16;  // most wavefronts of a workgroup
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_keep(float x)  // x of another lane; the lane's own where there is none
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROWS, 0xf, false));
+}
+// Minimum over each row of sixteen lanes, in the row's last lane.
+__device__ __forceinline__ float row_min(float x)
+{
+    x = fminf(x, dpp_keep<0x111, 0xf>(x));  // row_shr:1, 2, 4, 8
+    x = fminf(x, dpp_keep<0x112, 0xf>(x));
+    x = fminf(x, dpp_keep<0x114, 0xf>(x));
+    x = fminf(x, dpp_keep<0x118, 0xf>(x));
+    return x;
+}
+
+// The same over the wavefront, wave-uniform.
+__device__ __forceinline__ float wave_min(float x)
+{
+    x = row_min(x);
+    x = fminf(x, dpp_keep<0x142, 0xa>(x));  // row_bcast:15 into rows 1, 3
+    x = fminf(x, dpp_keep<0x143, 0xc>(x));  // row_bcast:31 into rows 2, 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// The grid over a frame's box centres (doubled centres: x1 + x2): AXIS x AXIS cells in four classes of box size.
+struct PlaceGrid {
+    float x0, y0, sx, sy;  // column = (x1 + x2 - x0) * sx
+};
+// A range that is empty or not finite maps to column 0.
+__device__ __forceinline__ float place_scale(float lo, float hi, float cells)
+{
+    const float range = hi - lo;
+    return range > 0x1p-100f && range < 0x1p100f ? cells * __builtin_amdgcn_rcpf(range) : 0.0f;
+}
+// Cell number: class (area below 2, 8, 32 cells of a 16 x 16 grid, or more), row, column.  Any coordinates give a legal cell:
+// clamped before the conversion, masked after.
+template <int AXIS>
+__device__ __forceinline__ unsigned place_cell(const float4 b, const PlaceGrid &g)
+{
+    const float cx = fminf(fmaxf((b.x + b.z - g.x0) * g.sx, 0.0f), (float)(AXIS - 1));
+    const float cy = fminf(fmaxf((b.y + b.w - g.y0) * g.sy, 0.0f), (float)(AXIS - 1));
+    const float t = ((b.z - b.x) * g.sx) * ((b.w - b.y) * g.sy) * (256.0f / (AXIS * AXIS));  // (g is for doubled coordinates: t = area in cells / 4)
+    const unsigned cls = t < 0.5f ? 0u : (t < 2.0f ? 1u : (t < 8.0f ? 2u : 3u));
+    unsigned c = (cls * AXIS + (unsigned)(int)cy) * AXIS + (unsigned)(int)cx;
+    asm volatile("" : "+v"(c));
+    return c & (unsigned)(4 * AXIS * AXIS - 1);
+}
+// The cells of a class in the order of a Hilbert curve: neighbours on the curve are neighbours in the picture.
+template <int AXIS>
+struct HilbertCells {
+    uint16_t at[AXIS * AXIS];
+    constexpr HilbertCells() : at()
+    {
+        for (unsigned i = 0; i < (unsigned)(AXIS * AXIS); ++i) {
+            unsigned d = i, x = 0, y = 0;
+            for (unsigned s = 1; s < (unsigned)AXIS; s <<= 1) {
+                const unsigned rx = 1u & (d >> 1), ry = 1u & (d ^ rx);
+                if (ry == 0) {
+                    if (rx == 1) {
+                        x = s - 1u - x;
+                        y = s - 1u - y;
+                    }
+                    const unsigned t = x;
+                    x = y;
+                    y = t;
+                }
+                x += s * rx;
+                y += s * ry;
+                d >>= 2;
+            }
+            at[i] = (uint16_t)(y * AXIS + x);
+        }
+    }
+};
+template <int AXIS>
+__device__ constexpr HilbertCells<AXIS> hilbert_cells = HilbertCells<AXIS>();
+// The cell that comes i-th: class by class, every second class backwards.
+template <int AXIS>
+__device__ __forceinline__ unsigned curve_cell(unsigned i)
+{
+    constexpr unsigned kClass = AXIS * AXIS;
+    const unsigned cls = i / kClass, d = i % kClass;
+    return cls * kClass + hilbert_cells<AXIS>.at[(cls & 1u) ? kClass - 1u - d : d];
+}
+
+constexpr int kPlaceGroup = 4;  // victims of a wavefront in the second stage
+
+// The tables of a frame.  P rows, AXIS cells per axis and size class.
+template <int P, int AXIS>
+struct PlaceShared {
+    static constexpr int kCells = 4 * AXIS * AXIS;
+    float4 box[P];
+    float T[P];
+    unsigned upper[P];                // upper half of the rank key
+    unsigned meta[P];                 // input index, cell << 16
+    union {
+        uint8_t keep[P];              // parts == 1: by input index
+        uint16_t row[P];              // parts > 1: row of an input element
+    };
+    float4 hull[kTile];               // per tile
+    uint2 tile[kTile];                // smallest T, best (smallest) upper half of the tile
+    union {
+        __align__(16) unsigned start[kCells];              // boxes per cell, then their first rows
+        uint16_t list[(P > 2 * kCells ? P : 2 * kCells)];  // after that: rows still alive after the first stage
+    };
+    unsigned best[kCells + 2 * AXIS + 2];  // from AXIS + 1 on: a well-ranked box of the cell: 20 bits of the rank key, 12 bits of the row; ~0: no box
+    unsigned wave_sum[kPlaceWaves];
+    unsigned long long dead[kPlaceWaves];  // first stage, few victims: per 64 of them
+    unsigned listed, next;
+};
+
+// W: wavefronts; E: boxes per thread (frames of at most 64 W E).  Grid: frames * parts workgroups; a workgroup builds the tables of the whole
+// frame and takes the victims of every parts-th 64 rows.
+template <int W, int E, int AXIS>
+__global__ void __launch_bounds__(W * 64)
+spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,
+                      int n_max, int split_log2, NmsThetaConst th, uint8_t *__restrict__ keep_out)
+{
+    constexpr int kThreads = W * 64;
+    constexpr int P = E * kThreads;
+    constexpr int kPer = 4 * AXIS * AXIS / kThreads;  // cells per thread in the prefix sum
+    static_assert(kPer >= 1 && kPer * kThreads == 4 * AXIS * AXIS && E <= 4 && P <= 4096, "cells per thread, sixteen lanes per tile, rows in 12 bits");
+    __shared__ PlaceShared<P, AXIS> sh;
+    const int f = blockIdx.x;
+    const int part = blockIdx.y, parts = gridDim.y;
+    const int tid = (int)threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_f = frame_count(counts, f, n_max);
+    const float4 *box_f = reinterpret_cast<const float4 *>(boxes) + (size_t)f * n_max;
+    const float *score_f = scores + (size_t)f * n_max;
+    uint8_t *keep_f = keep_out + (size_t)f * n_max;
+    if (part == 0)
+        for (int i = n_f + tid; i < n_max; i += kThreads) keep_f[i] = 0;
+    if (n_f == 0) return;
+
+    const float4 sample = box_f[(unsigned)(lane * n_f) / 64u];
+    float4 b[E];
+    unsigned upper[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+        const int e = q * kThreads + tid;
+        b[q] = box_f[e < n_f ? e : 0];
+        upper[q] = (unsigned)(nms_rank_key(score_f[e < n_f ? e : 0], 0u) >> 32);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        sh.start[i * kThreads + tid] = 0u;
+        sh.best[i * kThreads + tid] = ~0u;
+    }
+    if (tid < 2 * AXIS + 2) sh.best[4 * AXIS * AXIS + tid] = ~0u;
+    if (parts == 1) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) sh.keep[q * kThreads + tid] = 0;
+    }
+    if (tid < kPlaceWaves) sh.dead[tid] = 0ull;
+    if (tid == 0) {
+        sh.listed = 0u;
+        sh.next = 0u;
+    }
+    unsigned mine[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) mine[i] = curve_cell<AXIS>((unsigned)(kPer * tid + i));
+    lds_barrier();
+
+    // ---- the grid, over the centres of 64 boxes spread over the input (what lies outside goes to the border cells)
+    PlaceGrid grid;
+    {
+        const float cx = sample.x + sample.z, cy = sample.y + sample.w;
+        grid.x0 = wave_min(cx), grid.y0 = wave_min(cy);
+        const float hx = wave_min(-cx), hy = wave_min(-cy);
+        grid.sx = place_scale(grid.x0, -hx, (float)AXIS);
+        grid.sy = place_scale(grid.y0, -hy, (float)AXIS);
+    }
+
+    // ---- boxes per cell, the first row of every cell along the curve, the table
+    unsigned cell[E], within[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+        cell[q] = place_cell<AXIS>(b[q], grid);
+        within[q] = 0;
+        if (q * kThreads + tid < n_f) within[q] = atomicAdd(&sh.start[cell[q]], 1u);
+    }
+    lds_barrier();
+    {
+        unsigned in_cell[kPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            in_cell[i] = sh.start[mine[i]];
+            sum += in_cell[i];
+        }
+        const unsigned incl = wave_inclusive_sum(sum);
+        if (lane == 63) sh.wave_sum[wave] = incl;
+        lds_barrier();
+        const unsigned sums = row16_inclusive_sum(sh.wave_sum[lane & (W - 1)]);
+        unsigned at = (wave == 0 ? 0u : (unsigned)__builtin_amdgcn_readlane((int)sums, wave - 1)) + incl - sum;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            sh.start[mine[i]] = at;
+            at += in_cell[i];
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+        const int e = q * kThreads + tid;
+        if (e < n_f) {
+            const unsigned row = sh.start[cell[q]] + within[q];
+            sh.box[row] = b[q];
+            const float T = nms_pair_threshold(nms_box_area(b[q].x, b[q].y, b[q].z, b[q].w), th.m);
+            sh.T[row] = T;
+            sh.upper[row] = upper[q];
+            sh.meta[row] = (unsigned)e | (cell[q] << 16);
+            atomicMin(&sh.best[AXIS + 1 + cell[q]], (upper[q] & ~4095u) | row);
+            if (parts > 1) sh.row[e] = (uint16_t)row;
+        }
+    }
+    const int tiles = (n_f + kTile - 1) / kTile;
+    if (tid < tiles * kTile - n_f) {  // rows behind the last box: eliminate nothing
+        sh.box[n_f + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sh.T[n_f + tid] = INFINITY;
+        sh.upper[n_f + tid] = ~0u;
+        sh.meta[n_f + tid] = 0u;
+    }
+    lds_barrier();
+
+    // ---- per tile: hull, smallest T, best rank; sixteen lanes share a tile
+    {
+        const int t = tid / 16;
+        if (t < tiles) {  // (whole rows of sixteen lanes)
+            float4 h = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+            float least = INFINITY;
+            unsigned best = ~0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = t * kTile + i * 16 + (lane & 15);
+                const float4 v = sh.box[row];
+                const float T = sh.T[row];
+                const unsigned u = sh.upper[row];
+                const bool there = row < n_f;
+                h.x = fminf(h.x, there ? v.x : INFINITY);
+                h.y = fminf(h.y, there ? v.y : INFINITY);
+                h.z = fminf(h.z, there ? -v.z : INFINITY);
+                h.w = fminf(h.w, there ? -v.w : INFINITY);
+                least = fminf(least, T);
+                best = u < best ? u : best;
+            }
+            h.x = row_min(h.x), h.y = row_min(h.y), h.z = row_min(h.z), h.w = row_min(h.w);
+            least = row_min(least);
+            best = row16_min(best);
+            if ((lane & 15) == 15) {
+                sh.hull[t] = make_float4(h.x, h.y, -h.z, -h.w);
+                sh.tile[t] = make_uint2(__float_as_uint(least), best);
+            }
+        }
+    }
+    // ---- first stage: lane = victim, against a well-ranked box of each of the cells around, in its own size class and the next
+    // smaller: six lines of three cells, shared out among several wavefronts while there are fewer tiles of victims than those
+    // (one workgroup: 64 rows of the table; several: 64 neighbours of the input -- the order of rows inside a cell is each workgroup's own)
+    const int split = 1 << split_log2;
+    auto victim_row = [&](int t, bool &there) __attribute__((always_inline)) {
+        const int e = t * kTile + lane;
+        there = e < n_f;
+        return parts == 1 ? (there ? e : n_f - 1) : (int)sh.row[there ? e : n_f - 1];
+    };
+#pragma unroll 1
+    for (int t = part + parts * (wave >> split_log2); t < tiles; t += parts * W) {
+        bool owned;
+        const int row = victim_row(t, owned);
+        const float4 v = sh.box[row];
+        const unsigned v_key = sh.upper[row] & ~4095u;
+        const unsigned meta = sh.meta[row], c = meta >> 16;
+        bool alive = owned;
+        const bool smallest = c < (unsigned)(AXIS * AXIS);
+        // the cells of line dy of the class `below` smaller (at the border of the grid the cells of a neighbouring line: any box will do)
+        auto try_line = [&](int below, int dy) __attribute__((always_inline)) {
+            if (!alive || (below && smallest)) return;
+            const unsigned *at_line = sh.best + c + (AXIS + 1 + AXIS * dy - AXIS * AXIS * below);
+            unsigned r[3];
+            float4 cb[3];
+            float cT[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) r[x] = at_line[x - 1];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                cb[x] = sh.box[r[x] & (P - 1)];  // (of an empty cell: whatever is there, it is ranked before nothing)
+                cT[x] = sh.T[r[x] & (P - 1)];
+            }
+#pragma unroll
+            for (int x = 0; x < 3; ++x)  // (equal in the upper 20 bits of the key: left to the second stage)
+                alive = alive && !(nms_eliminates_fast(v.x, v.y, v.z, v.w, cb[x].x, cb[x].y, cb[x].z, cb[x].w, cT[x]) && r[x] < v_key);
+        };
+        if (split_log2 == 0) {
+#pragma unroll 1
+            for (int below = 0; below < 2; ++below) {
+#pragma unroll
+                for (int y = 0; y < 3; ++y) try_line(below, y == 2 ? -1 : y);
+                if (__ballot(alive) == 0) break;
+            }
+        } else {
+#pragma unroll 1
+            for (int l = wave & (split - 1); l < 6; l += split) {
+                const int y = l >= 3 ? l - 3 : l;
+                try_line(l >= 3 ? 1 : 0, y == 2 ? -1 : y);
+            }
+            const unsigned long long gone = __ballot(owned && !alive);
+            if (lane == 0 && gone != 0) atomicOr(&sh.dead[wave >> split_log2], gone);
+            break;
+        }
+        const unsigned long long m = __ballot(alive);
+        unsigned at = 0;
+        if (lane == 0) at = atomicAdd(&sh.listed, (unsigned)__builtin_popcountll(m));
+        at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+        if (alive)
+            sh.list[at + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (uint16_t)row;
+        else if (owned && parts > 1)
+            keep_f[meta & 0xffffu] = 0;
+    }
+    lds_barrier();
+    if (split_log2 > 0) {  // uniform; at most eight tiles of victims
+        // what each tile's wavefronts found together; a wavefront's place in the list follows from all of it
+        const int t_lane = lane & (kPlaceWaves - 1);
+        const int in_tile = n_f - (part + t_lane * parts) * kTile;
+        const unsigned long long there = in_tile >= kTile ? ~0ull : (in_tile > 0 ? (1ull << in_tile) - 1ull : 0ull);
+        const unsigned sums = row16_inclusive_sum((unsigned)__builtin_popcountll(there & ~sh.dead[t_lane]));
+        const int total = __builtin_amdgcn_readlane((int)sums, kPlaceWaves - 1);
+        const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane((int)sums, wave - 1);
+        bool owned;
+        const int row = victim_row(part + wave * parts, owned);
+        if (owned) {
+            const unsigned long long m = ~sh.dead[wave];
+            if ((m >> lane) & 1ull)  // (what is not there lies behind the last lane that is)
+                sh.list[before + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (uint16_t)row;
+            else if (parts > 1)
+                keep_f[sh.meta[row] & 0xffffu] = 0;
+        }
+        if (tid == 0) sh.listed = (unsigned)total;
+        lds_barrier();
+    }
+
+    // ---- second stage: the victims still alive, a group of neighbours at a time, lane = outranking box, the tiles that reach a victim
+    const int listed = (int)sh.listed;
+    const float4 th_hull = sh.hull[lane < tiles ? lane : 0];
+    const uint2 th_tile = sh.tile[lane < tiles ? lane : 0];
+    const float tile_T = lane < tiles ? __uint_as_float(th_tile.x) : INFINITY;
+    constexpr int G = kPlaceGroup;
+    const int group = listed >= W * G ? G : (listed + W - 1) / W;  // (no wavefront idle while another has several)
+#pragma unroll 1
+    for (int i0 = wave * group; i0 < listed;) {  // the first group is the wavefront's own, the others are handed out through a counter
+        int next = 0;
+        if (lane == 0) next = W * group + (int)atomicAdd(&sh.next, (unsigned)group);
+        const int members = listed - i0 < group ? listed - i0 : group;
+        float4 v[G];
+        unsigned v_upper[G], v_index[G];
+        unsigned long long reach[G];  // tiles that reach victim u; none once it has an eliminator
+        unsigned long long left = 0;
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            const int row = sh.list[u < members ? i0 + u : i0];
+            v[u] = sh.box[row];
+            v_upper[u] = sh.upper[row];
+            v_index[u] = sh.meta[row] & 0xffffu;
+        }
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            reach[u] = 0;
+            if (u < members)
+                reach[u] = __ballot(nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, th_hull.x, th_hull.y, th_hull.z, th_hull.w, tile_T) &&
+                                    th_tile.y <= v_upper[u]);
+            left |= reach[u];
+        }
+        unsigned dead = 0;
+        while (left != 0) {
+            const int t0 = __builtin_ctzll(left);
+            left &= left - 1;
+            const int t1 = left != 0 ? __builtin_ctzll(left) : t0;
+            left &= left - 1;  // (0 stays 0)
+            const float4 c0 = sh.box[t0 * kTile + lane], c1 = sh.box[t1 * kTile + lane];
+            const float T0 = sh.T[t0 * kTile + lane], T1 = sh.T[t1 * kTile + lane];
+            const unsigned u0 = sh.upper[t0 * kTile + lane], u1 = sh.upper[t1 * kTile + lane];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                if ((((reach[u] >> t0) | (reach[u] >> t1)) & 1ull) != 0) {  // wave-uniform
+                    const bool h0 = nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, c0.x, c0.y, c0.z, c0.w, T0);
+                    const bool h1 = nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, c1.x, c1.y, c1.z, c1.w, T1);
+                    const unsigned long long near0 = __ballot(h0) & __ballot(u0 <= v_upper[u]), near1 = __ballot(h1) & __ballot(u1 <= v_upper[u]);
+                    if ((near0 | near1) != 0) {
+                        asm volatile("" ::: "memory");  // keeps this a branch
+                        unsigned long long out = (near0 & __ballot(u0 < v_upper[u])) | (near1 & __ballot(u1 < v_upper[u]));
+                        // equal scores: the lower index is ranked first (the victim itself is not)
+                        if (out == 0)
+                            out = (near0 & __ballot((sh.meta[t0 * kTile + lane] & 0xffffu) < v_index[u])) |
+                                  (near1 & __ballot((sh.meta[t1 * kTile + lane] & 0xffffu) < v_index[u]));
+                        if (out != 0) {
+                            dead |= 1u << u;
+                            reach[u] = 0;
+                            left &= reach[0] | reach[1] | reach[2] | reach[3];
+                        }
+                    }
+                }
+            }
+        }
+        if (lane < members) {
+            unsigned e = v_index[0];
+#pragma unroll
+            for (int u = 1; u < G; ++u) e = lane == u ? v_index[u] : e;
+            const bool alive = ((dead >> lane) & 1u) == 0;
+            if (parts > 1) keep_f[e] = alive ? 1 : 0;
+            else if (alive) sh.keep[e] = 1;
+        }
+        i0 = __builtin_amdgcn_readfirstlane(next);
+    }
+    if (parts == 1) {
+        lds_barrier();
+#pragma unroll
+        for (int q = 0; q < E; ++q) {
+            const int e = q * kThreads + tid;
+            if (e < n_f) keep_f[e] = sh.keep[e];
+        }
+    }
+}

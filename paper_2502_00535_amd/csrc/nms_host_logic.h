@@ -245,6 +245,39 @@ NMS_HD bool nms_use_small_frames(int n_max, int frames)
     return tiles >= 11;
 }
 
+// ---- boxes in order of place (spatial_frames_kernel) -----------------------------------------------
+// Frames of up to 4096 boxes, for thresholds with a division-free form, whatever nms_route_for names for the
+// rest.  Its tables cost some 7 us whatever the batch; the line is where it passes the direct form and the
+// sort-free kernels on clustered detections (much eliminated) and on sparse anchors (little eliminated).  Whole
+// call, us, place / before: 16 x 1024 7.5 / 7.0 and 8.8 / 9.3, 32 x 1024 7.7 / 8.3 and 11.5 / 13.8, 64 x 600 8.0 / 9.9 and
+// 11.7 / 16.5, 16 x 600 6.8 / 5.9; 4 x 1300 8.5 / 7.0, 8 x 1300 7.8 / 9.6 and 9.1 / 9.6, 4 x 2048 8.4 / 9.6, 8 x 2048 8.5 / 9.1;
+// 1 x 4096 10.2 / 8.9, 2 x 4096 11.0 / 14.5, 2 x 3000 10.5 / 12.5.  Shorter frames gain on clustered detections only
+// (1000 x 300 14 / 34, but anchors 35 / 34) until there are many of some 500 boxes (512 x 512 13 / 19 and 35 / 41).
+NMS_HD bool nms_use_spatial_frames(int n_max, int frames, int sort_chunk)
+{
+    const long long total = (long long)frames * n_max;
+    if (n_max > sort_chunk) return false;
+    if (n_max > 2048) return frames >= 2;
+    if (n_max > 1024) return total >= 8000;
+    if (n_max > 512) return total >= 28000;
+    return n_max > 448 && frames >= 512;
+}
+
+// Workgroups that share a frame: one per compute unit, each with a tile of victims.
+NMS_HD int nms_spatial_frames_parts(int n_max, int frames)
+{
+    const int tiles = (n_max + 63) / 64;
+    const int fit = 256 / (frames < 256 ? frames : 256);
+    return fit < tiles ? fit : tiles;
+}
+
+// log2 of the wavefronts (of W) that share 64 victims in its first stage.
+NMS_HD int nms_spatial_frames_split(int n_max, int parts, int W)
+{
+    const int tiles = ((n_max + 63) / 64 + parts - 1) / parts;
+    return tiles * 4 <= W ? 2 : (tiles * 2 <= W ? 1 : 0);
+}
+
 // The route of the automatic whole-path call for a batch shape (1 <= n_max, 1 <= frames).
 NMS_HD int nms_route_for(int n_max, int frames, int sort_chunk)
 {

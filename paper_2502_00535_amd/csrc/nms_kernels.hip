@@ -59,6 +59,7 @@ __device__ __forceinline__ int frame_count(const int32_t *counts, int f, int n_m
 #include "kernels/staged.h"
 #include "kernels/small_frames.h"
 #include "kernels/matrix_form.h"
+#include "kernels/spatial_frames.h"
 
 // ----------------------------------------------------------------------------- host side
 
@@ -404,16 +405,10 @@ static int small_frames_launch(const float *boxes, const float *scores, const in
             small_frames_kernel<true><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
         else
             small_frames_kernel<false><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
-    } else if (n_max <= 2 * kSmallThreads) {
-        if (th.fast)
-            mid_frames_kernel<true, 2><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
-        else
-            mid_frames_kernel<false, 2><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
+    } else if (n_max <= 2 * kSmallThreads) {  // (with a division-free threshold these are frames of nms_use_spatial_frames)
+        mid_frames_kernel<2><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
     } else {
-        if (th.fast)
-            mid_frames_kernel<true, 4><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
-        else
-            mid_frames_kernel<false, 4><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
+        mid_frames_kernel<4><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, parts, th, keep_out);
     }
     return launch_status();
 }
@@ -445,6 +440,24 @@ static int staged_launch(const RunWorkspace &w, const int32_t *counts, int n_max
     return launch_status();
 }
 
+// Boxes in order of place, one launch (kernels/spatial_frames.h); th.fast.
+static int spatial_frames_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                                 const NmsThetaConst &th, uint8_t *keep_out, hipStream_t stream)
+{
+    const int parts = nms_spatial_frames_parts(n_max, frames);
+    const dim3 grid((unsigned)frames, (unsigned)parts);
+    begin_launch();
+#define NMS_LAUNCH_PLACE(W_, E_, AXIS_) \
+    spatial_frames_kernel<W_, E_, AXIS_><<<grid, dim3(W_ * 64), 0, stream>>>(boxes, scores, counts, n_max,                 \
+                                                                             nms_spatial_frames_split(n_max, parts, W_), th, keep_out)
+    if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+    else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
+    else if (n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
+    else NMS_LAUNCH_PLACE(16, 4, 32);
+#undef NMS_LAUNCH_PLACE
+    return launch_status();
+}
+
 // forward: defined with the early-exit entry point below
 static int early_exit_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
                              float threshold, uint8_t *keep_out, void *workspace, hipStream_t s);
@@ -471,6 +484,10 @@ static int run_routed(Route route, const float *boxes, const float *scores, cons
     }
 
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (route == kRouteAuto && nms_use_spatial_frames(n_max, frames, kChunk)) {
+        const NmsThetaConst th = nms_make_theta_const(threshold);
+        if (th.fast) return spatial_frames_launch(boxes, scores, counts, n_max, frames, th, keep_out, s);
+    }
     if (small)
         return small_frames_launch(boxes, scores, counts, n_max, frames, nms_make_theta_const(threshold), keep_out, s);
     if (route == kRouteAuto && !direct && nms_use_early_exit(n_max, frames, kChunk))
