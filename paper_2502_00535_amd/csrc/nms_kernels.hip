@@ -625,7 +625,7 @@ static int early_exit_launch(const float *boxes, const float *scores, const int3
     // (each stages the whole frame), which then need the ranked table in memory.
     int parts = 1;
     while (parts < (n_max > kChunk ? 256 : 16) && frames * parts * 2 <= 256) parts *= 2;
-    if (parts == 1 && n_max > kChunk / 2) {
+    if (parts == 1 && n_max > kChunk / 2 && n_max <= kChunk) {
         // the rank step would run with the same 1024 threads per frame: it is part of the kernel
         begin_launch();
         if (th.fast)
