@@ -143,8 +143,9 @@ int nms_reduce_batched(const uint64_t *mask, const int32_t *order, const int32_t
  * The call picks its route by size (nms_route() names it); every route returns the same bits.
  * Batches of frames of 449 to 4096 boxes whose threshold lies in [2^-40, 2^20] (two frames beyond
  * 2048 boxes, some 8000 boxes in frames beyond 1024, some 28,000 in shorter ones) are put in order
- * of place instead of rank and pairs of boxes that lie apart are left out, in one launch; the route
- * that nms_route() names is theirs for other thresholds.
+ * of place instead of rank and pairs of boxes that lie apart are left out, in one launch, and so
+ * are frames of more than 4096 boxes, in two; the route that nms_route() names is theirs for
+ * other thresholds.
  *   NMS_ROUTE_DIRECT      small work (up to about 2^25 pair slots = frames * n_max^2): one launch.
  *   NMS_ROUTE_SMALL_FRAMES  batches of ten or more frames of 513 to 1024 boxes (of 128 or more
  *                         frames from 449 boxes on), and 2 to about 40

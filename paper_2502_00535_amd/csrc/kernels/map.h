@@ -229,66 +229,6 @@ __device__ __forceinline__ unsigned long long fused_candidates(const float4 *__r
     return acc;
 }
 
-// The same with the next group's scalar loads in flight while a group is worked on, for launches
-// that leave a SIMD with one or two wavefronts and nobody else to cover a load's latency (the
-// two-launch route's second launch).  Groups of four (two buffers of 20 scalar registers).  Scalar
-// loads may complete out of order, so a wait for one buffer waits for all loads issued before it:
-// the next group is requested only after the current one has arrived.
-template <int PAIR, int MASK>
-__device__ __forceinline__ unsigned long long fused_candidates_ahead(const float4 *__restrict__ cb,
-                                                                     const float *__restrict__ caux, const float4 vb,
-                                                                     float y_one, float theta, int r_lane, int c_base)
-{
-    constexpr int kGroup = 4;
-    constexpr int kGroups = kTile / kGroup;
-    unsigned long long acc = 0;
-    float4 c[2][kGroup];
-    float a[2][kGroup];
-    auto fetch = [&](int buf, int grp) __attribute__((always_inline)) {
-        const nms_uniform_float_ptr cg = (nms_uniform_float_ptr)(uintptr_t)(cb + kGroup * grp);
-        const nms_uniform_float_ptr ag = (nms_uniform_float_ptr)(uintptr_t)(caux + kGroup * grp);
-#pragma unroll
-        for (int k = 0; k < kGroup; ++k) {
-            c[buf][k] = make_float4(cg[4 * k], cg[4 * k + 1], cg[4 * k + 2], cg[4 * k + 3]);
-            a[buf][k] = ag[k];
-        }
-    };
-    auto work = [&](int buf, int grp) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < kGroup; ++k) {
-            const float4 cc = c[buf][k];
-            const float aa = a[buf][k];
-            bool hit;
-            if (PAIR == kPairFastYScaled)
-                hit = nms_eliminates_fast_yscaled(vb.x, vb.y, vb.z, vb.w, cc.x, cc.y, cc.z, cc.w, aa, y_one);
-            else if (PAIR == kPairFast)
-                hit = nms_eliminates_fast(vb.x, vb.y, vb.z, vb.w, cc.x, cc.y, cc.z, cc.w, aa * (1.0f / NMS_YSCALE));
-            else
-                hit = nms_eliminates_exact(vb.x, vb.y, vb.z, vb.w, cc.x, cc.y, cc.z, cc.w, aa, theta);
-            unsigned long long word = __ballot(hit);
-            const int ci = kGroup * grp + k;
-            if (MASK == kMaskDiagonal) word &= ci == kTile - 1 ? 0ull : (~0ull << (ci + 1));
-            if (MASK == kMaskByRank) word &= __ballot(r_lane > c_base + ci);
-            acc |= word;
-        }
-    };
-    fetch(0, 0);
-#pragma unroll 1
-    for (int grp = 0; grp < kGroups; grp += 2) {
-        asm volatile("" ::"s"(a[0][kGroup - 1]));  // buffer 0 has arrived ...
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(1, grp + 1);                           // ... request the next group, then work
-        __builtin_amdgcn_sched_barrier(0);
-        work(0, grp);
-        asm volatile("" ::"s"(a[1][kGroup - 1]));
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(0, grp + 2 < kGroups ? grp + 2 : 0);  // (the last request is not used)
-        __builtin_amdgcn_sched_barrier(0);
-        work(1, grp + 1);
-    }
-    return acc;
-}
-
 // One wavefront = one unit: a victim tile row tr against up to kSuper tiles of outranking boxes
 // tc <= tr.  Units are numbered as in nms_triangle_unit with both tile indices counted from the
 // far end (u = T-1-tr, v = T-1-tc, v >= u, the v of a unit share v / kSuper).  keep_out was preset

@@ -22,6 +22,9 @@
 //
 // Same keep vector as the all-pairs kernel, bit for bit: a victim is dropped only once an
 // eliminator has been found, and every other pair is tested by the same instructions.
+//
+// For thresholds that take the literal division; with a division-free form the frames are put in order of place
+// (spatial_table.h).
 constexpr int kStageTiles = 32;   // outranking tiles of the first launch: the best 2048 ranks (1024: its 7 us against 11, but 26 us for the second launch against 13)
 constexpr int kStageSplit = 1;    // work units per outranking tile in the second launch (2: 15 us instead of 13; a unit's set-up costs more than its tile)
 constexpr int kStageWaves = 16;   // wavefronts per workgroup of the second launch
@@ -78,11 +81,9 @@ __device__ __forceinline__ void wave_exclusive_scan(int *table, int count, int l
 
 // First launch.  Unit g = (victim tile tr, outranking tile tc) with tc < kStageTiles, tc <= tr;
 // the four wavefronts of a workgroup share a victim tile.
-template <bool FAST>
 __global__ void __launch_bounds__(kMapWaves * 64)
 staged_first_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ counts, int n_max, int n_pad,
                     NmsThetaConst th, const int32_t *__restrict__ order, uint8_t *__restrict__ keep_out,
-                    const float4 *__restrict__ ysc, const unsigned *__restrict__ ytile, const float *__restrict__ tsc,
                     unsigned long long *__restrict__ dead_part)
 {
     const int lane = threadIdx.x & 63;
@@ -98,28 +99,13 @@ staged_first_kernel(const float *__restrict__ sorted5, const int32_t *__restrict
     const float *sorted_f = sorted5 + (size_t)f * 5 * n_pad;
     const float4 *__restrict__ box4 = reinterpret_cast<const float4 *>(sorted_f);
     const float *__restrict__ area = sorted_f + 4 * (size_t)n_pad;
-    const float4 *__restrict__ ysc4 = ysc + (size_t)f * n_pad;
-    const unsigned *__restrict__ ytile_f = ytile + (size_t)f * (n_pad / kTile);
-    const float *__restrict__ tsc_f = tsc + (size_t)f * n_pad;
-    float y_one;  // NMS_YSCALE in a vector register (opaque to the compiler so it stays there)
-    asm volatile("v_mov_b32 %0, 0x38800000" : "=v"(y_one));
-
     const int row = tr * kTile + lane;
     unsigned long long acc;
-    if (FAST && ytile_f[tr] != 0 && ytile_f[tc] != 0) {
-        const float4 vbs = ysc4[row];
-        if (tc == tr)
-            acc = fused_candidates<kPairFastYScaled, kMaskDiagonal>(ysc4 + tc * kTile, tsc_f + tc * kTile, vbs, y_one, th.theta, 0, 0);
-        else
-            acc = fused_candidates<kPairFastYScaled, kMaskNone>(ysc4 + tc * kTile, tsc_f + tc * kTile, vbs, y_one, th.theta, 0, 0);
-    } else {
-        const float4 vb = box4[row];
-        const float *caux = FAST ? tsc_f + tc * kTile : area + tc * kTile;
-        if (tc == tr)
-            acc = fused_candidates<FAST ? kPairFast : kPairExact, kMaskDiagonal>(box4 + tc * kTile, caux, vb, y_one, th.theta, 0, 0);
-        else
-            acc = fused_candidates<FAST ? kPairFast : kPairExact, kMaskNone>(box4 + tc * kTile, caux, vb, y_one, th.theta, 0, 0);
-    }
+    const float4 vb = box4[row];
+    if (tc == tr)
+        acc = fused_candidates<kPairExact, kMaskDiagonal>(box4 + tc * kTile, area + tc * kTile, vb, 0.0f, th.theta, 0, 0);
+    else
+        acc = fused_candidates<kPairExact, kMaskNone>(box4 + tc * kTile, area + tc * kTile, vb, 0.0f, th.theta, 0, 0);
     if (lane == 0) dead_part[((size_t)f * T + tr) * kStageTiles + tc] = acc;
     if (((acc >> lane) & 1ull) && row < n_f) keep_out[(size_t)f * n_max + order[(size_t)f * n_max + row]] = 0;
 }
@@ -131,11 +117,9 @@ struct StagedShared {
 };
 
 // Second launch: gridDim.x persistent workgroups per frame.
-template <bool FAST>
 __global__ void __launch_bounds__(kStageWaves * 64)
 staged_second_kernel(const float *__restrict__ sorted5, const int32_t *__restrict__ counts, int n_max, int n_pad,
                      NmsThetaConst th, const int32_t *__restrict__ order, uint8_t *__restrict__ keep_out,
-                     const float4 *__restrict__ ysc, const unsigned *__restrict__ ytile, const float *__restrict__ tsc,
                      const unsigned long long *__restrict__ dead_part)
 {
     __shared__ StagedShared sh;
@@ -202,11 +186,6 @@ staged_second_kernel(const float *__restrict__ sorted5, const int32_t *__restric
     const float *sorted_f = sorted5 + (size_t)f * 5 * n_pad;
     const float4 *__restrict__ box4 = reinterpret_cast<const float4 *>(sorted_f);
     const float *__restrict__ area = sorted_f + 4 * (size_t)n_pad;
-    const float4 *__restrict__ ysc4 = ysc + (size_t)f * n_pad;
-    const unsigned *__restrict__ ytile_f = ytile + (size_t)f * (n_pad / kTile);
-    const float *__restrict__ tsc_f = tsc + (size_t)f * n_pad;
-    float y_one;
-    asm volatile("v_mov_b32 %0, 0x38800000" : "=v"(y_one));
 
     const int stride = (int)gridDim.x * kStageWaves;
     for (int u = (int)blockIdx.x * kStageWaves + wave; u < U; u += stride) {  // u is wave-uniform
@@ -221,27 +200,12 @@ staged_second_kernel(const float *__restrict__ sorted5, const int32_t *__restric
         const int top = __builtin_amdgcn_readlane(r, last_lane) / kTile;
         const int tc = kStageTiles + piece / kStageSplit;  // <= top: run s has (top - kStageTiles + 1) * kStageSplit units
 
-        const float4 vbs = ysc4[r];
         const float4 vb = box4[r];
-        const bool v_regular = FAST && __ballot(active && !(nms_y_regular(vb.y) && nms_y_regular(vb.w))) == 0ull;
         unsigned long long acc;
-        const bool masked = tc >= lo_tile;  // the tile reaches into the ranks of this run's own victims
-        if (v_regular && ytile_f[tc] != 0) {
-            if (masked)
-                acc = fused_candidates_ahead<kPairFastYScaled, kMaskByRank>(ysc4 + tc * kTile, tsc_f + tc * kTile, vbs, y_one,
-                                                                            th.theta, mine, tc * kTile);
-            else
-                acc = fused_candidates_ahead<kPairFastYScaled, kMaskNone>(ysc4 + tc * kTile, tsc_f + tc * kTile, vbs, y_one,
-                                                                          th.theta, mine, tc * kTile);
-        } else {
-            const float *caux = FAST ? tsc_f + tc * kTile : area + tc * kTile;
-            if (masked)
-                acc = fused_candidates<FAST ? kPairFast : kPairExact, kMaskByRank>(box4 + tc * kTile, caux, vb, y_one, th.theta,
-                                                                                   mine, tc * kTile);
-            else
-                acc = fused_candidates<FAST ? kPairFast : kPairExact, kMaskNone>(box4 + tc * kTile, caux, vb, y_one, th.theta,
-                                                                                 mine, tc * kTile);
-        }
+        if (tc >= lo_tile)  // the tile reaches into the ranks of this run's own victims
+            acc = fused_candidates<kPairExact, kMaskByRank>(box4 + tc * kTile, area + tc * kTile, vb, 0.0f, th.theta, mine, tc * kTile);
+        else
+            acc = fused_candidates<kPairExact, kMaskNone>(box4 + tc * kTile, area + tc * kTile, vb, 0.0f, th.theta, mine, tc * kTile);
         if (active && ((acc >> lane) & 1ull)) keep_out[(size_t)f * n_max + order[(size_t)f * n_max + r]] = 0;
     }
 }

@@ -278,6 +278,14 @@ NMS_HD int nms_spatial_frames_split(int n_max, int parts, int W)
     return tiles * 4 <= W ? 2 : (tiles * 2 <= W ? 1 : 0);
 }
 
+// Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.
+NMS_HD int nms_place_share(int n_max, int frames)
+{
+    const int parts = 256 / (frames < 256 ? frames : 256);
+    const int share = ((n_max + parts - 1) / parts + 63) / 64 * 64;
+    return share < 1024 ? share : 1024;
+}
+
 // The route of the automatic whole-path call for a batch shape (1 <= n_max, 1 <= frames).
 NMS_HD int nms_route_for(int n_max, int frames, int sort_chunk)
 {

@@ -60,6 +60,7 @@ __device__ __forceinline__ int frame_count(const int32_t *counts, int f, int n_m
 #include "kernels/small_frames.h"
 #include "kernels/matrix_form.h"
 #include "kernels/spatial_frames.h"
+#include "kernels/spatial_table.h"
 
 // ----------------------------------------------------------------------------- host side
 
@@ -210,6 +211,38 @@ int map_launch(const float *sorted5, const int32_t *counts, int n_max, int frame
         if (super4) NMS_LAUNCH_MAP(false, 4); else if (super2) NMS_LAUNCH_MAP(false, 2); else NMS_LAUNCH_MAP(false, 1);
     }
 #undef NMS_LAUNCH_MAP
+    return launch_status();
+}
+
+template <bool IOU>
+int place_sort_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                             const PlaceTest &test, const PlaceTable &tab, uint8_t *keep_out, hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    const int share = nms_place_share(n_max, frames);
+    const dim3 grid((unsigned)frames, (unsigned)((n_max + share - 1) / share)), block(kSortThreads);
+    begin_launch();
+#define NMS_LAUNCH_SORT(E_, MULTI_)                                                                                     \
+    place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, keep_out)
+    if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
+    else if (n_max <= 16 * kSortThreads) NMS_LAUNCH_SORT(16, false);
+    else NMS_LAUNCH_SORT(16, true);
+#undef NMS_LAUNCH_SORT
+    return launch_status();
+}
+
+template <bool IOU>
+int place_scan_launch(const int32_t *counts, int n_max, int frames, const PlaceTest &test, const PlaceTable &tab, uint8_t *keep_out,
+                      hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    const int tiles = n_pad / kTile;
+    const dim3 grid((unsigned)frames, (unsigned)tiles);
+    begin_launch();
+    if ((long long)frames * tiles <= 512)
+        place_scan_kernel<16, IOU><<<grid, dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, test, tab, keep_out);
+    else
+        place_scan_kernel<4, IOU><<<grid, dim3(4 * 64), 0, stream>>>(counts, n_max, n_pad, test, tab, keep_out);
     return launch_status();
 }
 
@@ -422,21 +455,12 @@ static int staged_launch(const RunWorkspace &w, const int32_t *counts, int n_max
     int parts = 256 / frames;  // persistent workgroups of the second launch: one per compute unit (192 to 384 measure alike, 512: +3 %, 128: +18 %)
     if (parts < 1) parts = 1;
     begin_launch();
-    if (th.fast)
-        staged_first_kernel<true><<<first_grid, dim3(kMapWaves * 64), 0, stream>>>(w.sorted5, counts, n_max, n_pad, th, w.order,
-                                                                                   keep_out, w.ysc, w.ytile, w.tsc, w.stage);
-    else
-        staged_first_kernel<false><<<first_grid, dim3(kMapWaves * 64), 0, stream>>>(w.sorted5, counts, n_max, n_pad, th, w.order,
-                                                                                    keep_out, w.ysc, w.ytile, w.tsc, w.stage);
+    staged_first_kernel<<<first_grid, dim3(kMapWaves * 64), 0, stream>>>(w.sorted5, counts, n_max, n_pad, th, w.order, keep_out, w.stage);
     int st = launch_status();
     if (st != NMS_OK) return st;
     begin_launch();
-    if (th.fast)
-        staged_second_kernel<true><<<dim3(parts, frames), dim3(kStageWaves * 64), 0, stream>>>(
-            w.sorted5, counts, n_max, n_pad, th, w.order, keep_out, w.ysc, w.ytile, w.tsc, w.stage);
-    else
-        staged_second_kernel<false><<<dim3(parts, frames), dim3(kStageWaves * 64), 0, stream>>>(
-            w.sorted5, counts, n_max, n_pad, th, w.order, keep_out, w.ysc, w.ytile, w.tsc, w.stage);
+    staged_second_kernel<<<dim3(parts, frames), dim3(kStageWaves * 64), 0, stream>>>(w.sorted5, counts, n_max, n_pad, th, w.order,
+                                                                                     keep_out, w.stage);
     return launch_status();
 }
 
@@ -456,6 +480,35 @@ static int spatial_frames_launch(const float *boxes, const float *scores, const 
     else NMS_LAUNCH_PLACE(16, 4, 32);
 #undef NMS_LAUNCH_PLACE
     return launch_status();
+}
+
+// The table's parts lie where the ranked routes keep theirs (the layout of nms_run_layout): boxes and T in sorted5's place,
+// rank keys in tsc's, input indices in order's, the tiles' hulls in ysc's.
+static PlaceTable place_table(const RunWorkspace &w, int n_pad, int frames, int32_t *label)
+{
+    PlaceTable t;
+    const size_t tiles = (size_t)frames * (n_pad / kTile);
+    t.box = reinterpret_cast<float4 *>(w.sorted5);
+    t.T = w.sorted5 + (size_t)frames * 4 * n_pad;
+    t.upper = reinterpret_cast<unsigned *>(w.tsc);
+    t.index = reinterpret_cast<unsigned *>(w.order);
+    t.label = label;
+    t.hull = w.ysc;
+    t.tile = reinterpret_cast<uint2 *>(t.hull + tiles);
+    return t;
+}
+
+// The paper's rule on long frames: table, scan.
+static int place_paper_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                              const NmsThetaConst &th, uint8_t *keep_out, void *workspace, hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    const RunWorkspace w = carve_workspace(workspace, n_max, frames);
+    const PlaceTable tab = place_table(w, n_pad, frames, nullptr);
+    const PlaceTest test = {th.m, 1.0f, 0, nullptr};
+    const int st = place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
+    if (st != NMS_OK) return st;
+    return place_scan_launch<false>(counts, n_max, frames, test, tab, keep_out, stream);
 }
 
 // forward: defined with the early-exit entry point below
@@ -487,6 +540,10 @@ static int run_routed(Route route, const float *boxes, const float *scores, cons
     if (route == kRouteAuto && nms_use_spatial_frames(n_max, frames, kChunk)) {
         const NmsThetaConst th = nms_make_theta_const(threshold);
         if (th.fast) return spatial_frames_launch(boxes, scores, counts, n_max, frames, th, keep_out, s);
+    }
+    if (route == kRouteAuto && n_max > kChunk) {
+        const NmsThetaConst th = nms_make_theta_const(threshold);
+        if (th.fast) return place_paper_launch(boxes, scores, counts, n_max, frames, th, keep_out, workspace, s);
     }
     if (small)
         return small_frames_launch(boxes, scores, counts, n_max, frames, nms_make_theta_const(threshold), keep_out, s);
@@ -766,6 +823,18 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     float *ranked_area = reinterpret_cast<float *>(p);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // rounding boundary of the division next to theta, exact in float64: below theta for ">=", above it for ">"
+    double boundary = 0.0;
+    bool divide = true;
+    if (threshold >= 0x1p-40f && threshold <= 0x1p20f) {
+        uint32_t bits;
+        memcpy(&bits, &threshold, sizeof bits);
+        const uint32_t other_bits = opt.compare == NMS_COMPARE_GT ? bits + 1u : bits - 1u;
+        float other;
+        memcpy(&other, &other_bits, sizeof other);
+        boundary = 0.5 * ((double)threshold + (double)other);
+        divide = false;
+    }
     // under the paper's rule the row reduction is folded into the map kernel: keep_out starts at 1
     const bool fold = opt.rule == NMS_RULE_PAPER;
     st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
@@ -787,18 +856,6 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     const int tile_blocks = (tiles + kMapWaves - 1) / kMapWaves;
     const int xcd_frames = frames >= 8 ? 1 : 0;
     const dim3 grid = xcd_frames ? dim3((unsigned)(((frames + 7) / 8) * 8 * tile_blocks)) : dim3(tile_blocks, frames);
-    // rounding boundary of the division next to theta, exact in float64: below theta for ">=", above it for ">"
-    double boundary = 0.0;
-    bool divide = true;
-    if (threshold >= 0x1p-40f && threshold <= 0x1p20f) {
-        uint32_t bits;
-        memcpy(&bits, &threshold, sizeof bits);
-        const uint32_t other_bits = opt.compare == NMS_COMPARE_GT ? bits + 1u : bits - 1u;
-        float other;
-        memcpy(&other, &other_bits, sizeof other);
-        boundary = 0.5 * ((double)threshold + (double)other);
-        divide = false;
-    }
     // a float32 at or below boundary * (1 - 2^-22): the factor of the variants kernel's first, float32 test
     float boundary_lo = 0.0f;
     if (!divide) {
