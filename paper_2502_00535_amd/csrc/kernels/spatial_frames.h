@@ -68,18 +68,23 @@ __device__ __forceinline__ float place_scale(float lo, float hi, float cells)
     const float range = hi - lo;
     return range > 0x1p-100f && range < 0x1p100f ? cells * __builtin_amdgcn_rcpf(range) : 0.0f;
 }
-// Cell number: class (area below 2, 8, 32 cells of a 16 x 16 grid, or more), row, column.  Any coordinates give a legal cell:
-// clamped before the conversion, masked after.
+// Row and column of a box's centre.  Any coordinates give a legal cell: clamped before the conversion, masked after.
 template <int AXIS>
-__device__ __forceinline__ unsigned place_cell(const float4 b, const PlaceGrid &g)
+__device__ __forceinline__ unsigned place_spot(const float4 b, const PlaceGrid &g)
 {
     const float cx = fminf(fmaxf((b.x + b.z - g.x0) * g.sx, 0.0f), (float)(AXIS - 1));
     const float cy = fminf(fmaxf((b.y + b.w - g.y0) * g.sy, 0.0f), (float)(AXIS - 1));
+    unsigned c = (unsigned)(int)cy * AXIS + (unsigned)(int)cx;
+    asm volatile("" : "+v"(c));
+    return c & (unsigned)(AXIS * AXIS - 1);
+}
+// Cell number: size class (area below 2, 8, 32 cells of a 16 x 16 grid, or more), row, column.
+template <int AXIS>
+__device__ __forceinline__ unsigned place_cell(const float4 b, const PlaceGrid &g)
+{
     const float t = ((b.z - b.x) * g.sx) * ((b.w - b.y) * g.sy) * (256.0f / (AXIS * AXIS));  // (g is for doubled coordinates: t = area in cells / 4)
     const unsigned cls = t < 0.5f ? 0u : (t < 2.0f ? 1u : (t < 8.0f ? 2u : 3u));
-    unsigned c = (cls * AXIS + (unsigned)(int)cy) * AXIS + (unsigned)(int)cx;
-    asm volatile("" : "+v"(c));
-    return c & (unsigned)(4 * AXIS * AXIS - 1);
+    return cls * (unsigned)(AXIS * AXIS) + place_spot<AXIS>(b, g);
 }
 // The cells of a class in the order of a Hilbert curve: neighbours on the curve are neighbours in the picture.
 template <int AXIS>
@@ -120,6 +125,27 @@ __device__ __forceinline__ unsigned curve_cell(unsigned i)
 }
 
 constexpr int kPlaceGroup = 4;  // victims of a wavefront in the second stage
+constexpr int kPlaceBins = 16;  // of labels
+
+// The variant of the pair test and of the rule.
+struct PlaceTest {
+    double boundary;         // rounding boundary next to the threshold (map_tile_ex_kernel)
+    float offset;            // pixel offset (IoU; the outranking-area forms are for 1)
+    int ties_ignore;
+    const int32_t *classes;  // null: no labels
+};
+
+// The float32 below which an intersection with a box eliminates nothing: the value that decides (outranking area), or, under
+// IoU, a bound that no union undercuts (c_T1 of map_tile_ex_kernel).
+template <bool IOU>
+__device__ __forceinline__ float place_threshold(float area, double boundary)
+{
+    if (!IOU) return nms_pair_threshold(area, boundary);
+    const double t = boundary * (double)area * (1.0 - 0x1p-21);
+    float t1 = (float)t;
+    if ((double)t1 > t) t1 = __uint_as_float(__float_as_uint(t1) - 1u);  // next float32 down (t > 0)
+    return t1 > 0.0f ? t1 : 0.0f;
+}
 
 // The tables of a frame.  P rows, AXIS cells per axis and size class.
 template <int P, int AXIS>
@@ -128,33 +154,45 @@ struct PlaceShared {
     float4 box[P];
     float T[P];
     unsigned upper[P];                // upper half of the rank key
-    unsigned meta[P];                 // input index, cell << 16
+    unsigned meta[P];                 // input index, cell << 16, bits 4 to 7 of the label << 28
     union {
         uint8_t keep[P];              // parts == 1: by input index
         uint16_t row[P];              // parts > 1: row of an input element
     };
     float4 hull[kTile];               // per tile
     uint2 tile[kTile];                // smallest T, best (smallest) upper half of the tile
+    unsigned bins[kTile];             // labels: the bins that the tile holds
     union {
-        __align__(16) unsigned start[kCells];              // boxes per cell, then their first rows
-        uint16_t list[(P > 2 * kCells ? P : 2 * kCells)];  // after that: rows still alive after the first stage
+        __align__(16) unsigned start[kCells];  // boxes per cell, then their first rows
+        uint16_t list[P > 2 * kCells ? P : 2 * kCells];  // after that: rows still alive after the first stage
     };
-    unsigned best[kCells + 2 * AXIS + 2];  // from AXIS + 1 on: a well-ranked box of the cell: 20 bits of the rank key, 12 bits of the row; ~0: no box
+    unsigned best[kCells + 2 * AXIS + 2];  // from a line and one on: a well-ranked box of the cell: 20 bits of the rank key, 12 bits of the row; ~0: no box
     unsigned wave_sum[kPlaceWaves];
     unsigned long long dead[kPlaceWaves];  // first stage, few victims: per 64 of them
-    unsigned listed, next;
+    unsigned listed, next, wide;
 };
 
-// W: wavefronts; E: boxes per thread (frames of at most 64 W E).  Grid: frames * parts workgroups; a workgroup builds the tables of the whole
-// frame and takes the victims of every parts-th 64 rows.
-template <int W, int E, int AXIS>
+// W: wavefronts; E: boxes per thread (frames of at most 64 W E).  Grid: frames x parts workgroups; a workgroup builds the tables
+// of the whole frame and takes the victims of every parts-th 64 boxes.  split_log2: wavefronts per
+// 64 victims in stage 1; when above 0 the workgroup has at most W / 2 such tiles.  (Integer divisions by the number of
+// workgroups or tiles cost a chain this short 1.0 us: what they would say is in the grid and in split_log2.)
+//
+// IOU: intersection over union; the first test can only err towards "maybe", and what passes is decided in float64 behind a
+// branch, as in map_tile_ex_kernel.  A box without area (T = 0) may eliminate what it does not touch: its tile reaches everything.
+// LABELS: sixteen bins of labels take the place of the size classes, each with a grid of half the lines: tiles hold a label or
+// two, and a victim meets the tiles of its bin only.  The bin and the four bits kept in meta tell labels from 0 to 255
+// apart; a frame with others (wide) looks them up where boxes hit.
+template <int W, int E, int AXIS, bool IOU, bool LABELS>
 __global__ void __launch_bounds__(W * 64)
 spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,
-                      int n_max, int split_log2, NmsThetaConst th, uint8_t *__restrict__ keep_out)
+                      int n_max, int split_log2, PlaceTest test, uint8_t *__restrict__ keep_out)
 {
     constexpr int kThreads = W * 64;
     constexpr int P = E * kThreads;
     constexpr int kPer = 4 * AXIS * AXIS / kThreads;  // cells per thread in the prefix sum
+    constexpr int A = LABELS ? AXIS / 2 : AXIS;       // cells per axis
+    constexpr int kLines = LABELS ? 3 : 6;            // of cells tried in stage 1
+    constexpr unsigned kSame = (unsigned)(kPlaceBins - 1) * (unsigned)(A * A) << 16 | 0xf0000000u;  // of meta: the label
     static_assert(kPer >= 1 && kPer * kThreads == 4 * AXIS * AXIS && E <= 4 && P <= 4096, "cells per thread, sixteen lanes per tile, rows in 12 bits");
     __shared__ PlaceShared<P, AXIS> sh;
     const int f = blockIdx.x;
@@ -165,7 +203,9 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
     const int n_f = frame_count(counts, f, n_max);
     const float4 *box_f = reinterpret_cast<const float4 *>(boxes) + (size_t)f * n_max;
     const float *score_f = scores + (size_t)f * n_max;
+    const int32_t *label_f = LABELS ? test.classes + (size_t)f * n_max : nullptr;
     uint8_t *keep_f = keep_out + (size_t)f * n_max;
+    const float off = IOU ? test.offset : 1.0f;
     if (part == 0)
         for (int i = n_f + tid; i < n_max; i += kThreads) keep_f[i] = 0;
     if (n_f == 0) return;
@@ -173,11 +213,13 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
     const float4 sample = box_f[(unsigned)(lane * n_f) / 64u];
     float4 b[E];
     unsigned upper[E];
+    int label[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) {
         const int e = q * kThreads + tid;
         b[q] = box_f[e < n_f ? e : 0];
         upper[q] = (unsigned)(nms_rank_key(score_f[e < n_f ? e : 0], 0u) >> 32);
+        label[q] = LABELS ? label_f[e < n_f ? e : 0] : 0;
     }
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
@@ -190,13 +232,15 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
         for (int q = 0; q < E; ++q) sh.keep[q * kThreads + tid] = 0;
     }
     if (tid < kPlaceWaves) sh.dead[tid] = 0ull;
+    if (LABELS && tid < kTile) sh.bins[tid] = 0u;
     if (tid == 0) {
         sh.listed = 0u;
         sh.next = 0u;
+        sh.wide = 0u;
     }
     unsigned mine[kPer];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) mine[i] = curve_cell<AXIS>((unsigned)(kPer * tid + i));
+    for (int i = 0; i < kPer; ++i) mine[i] = curve_cell<A>((unsigned)(kPer * tid + i));
     lds_barrier();
 
     // ---- the grid, over the centres of 64 boxes spread over the input (what lies outside goes to the border cells)
@@ -205,17 +249,20 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
         const float cx = sample.x + sample.z, cy = sample.y + sample.w;
         grid.x0 = wave_min(cx), grid.y0 = wave_min(cy);
         const float hx = wave_min(-cx), hy = wave_min(-cy);
-        grid.sx = place_scale(grid.x0, -hx, (float)AXIS);
-        grid.sy = place_scale(grid.y0, -hy, (float)AXIS);
+        grid.sx = place_scale(grid.x0, -hx, (float)A);
+        grid.sy = place_scale(grid.y0, -hy, (float)A);
     }
 
     // ---- boxes per cell, the first row of every cell along the curve, the table
     unsigned cell[E], within[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) {
-        cell[q] = place_cell<AXIS>(b[q], grid);
+        cell[q] = LABELS ? (unsigned)(label[q] & (kPlaceBins - 1)) * (unsigned)(A * A) + place_spot<A>(b[q], grid) : place_cell<A>(b[q], grid);
         within[q] = 0;
-        if (q * kThreads + tid < n_f) within[q] = atomicAdd(&sh.start[cell[q]], 1u);
+        if (q * kThreads + tid < n_f) {
+            within[q] = atomicAdd(&sh.start[cell[q]], 1u);
+            if (LABELS && (unsigned)label[q] > 255u) sh.wide = 1u;
+        }
     }
     lds_barrier();
     {
@@ -243,11 +290,11 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
         if (e < n_f) {
             const unsigned row = sh.start[cell[q]] + within[q];
             sh.box[row] = b[q];
-            const float T = nms_pair_threshold(nms_box_area(b[q].x, b[q].y, b[q].z, b[q].w), th.m);
-            sh.T[row] = T;
+            sh.T[row] = place_threshold<IOU>(((b[q].z - b[q].x) + off) * ((b[q].w - b[q].y) + off), test.boundary);
             sh.upper[row] = upper[q];
-            sh.meta[row] = (unsigned)e | (cell[q] << 16);
-            atomicMin(&sh.best[AXIS + 1 + cell[q]], (upper[q] & ~4095u) | row);
+            sh.meta[row] = (unsigned)e | (cell[q] << 16) | (LABELS ? (unsigned)(label[q] & 0xf0) << 24 : 0u);
+            atomicMin(&sh.best[A + 1 + cell[q]], (upper[q] & ~4095u) | row);
+            if (LABELS) atomicOr(&sh.bins[row / kTile], 1u << (label[q] & (kPlaceBins - 1)));
             if (parts > 1) sh.row[e] = (uint16_t)row;
         }
     }
@@ -259,6 +306,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
         sh.meta[n_f + tid] = 0u;
     }
     lds_barrier();
+    const bool wide = LABELS && sh.wide != 0u;
 
     // ---- per tile: hull, smallest T, best rank; sixteen lanes share a tile
     {
@@ -271,13 +319,16 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             for (int i = 0; i < 4; ++i) {
                 const int row = t * kTile + i * 16 + (lane & 15);
                 const float4 v = sh.box[row];
-                const float T = sh.T[row];
+                float T = sh.T[row];
                 const unsigned u = sh.upper[row];
                 const bool there = row < n_f;
-                h.x = fminf(h.x, there ? v.x : INFINITY);
-                h.y = fminf(h.y, there ? v.y : INFINITY);
-                h.z = fminf(h.z, there ? -v.z : INFINITY);
-                h.w = fminf(h.w, there ? -v.w : INFINITY);
+                const bool odd = IOU && !(T > 0.0f);
+                const float far = odd ? -INFINITY : INFINITY;
+                if (odd) T = -INFINITY;
+                h.x = fminf(h.x, there && !odd ? v.x : far);
+                h.y = fminf(h.y, there && !odd ? v.y : far);
+                h.z = fminf(h.z, there && !odd ? -v.z : far);
+                h.w = fminf(h.w, there && !odd ? -v.w : far);
                 least = fminf(least, T);
                 best = u < best ? u : best;
             }
@@ -290,8 +341,79 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             }
         }
     }
-    // ---- first stage: lane = victim, against a well-ranked box of each of the cells around, in its own size class and the next
-    // smaller: six lines of three cells, shared out among several wavefronts while there are fewer tiles of victims than those
+    auto inter_with = [&](const float4 v, const float4 c) __attribute__((always_inline)) {
+        const float iw = (fminf(v.z, c.z) - fmaxf(v.x, c.x)) + off;  // one floor is enough where T > 0: see nms_pair.h
+        const float ih = fmaxf(0.0f, (fminf(v.w, c.w) - fmaxf(v.y, c.y)) + off);
+        return iw * ih;
+    };
+    auto area_of = [&](const float4 v) __attribute__((always_inline)) { return ((v.z - v.x) + off) * ((v.w - v.y) + off); };
+
+    // A lane's victim against the boxes named in the cells of a line around it: `below` classes smaller, dy lines on (at the border of the
+    // grid the cells of a neighbouring line: any box will do).  Scores equal in the upper 20 bits are left to the scan.
+    struct LaneVictim {
+        float4 box;
+        float T, area;
+        unsigned key, meta;
+        int label;
+    };
+    auto lane_victim = [&](int row) __attribute__((always_inline)) {
+        LaneVictim v;
+        v.box = sh.box[row];
+        v.key = sh.upper[row] & ~4095u;
+        v.meta = sh.meta[row];
+        v.T = IOU ? sh.T[row] : 0.0f;
+        v.area = IOU ? area_of(v.box) : 0.0f;
+        v.label = wide ? label_f[v.meta & 0xffffu] : 0;
+        return v;
+    };
+    auto try_line = [&](const LaneVictim &v, bool &alive, int below, int dy) __attribute__((always_inline)) {
+        const unsigned c = (v.meta >> 16) & 0xfffu;
+        if (!alive || (below && c < (unsigned)(A * A))) return;
+        const unsigned *at_line = sh.best + c + (A + 1 + A * dy - A * A * below);
+        unsigned r[3];
+        float4 cb[3];
+        float cT[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) r[x] = at_line[x - 1];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            cb[x] = sh.box[r[x] & (P - 1)];  // (of an empty cell: whatever is there, it is ranked before nothing)
+            cT[x] = sh.T[r[x] & (P - 1)];
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const float inter = inter_with(v.box, cb[x]);
+            bool hit = inter >= (IOU ? fmaxf(cT[x], v.T) : cT[x]) && r[x] < v.key;
+            if ((IOU || LABELS) && __ballot(hit) != 0) {
+                asm volatile("" ::: "memory");  // keeps this a branch
+                if (IOU) hit = hit && (double)inter >= test.boundary * (double)((v.area + area_of(cb[x])) - inter);
+                if (LABELS) {
+                    const unsigned cm = sh.meta[r[x] & (P - 1)];
+                    hit = hit && ((cm ^ v.meta) & kSame) == 0;
+                    if (wide && hit) hit = label_f[cm & 0xffffu] == v.label;
+                }
+            }
+            alive = alive && !hit;
+        }
+    };
+    auto try_lines = [&](const LaneVictim &v, bool &alive) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int below = 0; below < kLines / 3; ++below) {
+#pragma unroll
+            for (int y = 0; y < 3; ++y) try_line(v, alive, below, y == 2 ? -1 : y);
+            if (__ballot(alive) == 0) break;
+        }
+    };
+    // the lanes' rows go to a list of the workgroup
+    auto append = [&](bool is, int row, uint16_t *list, unsigned *count) __attribute__((always_inline)) {
+        const unsigned long long m = __ballot(is);
+        unsigned at = 0;
+        if (lane == 0) at = atomicAdd(count, (unsigned)__builtin_popcountll(m));
+        at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+        if (is) list[at + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (uint16_t)row;
+    };
+
+    // ---- first stage: lane = victim
     // (one workgroup: 64 rows of the table; several: 64 neighbours of the input -- the order of rows inside a cell is each workgroup's own)
     const int split = 1 << split_log2;
     auto victim_row = [&](int t, bool &there) __attribute__((always_inline)) {
@@ -303,54 +425,22 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
     for (int t = part + parts * (wave >> split_log2); t < tiles; t += parts * W) {
         bool owned;
         const int row = victim_row(t, owned);
-        const float4 v = sh.box[row];
-        const unsigned v_key = sh.upper[row] & ~4095u;
-        const unsigned meta = sh.meta[row], c = meta >> 16;
+        const LaneVictim v = lane_victim(row);
         bool alive = owned;
-        const bool smallest = c < (unsigned)(AXIS * AXIS);
-        // the cells of line dy of the class `below` smaller (at the border of the grid the cells of a neighbouring line: any box will do)
-        auto try_line = [&](int below, int dy) __attribute__((always_inline)) {
-            if (!alive || (below && smallest)) return;
-            const unsigned *at_line = sh.best + c + (AXIS + 1 + AXIS * dy - AXIS * AXIS * below);
-            unsigned r[3];
-            float4 cb[3];
-            float cT[3];
-#pragma unroll
-            for (int x = 0; x < 3; ++x) r[x] = at_line[x - 1];
-#pragma unroll
-            for (int x = 0; x < 3; ++x) {
-                cb[x] = sh.box[r[x] & (P - 1)];  // (of an empty cell: whatever is there, it is ranked before nothing)
-                cT[x] = sh.T[r[x] & (P - 1)];
-            }
-#pragma unroll
-            for (int x = 0; x < 3; ++x)  // (equal in the upper 20 bits of the key: left to the second stage)
-                alive = alive && !(nms_eliminates_fast(v.x, v.y, v.z, v.w, cb[x].x, cb[x].y, cb[x].z, cb[x].w, cT[x]) && r[x] < v_key);
-        };
         if (split_log2 == 0) {
-#pragma unroll 1
-            for (int below = 0; below < 2; ++below) {
-#pragma unroll
-                for (int y = 0; y < 3; ++y) try_line(below, y == 2 ? -1 : y);
-                if (__ballot(alive) == 0) break;
-            }
+            try_lines(v, alive);
         } else {
 #pragma unroll 1
-            for (int l = wave & (split - 1); l < 6; l += split) {
+            for (int l = wave & (split - 1); l < kLines; l += split) {
                 const int y = l >= 3 ? l - 3 : l;
-                try_line(l >= 3 ? 1 : 0, y == 2 ? -1 : y);
+                try_line(v, alive, l >= 3 ? 1 : 0, y == 2 ? -1 : y);
             }
             const unsigned long long gone = __ballot(owned && !alive);
             if (lane == 0 && gone != 0) atomicOr(&sh.dead[wave >> split_log2], gone);
             break;
         }
-        const unsigned long long m = __ballot(alive);
-        unsigned at = 0;
-        if (lane == 0) at = atomicAdd(&sh.listed, (unsigned)__builtin_popcountll(m));
-        at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
-        if (alive)
-            sh.list[at + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (uint16_t)row;
-        else if (owned && parts > 1)
-            keep_f[meta & 0xffffu] = 0;
+        append(alive, row, sh.list, &sh.listed);
+        if (owned && !alive && parts > 1) keep_f[v.meta & 0xffffu] = 0;
     }
     lds_barrier();
     if (split_log2 > 0) {  // uniform; at most eight tiles of victims
@@ -371,80 +461,109 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
                 keep_f[sh.meta[row] & 0xffffu] = 0;
         }
         if (tid == 0) sh.listed = (unsigned)total;
-        lds_barrier();
     }
+    if (split_log2 > 0) lds_barrier();
 
     // ---- second stage: the victims still alive, a group of neighbours at a time, lane = outranking box, the tiles that reach a victim
-    const int listed = (int)sh.listed;
     const float4 th_hull = sh.hull[lane < tiles ? lane : 0];
     const uint2 th_tile = sh.tile[lane < tiles ? lane : 0];
+    const unsigned th_bins = LABELS ? sh.bins[lane < tiles ? lane : 0] : 0u;
     const float tile_T = lane < tiles ? __uint_as_float(th_tile.x) : INFINITY;
     constexpr int G = kPlaceGroup;
-    const int group = listed >= W * G ? G : (listed + W - 1) / W;  // (no wavefront idle while another has several)
+    float4 g_box[G];
+    float g_T[G], g_area[G];
+    unsigned g_upper[G], g_meta[G];
+    int g_label[G];
+    static_assert(G == 4, "a lane per member further down");
+    {
+        const int listed = (int)sh.listed;
+        const int group = listed >= W * G ? G : (listed + W - 1) / W;  // (no wavefront idle while another has several)
 #pragma unroll 1
-    for (int i0 = wave * group; i0 < listed;) {  // the first group is the wavefront's own, the others are handed out through a counter
-        int next = 0;
-        if (lane == 0) next = W * group + (int)atomicAdd(&sh.next, (unsigned)group);
-        const int members = listed - i0 < group ? listed - i0 : group;
-        float4 v[G];
-        unsigned v_upper[G], v_index[G];
-        unsigned long long reach[G];  // tiles that reach victim u; none once it has an eliminator
-        unsigned long long left = 0;
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int row = sh.list[u < members ? i0 + u : i0];
-            v[u] = sh.box[row];
-            v_upper[u] = sh.upper[row];
-            v_index[u] = sh.meta[row] & 0xffffu;
-        }
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            reach[u] = 0;
-            if (u < members)
-                reach[u] = __ballot(nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, th_hull.x, th_hull.y, th_hull.z, th_hull.w, tile_T) &&
-                                    th_tile.y <= v_upper[u]);
-            left |= reach[u];
-        }
-        unsigned dead = 0;
-        while (left != 0) {
-            const int t0 = __builtin_ctzll(left);
-            left &= left - 1;
-            const int t1 = left != 0 ? __builtin_ctzll(left) : t0;
-            left &= left - 1;  // (0 stays 0)
-            const float4 c0 = sh.box[t0 * kTile + lane], c1 = sh.box[t1 * kTile + lane];
-            const float T0 = sh.T[t0 * kTile + lane], T1 = sh.T[t1 * kTile + lane];
-            const unsigned u0 = sh.upper[t0 * kTile + lane], u1 = sh.upper[t1 * kTile + lane];
+        for (int i0 = wave * group; i0 < listed;) {  // the first group is the wavefront's own, the others are handed out through a counter
+            int next = 0;
+            if (lane == 0) next = W * group + (int)atomicAdd(&sh.next, (unsigned)group);
+            const int members = listed - i0 < group ? listed - i0 : group;
+            unsigned dead = 0;
+            unsigned long long reach[G];  // tiles that reach victim u; none once it is settled
+            unsigned long long left = 0;
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                if ((((reach[u] >> t0) | (reach[u] >> t1)) & 1ull) != 0) {  // wave-uniform
-                    const bool h0 = nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, c0.x, c0.y, c0.z, c0.w, T0);
-                    const bool h1 = nms_eliminates_fast(v[u].x, v[u].y, v[u].z, v[u].w, c1.x, c1.y, c1.z, c1.w, T1);
-                    const unsigned long long near0 = __ballot(h0) & __ballot(u0 <= v_upper[u]), near1 = __ballot(h1) & __ballot(u1 <= v_upper[u]);
-                    if ((near0 | near1) != 0) {
-                        asm volatile("" ::: "memory");  // keeps this a branch
-                        unsigned long long out = (near0 & __ballot(u0 < v_upper[u])) | (near1 & __ballot(u1 < v_upper[u]));
-                        // equal scores: the lower index is ranked first (the victim itself is not)
-                        if (out == 0)
-                            out = (near0 & __ballot((sh.meta[t0 * kTile + lane] & 0xffffu) < v_index[u])) |
-                                  (near1 & __ballot((sh.meta[t1 * kTile + lane] & 0xffffu) < v_index[u]));
-                        if (out != 0) {
-                            dead |= 1u << u;
-                            reach[u] = 0;
-                            left &= reach[0] | reach[1] | reach[2] | reach[3];
+                const unsigned row = sh.list[u < members ? i0 + u : i0];
+                g_box[u] = sh.box[row];
+                g_upper[u] = sh.upper[row];
+                g_meta[u] = sh.meta[row];
+                g_T[u] = IOU ? sh.T[row] : 0.0f;
+                g_area[u] = IOU ? area_of(g_box[u]) : 0.0f;
+                g_label[u] = wide ? label_f[g_meta[u] & 0xffffu] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                reach[u] = 0;
+                if (u < members) {
+                    const float inter = inter_with(g_box[u], th_hull);
+                    bool near = inter >= (IOU ? (tile_T < 0.0f ? tile_T : fmaxf(tile_T, g_T[u])) : tile_T) && th_tile.y <= g_upper[u];
+                    if (LABELS) near = near && ((th_bins >> ((g_meta[u] >> 16) / (unsigned)(A * A) & (kPlaceBins - 1))) & 1u) != 0;
+                    reach[u] = __ballot(near);
+                }
+                left |= reach[u];
+            }
+            while (left != 0) {
+                const int t0 = __builtin_ctzll(left);
+                left &= left - 1;
+                const int t1 = left != 0 ? __builtin_ctzll(left) : t0;
+                left &= left - 1;  // (0 stays 0)
+                const int r0 = t0 * kTile + lane, r1 = t1 * kTile + lane;
+                const float4 c0 = sh.box[r0], c1 = sh.box[r1];
+                const float T0 = sh.T[r0], T1 = sh.T[r1];
+                const unsigned u0 = sh.upper[r0], u1 = sh.upper[r1];
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    if ((((reach[u] >> t0) | (reach[u] >> t1)) & 1ull) != 0) {  // wave-uniform
+                        const float i0 = inter_with(g_box[u], c0), i1 = inter_with(g_box[u], c1);
+                        unsigned long long near0 = __ballot(i0 >= (IOU ? fmaxf(T0, g_T[u]) : T0)) & __ballot(u0 <= g_upper[u]);
+                        unsigned long long near1 = __ballot(i1 >= (IOU ? fmaxf(T1, g_T[u]) : T1)) & __ballot(u1 <= g_upper[u]);
+                        if ((near0 | near1) != 0) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
+                            if (IOU) {
+                                near0 &= __ballot((double)i0 >= test.boundary * (double)((g_area[u] + area_of(c0)) - i0));
+                                near1 &= __ballot((double)i1 >= test.boundary * (double)((g_area[u] + area_of(c1)) - i1));
+                            }
+                            if (LABELS) {
+                                const unsigned m0 = sh.meta[r0], m1 = sh.meta[r1];
+                                near0 &= __ballot(((m0 ^ g_meta[u]) & kSame) == 0);
+                                near1 &= __ballot(((m1 ^ g_meta[u]) & kSame) == 0);
+                                if (wide) {
+                                    near0 &= __ballot(label_f[m0 & 0xffffu] == g_label[u]);
+                                    near1 &= __ballot(label_f[m1 & 0xffffu] == g_label[u]);
+                                }
+                            }
+                            const unsigned long long before0 = __ballot(u0 < g_upper[u]), before1 = __ballot(u1 < g_upper[u]);
+                            unsigned long long out0 = near0 & before0, out1 = near1 & before1;
+                            // equal scores: the lower index is ranked first (the victim itself is not)
+                            if (!test.ties_ignore && (out0 | out1) == 0) {
+                                out0 |= near0 & ~before0 & __ballot((sh.meta[r0] & 0xffffu) < (g_meta[u] & 0xffffu));
+                                out1 |= near1 & ~before1 & __ballot((sh.meta[r1] & 0xffffu) < (g_meta[u] & 0xffffu));
+                            }
+                            if ((out0 | out1) != 0) {
+                                dead |= 1u << u;
+                                reach[u] = 0;
+                                left &= reach[0] | reach[1] | reach[2] | reach[3];
+                            }
                         }
                     }
                 }
             }
+            if (lane < members) {
+                const unsigned meta = lane == 0 ? g_meta[0] : (lane == 1 ? g_meta[1] : (lane == 2 ? g_meta[2] : g_meta[3]));
+                const bool alive = ((dead >> lane) & 1u) == 0;
+                if (parts > 1) {
+                    keep_f[meta & 0xffffu] = alive ? 1 : 0;
+                } else if (alive) {
+                    sh.keep[meta & 0xffffu] = 1;
+                }
+            }
+            i0 = __builtin_amdgcn_readfirstlane(next);
         }
-        if (lane < members) {
-            unsigned e = v_index[0];
-#pragma unroll
-            for (int u = 1; u < G; ++u) e = lane == u ? v_index[u] : e;
-            const bool alive = ((dead >> lane) & 1u) == 0;
-            if (parts > 1) keep_f[e] = alive ? 1 : 0;
-            else if (alive) sh.keep[e] = 1;
-        }
-        i0 = __builtin_amdgcn_readfirstlane(next);
     }
     if (parts == 1) {
         lds_barrier();

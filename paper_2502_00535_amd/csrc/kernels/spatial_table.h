@@ -20,26 +20,6 @@ struct PlaceTable {
     uint2 *tile;         // [frames][n_pad / 64]   smallest T, best (smallest) upper half
 };
 
-// The variant of the pair test: pixel offset, rounding boundary next to the threshold (map_tile_ex_kernel).
-struct PlaceTest {
-    double boundary;
-    float offset;
-    int ties_ignore;
-    const int32_t *classes;  // null: no labels
-};
-
-// The float32 below which an intersection with a box eliminates nothing: the value that decides (outranking area), or, under
-// IoU, a bound that no union undercuts (c_T1 of map_tile_ex_kernel).
-template <bool IOU>
-__device__ __forceinline__ float place_threshold(float area, double boundary)
-{
-    if (!IOU) return nms_pair_threshold(area, boundary);
-    const double t = boundary * (double)area * (1.0 - 0x1p-21);
-    float t1 = (float)t;
-    if ((double)t1 > t) t1 = __uint_as_float(__float_as_uint(t1) - 1u);  // next float32 down (t > 0)
-    return t1 > 0.0f ? t1 : 0.0f;
-}
-
 constexpr int kSortWaves = 16;
 constexpr int kSortThreads = kSortWaves * 64;
 constexpr int kSortAxis = 32;

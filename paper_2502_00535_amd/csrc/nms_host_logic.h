@@ -278,6 +278,19 @@ NMS_HD int nms_spatial_frames_split(int n_max, int parts, int W)
     return tiles * 4 <= W ? 2 : (tiles * 2 <= W ? 1 : 0);
 }
 
+// The same for the paper's rule with IoU, labels, a strict compare or ignored ties, against rank and map step.  Whole call, us, place / before,
+// sparse anchors, then clustered with 20 labels: 1 x 1000 9.4 / 11.4, 9.0 / 15.5; 60 x 1000 19.0 / 23.7, 17.5 / 30.3; 200 x 700 35 / 29, 28 / 39;
+// 100 x 2000 59 / 74, 46 / 104; 20 x 4096 31 / 71, 26 / 94; 10 x 500 10.4 / 10.6, 10.0 / 13.4; 60 x 300 13.4 / 11.5, 12.0 / 14.4;
+// 60 x 200 13.2 / 12.6, 12.9 / 15.2.  Longer frames: 5 x 7000 crowd 19 / 60.
+NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool labelled)
+{
+    const long long total = (long long)frames * n_max;
+    if (n_max > 1024) return true;
+    if (n_max > 512) return total <= 100000;
+    if (n_max > 256) return total <= 6000;
+    return labelled && total <= 12000;
+}
+
 // Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.
 NMS_HD int nms_place_share(int n_max, int frames)
 {

@@ -246,6 +246,27 @@ int place_scan_launch(const int32_t *counts, int n_max, int frames, const PlaceT
     return launch_status();
 }
 
+// Boxes in order of place, one launch (kernels/spatial_frames.h); thresholds with a division-free form.
+template <bool IOU, bool LABELS>
+int spatial_frames_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                          const PlaceTest &test, uint8_t *keep_out, hipStream_t stream)
+{
+    const int parts = nms_spatial_frames_parts(n_max, frames);
+    const dim3 grid((unsigned)frames, (unsigned)parts);
+    begin_launch();
+#define NMS_LAUNCH_PLACE(W_, E_, AXIS_)                                                                                \
+    spatial_frames_kernel<W_, E_, AXIS_, IOU, LABELS><<<grid, dim3(W_ * 64), 0, stream>>>(                     \
+        boxes, scores, counts, n_max, nms_spatial_frames_split(n_max, parts, W_), test, keep_out)
+    constexpr bool kVariant = IOU || LABELS;
+    if (kVariant && n_max <= 256) NMS_LAUNCH_PLACE(4, 1, 8);
+    else if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+    else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
+    else if (!LABELS && n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
+    else NMS_LAUNCH_PLACE(16, 4, 32);
+#undef NMS_LAUNCH_PLACE
+    return launch_status();
+}
+
 }  // namespace
 
 // ----------------------------------------------------------------------------- C ABI
@@ -464,24 +485,6 @@ static int staged_launch(const RunWorkspace &w, const int32_t *counts, int n_max
     return launch_status();
 }
 
-// Boxes in order of place, one launch (kernels/spatial_frames.h); th.fast.
-static int spatial_frames_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
-                                 const NmsThetaConst &th, uint8_t *keep_out, hipStream_t stream)
-{
-    const int parts = nms_spatial_frames_parts(n_max, frames);
-    const dim3 grid((unsigned)frames, (unsigned)parts);
-    begin_launch();
-#define NMS_LAUNCH_PLACE(W_, E_, AXIS_) \
-    spatial_frames_kernel<W_, E_, AXIS_><<<grid, dim3(W_ * 64), 0, stream>>>(boxes, scores, counts, n_max,                 \
-                                                                             nms_spatial_frames_split(n_max, parts, W_), th, keep_out)
-    if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
-    else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
-    else if (n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
-    else NMS_LAUNCH_PLACE(16, 4, 32);
-#undef NMS_LAUNCH_PLACE
-    return launch_status();
-}
-
 // The table's parts lie where the ranked routes keep theirs (the layout of nms_run_layout): boxes and T in sorted5's place,
 // rank keys in tsc's, input indices in order's, the tiles' hulls in ysc's.
 static PlaceTable place_table(const RunWorkspace &w, int n_pad, int frames, int32_t *label)
@@ -499,16 +502,16 @@ static PlaceTable place_table(const RunWorkspace &w, int n_pad, int frames, int3
 }
 
 // The paper's rule on long frames: table, scan.
-static int place_paper_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
-                              const NmsThetaConst &th, uint8_t *keep_out, void *workspace, hipStream_t stream)
+static int place_paper_launch(bool iou, const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                              const PlaceTest &test, uint8_t *keep_out, void *workspace, int32_t *label, hipStream_t stream)
 {
-    const int n_pad = nms_padded_n(n_max);
     const RunWorkspace w = carve_workspace(workspace, n_max, frames);
-    const PlaceTable tab = place_table(w, n_pad, frames, nullptr);
-    const PlaceTest test = {th.m, 1.0f, 0, nullptr};
-    const int st = place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
+    const PlaceTable tab = place_table(w, nms_padded_n(n_max), frames, label);
+    const int st = iou ? place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream)
+                       : place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
     if (st != NMS_OK) return st;
-    return place_scan_launch<false>(counts, n_max, frames, test, tab, keep_out, stream);
+    return iou ? place_scan_launch<true>(counts, n_max, frames, test, tab, keep_out, stream)
+               : place_scan_launch<false>(counts, n_max, frames, test, tab, keep_out, stream);
 }
 
 // forward: defined with the early-exit entry point below
@@ -539,11 +542,11 @@ static int run_routed(Route route, const float *boxes, const float *scores, cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (route == kRouteAuto && nms_use_spatial_frames(n_max, frames, kChunk)) {
         const NmsThetaConst th = nms_make_theta_const(threshold);
-        if (th.fast) return spatial_frames_launch(boxes, scores, counts, n_max, frames, th, keep_out, s);
+        if (th.fast) return spatial_frames_launch<false, false>(boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, s);
     }
     if (route == kRouteAuto && n_max > kChunk) {
         const NmsThetaConst th = nms_make_theta_const(threshold);
-        if (th.fast) return place_paper_launch(boxes, scores, counts, n_max, frames, th, keep_out, workspace, s);
+        if (th.fast) return place_paper_launch(false, boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, workspace, nullptr, s);
     }
     if (small)
         return small_frames_launch(boxes, scores, counts, n_max, frames, nms_make_theta_const(threshold), keep_out, s);
@@ -835,6 +838,20 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         boundary = 0.5 * ((double)threshold + (double)other);
         divide = false;
     }
+    const int flags = (opt.ties == NMS_TIES_IGNORE ? kExTiesIgnore : 0) | (opt.classes ? kExClasses : 0);
+    const int mode = !divide ? kExBoundary : (opt.compare == NMS_COMPARE_GT ? kExDivideGt : kExDivideGe);
+    const bool iou = opt.measure == NMS_MEASURE_IOU;
+    const bool aux = flags != 0;
+    if (opt.rule == NMS_RULE_PAPER && !divide && (iou || opt.pixel_offset == 1.0f) &&
+        nms_use_spatial_variant(n_max, frames, opt.classes != nullptr)) {
+        const PlaceTest test = {boundary, opt.pixel_offset, opt.ties == NMS_TIES_IGNORE ? 1 : 0, opt.classes};
+        if (n_max > kChunk) return place_paper_launch(iou, boxes, scores, counts, n_max, frames, test, keep_out, workspace, ranked_class, s);
+        if (iou)
+            return opt.classes ? spatial_frames_launch<true, true>(boxes, scores, counts, n_max, frames, test, keep_out, s)
+                               : spatial_frames_launch<true, false>(boxes, scores, counts, n_max, frames, test, keep_out, s);
+        return opt.classes ? spatial_frames_launch<false, true>(boxes, scores, counts, n_max, frames, test, keep_out, s)
+                           : spatial_frames_launch<false, false>(boxes, scores, counts, n_max, frames, test, keep_out, s);
+    }
     // under the paper's rule the row reduction is folded into the map kernel: keep_out starts at 1
     const bool fold = opt.rule == NMS_RULE_PAPER;
     st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, fold ? keep_out : nullptr, nullptr,
@@ -863,10 +880,6 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         boundary_lo = (float)want;
         if ((double)boundary_lo > want) boundary_lo = nextafterf(boundary_lo, 0.0f);
     }
-    const int flags = (opt.ties == NMS_TIES_IGNORE ? kExTiesIgnore : 0) | (opt.classes ? kExClasses : 0);
-    const int mode = !divide ? kExBoundary : (opt.compare == NMS_COMPARE_GT ? kExDivideGt : kExDivideGe);
-    const bool iou = opt.measure == NMS_MEASURE_IOU;
-    const bool aux = flags != 0;
     if (opt.rule == NMS_RULE_GREEDY && n_max <= kChunk && (long long)frames * n_max >= kGreedyFusedBoxes) {
         // large batches under the greedy rule: the mask-free walk, one workgroup per frame
         const NmsThetaConst th = nms_make_theta_const(threshold);

@@ -1,0 +1,74 @@
+"""The paper's rule with IoU, strict compare, ignored ties and labels in order of place (spatial_frames_kernel, place_sort_kernel and
+place_scan_kernel with the variants) against the oracle, 0 differing bits: every table size, labels in and outside 0 .. 255 and in one bin, boxes without area, ties between copies."""
+import itertools
+
+import numpy as np
+import pytest
+
+from test_gpu_variants import ExFrames, oracle_ex
+from workloads import clustered_frame, random_frame
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nms():
+    import torch
+
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2502_00535_amd.binding as binding
+
+    return binding
+
+
+def batch(seed, frames, n, offset0=False):
+    rng = np.random.default_rng(seed)
+    boxes, scores, labels = np.zeros((frames, n, 4), np.float32), np.zeros((frames, n), np.float32), np.zeros((frames, n), np.int32)
+    for f in range(frames):
+        if f % 2:
+            b, s = clustered_frame(seed + f, objects=(n + 15) // 16, width=1920, height=1080, size_lo=16.0, size_hi=300.0)
+            b, s = b[:n], s[:n]
+        else:
+            b, s = random_frame(seed + f, n, extent=900, max_side=80, integer=f % 4 == 0, score_levels=max(3, n // 4))
+        src, dst = rng.integers(0, n, n // 8), rng.integers(0, n, n // 8)
+        b[dst], s[dst] = b[src], s[src]
+        boxes[f], scores[f] = b, s
+        labels[f] = [rng.integers(0, 5, n), rng.integers(0, 20, n), 16 * rng.integers(0, 9, n), rng.integers(-3, 400, n), np.full(n, 7)][f % 5]
+    if offset0:  # continuous coordinates: extents above 0
+        boxes[..., 2:] += np.float32(1.0)
+    counts = rng.integers(0, n + 1, frames).astype(np.int32)
+    counts[0] = n
+    return boxes, scores, labels, counts
+
+
+def check(nms, oracle, data, theta, opts):
+    boxes, scores, labels, counts = data
+    want = oracle_ex(oracle, boxes, scores, labels, theta, opts, counts, workers=16)
+    dev = ExFrames(nms, boxes, scores, labels, counts)
+    got = dev.run(theta, opts)
+    assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits: {opts}"
+
+
+@pytest.mark.parametrize("frames,n", [(9, 100), (40, 256), (10, 300), (6, 512), (11, 1000), (5, 1025), (6, 2048), (5, 2049), (7, 4096), (2, 4097), (3, 9000)])
+def test_papers_rule(nms, oracle, frames, n):
+    for measure, compare, ties, labelled in itertools.product(("iou", "outranking_area"), ("ge", "gt"), ("index", "ignore"), (False, True)):
+        opts = dict(rule="paper", measure=measure, compare=compare, ties=ties, pixel_offset=1.0 if compare == "ge" or measure != "iou" else 0.0,
+                    labelled=labelled)
+        print(f"case {frames} x {n} {opts}", flush=True)
+        check(nms, oracle, batch(n, frames, n, offset0=opts["pixel_offset"] == 0.0), 0.45, opts)
+
+
+def test_equal_iou_at_the_threshold(nms, oracle):
+    """Pairs whose quotient is the threshold exactly, where the compare decides."""
+    n = 1500
+    base = np.zeros((n, 4), np.float32)
+    cell = np.arange(n)
+    base[:, 0], base[:, 1] = (cell % 40) * 64.0, (cell // 40) * 64.0
+    base[:, 2:] = base[:, :2] + 32.0
+    base[1::2, :2] = base[:-1:2, :2]
+    base[1::2, 2:] = base[:-1:2, :2] + np.array([32.0, 16.0], np.float32)   # IoU 1/2 with offset 0
+    scores = np.random.default_rng(1).permutation(n).astype(np.float32)[None]
+    labels = np.zeros((1, n), np.int32)
+    for compare, labelled in itertools.product(("ge", "gt"), (False, True)):
+        opts = dict(rule="paper", measure="iou", compare=compare, ties="index", pixel_offset=0.0, labelled=labelled)
+        check(nms, oracle, (base[None], scores, labels, np.array([n], np.int32)), 0.5, opts)
