@@ -107,6 +107,12 @@ NMS_HD int nms_count_rank_elements(int n_max, int frames)
     return n_max > 384 && (long long)frames * n_max <= (n_max > 1024 ? 8192 : 4096) ? 16 : 64;
 }
 
+// ---- greedy rule, small frames -----------------------------------------------------------------------
+// Frames of at most this many boxes are settled by one workgroup in one launch (greedy_small_kernel) instead of rank, mask and
+// sweep.  Whole call, us, one launch / three: 30 x 70 6.7 / 11.6 (IoU 7.0 / 14.1, with labels 9.6 / 16.5), 1 x 128 7.3 / 12.3, 200 x 128 7.9 / 12.5,
+// 50 x 160 8.8 / 12.2, 400 x 70 7.6 / 15.0; with a fourth tile 20 x 200 11.4 / 12.3, 100 x 256 12.8 / 13.1, 8000 x 250 263 / 243.
+constexpr int kGreedySmallBoxes = 192;
+
 // ---- greedy rule with labels ----------------------------------------------------------------------
 // Large batches under the greedy rule with labels (greedy_classes_kernel; a batch there holds at least
 // 131,072 boxes).  The figures: IoU, whole call, scenes where much / little is eliminated, in us.

@@ -54,6 +54,7 @@ __device__ __forceinline__ int frame_count(const int32_t *counts, int f, int n_m
 #include "kernels/greedy_sweep.h"
 #include "kernels/greedy_walk.h"
 #include "kernels/greedy_classes.h"
+#include "kernels/greedy_small.h"
 #include "kernels/variants.h"
 #include "kernels/early_exit.h"
 #include "kernels/staged.h"
@@ -264,6 +265,19 @@ int spatial_frames_launch(const float *boxes, const float *scores, const int32_t
     else if (!LABELS && n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
     else NMS_LAUNCH_PLACE(16, 4, 32);
 #undef NMS_LAUNCH_PLACE
+    return launch_status();
+}
+
+// The greedy rule on frames of at most kGreedySmallBoxes boxes (kernels/greedy_small.h).
+template <bool EX, bool IOU, int MODE, bool AUX>
+int greedy_small_launch(const float *boxes, const float *scores, const int32_t *classes, const int32_t *counts, int n_max, int frames,
+                        const NmsThetaConst &th, const FusedVariant &v, uint8_t *keep_out, hipStream_t stream)
+{
+    begin_launch();
+    if (n_max <= 128)
+        greedy_small_kernel<128, EX, IOU, MODE, AUX><<<dim3((unsigned)frames), dim3(4 * 128), 0, stream>>>(boxes, scores, classes, counts, n_max, th, v, keep_out);
+    else
+        greedy_small_kernel<kGreedySmallBoxes, EX, IOU, MODE, AUX><<<dim3((unsigned)frames), dim3(4 * kGreedySmallBoxes), 0, stream>>>(boxes, scores, classes, counts, n_max, th, v, keep_out);
     return launch_status();
 }
 
@@ -762,6 +776,13 @@ int nms_run_greedy_batched(const float *boxes, const float *scores, const int32_
     if (!boxes || !scores || !keep_out) return NMS_ERR_INVALID_ARG;
     if (!workspace || ws_bytes < nms_greedy_workspace_bytes(n_max, frames) || ((uintptr_t)workspace & 255))
         return NMS_ERR_WORKSPACE;
+    if (n_max <= kGreedySmallBoxes) {
+        const NmsThetaConst th = nms_make_theta_const(threshold);
+        const FusedVariant none = {nullptr, nullptr, 0.0, 1.0f, 0};
+        hipStream_t small = static_cast<hipStream_t>(stream);
+        return th.fast ? greedy_small_launch<false, false, kExBoundary, false>(boxes, scores, nullptr, counts, n_max, frames, th, none, keep_out, small)
+                       : greedy_small_launch<false, false, kExDivideGe, false>(boxes, scores, nullptr, counts, n_max, frames, th, none, keep_out, small);
+    }
     // batches with a few dozen frames or more: one workgroup walks each frame, no mask
     if (n_max <= kChunk && (long long)frames * n_max >= kGreedyFusedBoxes)
         return run_greedy_fused(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace,
@@ -842,6 +863,19 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     const int mode = !divide ? kExBoundary : (opt.compare == NMS_COMPARE_GT ? kExDivideGt : kExDivideGe);
     const bool iou = opt.measure == NMS_MEASURE_IOU;
     const bool aux = flags != 0;
+    if (opt.rule == NMS_RULE_GREEDY && n_max <= kGreedySmallBoxes) {
+        const NmsThetaConst th = nms_make_theta_const(threshold);
+        const FusedVariant v = {nullptr, nullptr, boundary, opt.pixel_offset, flags};
+#define NMS_SMALL(IOU_, MODE_, AUX_) \
+    greedy_small_launch<true, IOU_, MODE_, AUX_>(boxes, scores, opt.classes, counts, n_max, frames, th, v, keep_out, s)
+#define NMS_SMALL_MODE(IOU_, AUX_)                                                                        \
+    (mode == kExBoundary ? NMS_SMALL(IOU_, kExBoundary, AUX_)                                             \
+                         : (mode == kExDivideGe ? NMS_SMALL(IOU_, kExDivideGe, AUX_) : NMS_SMALL(IOU_, kExDivideGt, AUX_)))
+        if (iou) return aux ? NMS_SMALL_MODE(true, true) : NMS_SMALL_MODE(true, false);
+        return aux ? NMS_SMALL_MODE(false, true) : NMS_SMALL_MODE(false, false);
+#undef NMS_SMALL_MODE
+#undef NMS_SMALL
+    }
     if (opt.rule == NMS_RULE_PAPER && !divide && (iou || opt.pixel_offset == 1.0f) &&
         nms_use_spatial_variant(n_max, frames, opt.classes != nullptr)) {
         const PlaceTest test = {boundary, opt.pixel_offset, opt.ties == NMS_TIES_IGNORE ? 1 : 0, opt.classes};
@@ -900,8 +934,7 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
                 w.sorted5, w.order, counts, n_max, n_pad, parts, th, v, keep_out);                      \
     } while (0)
             const int waves = nms_class_waves(n_max, frames);
-            if (waves == 4 && n_max <= 256) NMS_LAUNCH_CLASSES(4, 256);
-            else if (waves == 4 && n_max <= 512) NMS_LAUNCH_CLASSES(4, 512);
+            if (waves == 4 && n_max <= 512) NMS_LAUNCH_CLASSES(4, 512);
             else if (waves == 4) NMS_LAUNCH_CLASSES(4, 1024);
             else if (waves == 8 && n_max <= 512) NMS_LAUNCH_CLASSES(8, 512);
             else if (waves == 8) NMS_LAUNCH_CLASSES(8, 1024);

@@ -1,5 +1,7 @@
 """The paper's rule with IoU, strict compare, ignored ties and labels in order of place (spatial_frames_kernel, place_sort_kernel and
-place_scan_kernel with the variants) against the oracle, 0 differing bits: every table size, labels in and outside 0 .. 255 and in one bin, boxes without area, ties between copies."""
+place_scan_kernel with the variants), and the greedy rule on short frames (greedy_small_kernel), against the oracle, 0 differing
+bits: every table size, labels in and outside 0 .. 255 and in one bin, boxes without area, ties between copies, frame lengths around
+tiles, thresholds with and without a division-free form."""
 import itertools
 
 import numpy as np
@@ -72,3 +74,13 @@ def test_equal_iou_at_the_threshold(nms, oracle):
     for compare, labelled in itertools.product(("ge", "gt"), (False, True)):
         opts = dict(rule="paper", measure="iou", compare=compare, ties="index", pixel_offset=0.0, labelled=labelled)
         check(nms, oracle, (base[None], scores, labels, np.array([n], np.int32)), 0.5, opts)
+
+
+@pytest.mark.parametrize("frames,n", [(3, 1), (5, 63), (5, 64), (7, 65), (40, 128), (9, 129), (30, 191), (300, 192), (9, 193)])
+def test_greedy_on_short_frames(nms, oracle, frames, n):
+    print(f"case {frames} x {n}", flush=True)
+    for measure, compare, ties, labelled in itertools.product(("outranking_area", "iou"), ("ge", "gt"), ("index", "ignore"), (False, True)):
+        opts = dict(rule="greedy", measure=measure, compare=compare, ties=ties, pixel_offset=1.0 if compare == "ge" else 0.0, labelled=labelled)
+        data = batch(7 * n, frames, n, offset0=compare == "gt")
+        for theta in (0.4, 0.0):
+            check(nms, oracle, data, theta, opts)
