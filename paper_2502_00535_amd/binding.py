@@ -149,7 +149,9 @@ def _on_device(t) -> bool:
 
 # A call on a small frame is as long as its marshalling (10 us of it at 360 boxes before the helpers below
 # compared dtypes as objects, passed addresses as plain integers and asked for the raw stream): they
-# build nothing that the call does not need.
+# build nothing that the call does not need, and look at what is in order in one expression.  The whole-path calls on
+# one frame and on batches go through _marshal (csrc/marshal.c), which does the same in native code.
+_Tensor = torch.Tensor
 _DTYPES = {"float32": torch.float32, "int32": torch.int32, "int64": torch.int64, "uint8": torch.uint8}
 
 
@@ -160,6 +162,9 @@ def _ptr(t, dtype_name: str | None, what: str, need: int = 0):
     kernel could run past its end."""
     if t is None:
         return None
+    if (isinstance(t, _Tensor) and t.is_cuda and t.is_contiguous() and t.numel() >= need
+            and (dtype_name is None or t.dtype == _DTYPES[dtype_name])):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{what}: expected a torch tensor")
     if t.numel() < need:
@@ -175,7 +180,8 @@ def _ptr(t, dtype_name: str | None, what: str, need: int = 0):
 
 def _boxes(n_max, frames):
     """frames * n_max, the element count of the per-box buffers; 0 when the library will refuse the sizes anyway."""
-    n_max, frames = int(n_max), int(frames)
+    if type(n_max) is not int or type(frames) is not int:
+        n_max, frames = int(n_max), int(frames)
     return frames * n_max if n_max >= 0 and frames >= 0 else 0
 
 
@@ -191,12 +197,13 @@ def _sizes(n_max, frames):
 def _ws(t):
     if t is None:
         return None, 0
-    return _ptr(t, None, "workspace"), t.numel() * t.element_size()
+    return _ptr(t, None, "workspace"), t.nbytes
 
 
 # The current stream's handle without a Stream object around it, where this torch has that (it is not part of
 # torch's public interface, so another version may lack it).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)  # torch.cuda.current_device without its check for an initialized runtime
 
 
 def _stream(stream):
@@ -204,7 +211,21 @@ def _stream(stream):
         return stream.cuda_stream
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    if _current_device is None or not torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_current_device())
+
+
+from . import _marshal  # noqa: E402  (built with the library)
+
+_marshal.setup(torch.Tensor, torch.float32, torch.int32, torch.uint8, _current_device, _raw_stream)
+
+
+def _address(name):
+    return ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+
+
+_RUN_BATCHED, _RUN_RANKED, _RUN_GREEDY = (_address(n) for n in ("nms_run_batched", "nms_run_ranked_batched", "nms_run_greedy_batched"))
 
 
 def _check(status: int, where: str):
@@ -294,6 +315,11 @@ def nms_reduce_batched(mask, order, counts, n_max, frames, keep_out, stream=None
 
 
 def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
+    status = _marshal.run(_RUN_BATCHED, boxes, scores, None, n, 1, threshold, keep_out, workspace, stream)  # what nms_run_ws calls
+    if status == NMS_OK:
+        return
+    if status is not None:
+        raise NmsError(status, "nms_run_ws")
     fn_ = _boxes(n, 1)
     w, wb = _ws(workspace)
     _check(lib.nms_run_ws(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_), int(n),
@@ -302,6 +328,11 @@ def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
 
 
 def nms_run_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
+    status = _marshal.run(_RUN_BATCHED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    if status == NMS_OK:
+        return
+    if status is not None:
+        raise NmsError(status, "nms_run_batched")
     fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
@@ -341,6 +372,11 @@ class RunPlan:
 
 
 def nms_run_ranked_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
+    status = _marshal.run(_RUN_RANKED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    if status == NMS_OK:
+        return
+    if status is not None:
+        raise NmsError(status, "nms_run_ranked_batched")
     fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_ranked_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),
@@ -387,6 +423,11 @@ def nms_greedy_workspace_bytes(n_max: int, frames: int) -> int:
 
 
 def nms_run_greedy_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
+    status = _marshal.run(_RUN_GREEDY, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    if status == NMS_OK:
+        return
+    if status is not None:
+        raise NmsError(status, "nms_run_greedy_batched")
     fn_ = _boxes(n_max, frames)
     w, wb = _ws(workspace)
     _check(lib.nms_run_greedy_batched(_ptr(boxes, "float32", "boxes", 4 * fn_), _ptr(scores, "float32", "scores", fn_),

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = [os.path.join(_HERE, "csrc", "nms_kernels.hip")]
@@ -11,6 +12,8 @@ HEADERS = [os.path.join(_HERE, "csrc", "nms_pair.h"), os.path.join(_HERE, "csrc"
            *sorted(os.path.join(_HERE, "csrc", "kernels", f)
                    for f in os.listdir(os.path.join(_HERE, "csrc", "kernels")) if f.endswith(".h"))]
 LIBRARY = os.path.join(_HERE, "libnms_mi355x.so")
+MARSHAL_SOURCE = os.path.join(_HERE, "csrc", "marshal.c")
+MARSHAL = os.path.join(_HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 # -ffp-contract=off: the pair test must round every operation on its own (the one
 #   fused multiply-add it uses is written explicitly).
@@ -28,14 +31,26 @@ HIPCC_FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIBRARY):
+    if not os.path.exists(LIBRARY) or not os.path.exists(MARSHAL):
         return True
     built = os.path.getmtime(LIBRARY)
-    return any(os.path.getmtime(p) > built for p in SOURCES + HEADERS)
+    return any(os.path.getmtime(p) > built for p in SOURCES + HEADERS) or os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL)
+
+
+def build_marshal() -> str:
+    """The binding's native marshalling (CPython's C API, no device code); returns the path of the module."""
+    tmp = MARSHAL + f".tmp{os.getpid()}"
+    cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], MARSHAL_SOURCE, "-o", tmp]
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("gcc failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 def build_library(verbose: bool = False) -> str:
-    """Always compiles; returns the path of the shared object."""
+    """Always compiles (the binding's marshalling module as well); returns the path of the shared object."""
+    build_marshal()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIBRARY + f".tmp{os.getpid()}"
     cmd = [hipcc, *HIPCC_FLAGS, *SOURCES, "-o", tmp]

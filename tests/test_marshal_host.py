@@ -1,0 +1,50 @@
+"""The native marshalling leaves every argument that is not in order to the Python path, which names it; no GPU needed."""
+import numpy as np
+import pytest
+import torch
+
+
+def test_what_is_not_in_order_is_named():
+    import paper_2502_00535_amd.binding as nms
+
+    n = 8
+    boxes, scores = torch.zeros(1, n, 4), torch.zeros(1, n)
+    keep, ws = torch.zeros(1, n, dtype=torch.uint8), torch.zeros(1 << 16, dtype=torch.uint8)
+    run = nms._marshal.run
+    good = [nms._RUN_BATCHED, boxes, scores, None, n, 1, 0.5, keep, ws, None]
+    assert run(*good) is None                                     # tensors of the CPU
+    for at, other in ((1, "boxes"), (1, None), (3, 5), (4, -1), (4, 1 << 40), (4, 8.0), (5, True), (6, 1), (8, None)):
+        assert run(*(good[:at] + [other] + good[at + 1:])) is None
+    with pytest.raises(TypeError):
+        run(*good[:-1])
+    for call, args in ((nms.nms_run_ws, (boxes, scores, n, 0.5, keep, None)), (nms.nms_run_batched, (boxes, scores, None, n, 1, 0.5, keep, None)),
+                       (nms.nms_run_ranked_batched, (boxes, scores, None, n, 1, 0.5, keep, None)),
+                       (nms.nms_run_greedy_batched, (boxes, scores, None, n, 1, 0.5, keep, None))):
+        with pytest.raises(ValueError, match="boxes: tensor must live on the GPU"):
+            call(*args)
+        with pytest.raises(TypeError, match="boxes: expected a torch tensor"):
+            call("boxes", *args[1:])
+
+
+@pytest.mark.gpu
+def test_the_two_paths_agree():
+    import paper_2502_00535_amd.binding as nms
+
+    n = 300
+    g = torch.Generator().manual_seed(1)
+    xy = torch.rand(2, n, 2, generator=g) * 200
+    boxes, scores = torch.cat([xy, xy + 30], -1).cuda(), torch.rand(2, n, generator=g).cuda()
+    ws = torch.empty(nms.nms_workspace_bytes(n, 2), dtype=torch.uint8, device="cuda")
+    a, b, c = (torch.full((2, n), 9, dtype=torch.uint8, device="cuda") for _ in range(3))
+    nms.nms_run_batched(boxes, scores, None, n, 2, 0.5, a, ws)
+    nms.nms_run_batched(boxes, scores, None, n, 2, np.float32(0.5), b, ws)  # not a float: the Python path
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    nms.nms_run_batched(boxes, scores, None, n, 2, 0.5, c, ws, stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and torch.equal(a, c) and int(a.max()) == 1
+    for bad in (boxes.double(), boxes[:, ::2], boxes[:1], boxes.cpu()):
+        with pytest.raises((TypeError, ValueError)):
+            nms.nms_run_batched(bad, scores, None, n, 2, 0.5, a, ws)
+    with pytest.raises(nms.NmsError):
+        nms.nms_run_batched(boxes, scores, None, n, 2, 0.5, a, ws[:256])
