@@ -297,6 +297,20 @@ NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool labelled)
     return labelled && total <= 12000;
 }
 
+// The greedy rule under IoU in order of place (place_relation_kernel, place_resolve_kernel) against rank, mask and sweep; from walk_boxes boxes in
+// frames of up to sort_chunk on the walk and the class kernel take them.  Whole call, us, place / before, clustered, then sparse anchors:
+// 1 x 4096 27.5 / 36.0, 24.1 / 35.4; 4 x 4096 33.9 / 49.0, 28.3 / 47.4; 31 x 4096 89 / 136, 72 / 121; 20 x 3000 53 / 73, 43 / 64; 1 x 8000 41 / 87;
+// 6 x 8000 57 / 136; 3 x 2000 22.9 / 24.0, 19.0 / 23.0, but 8 x 2000 29.7 / 26.8, 22.4 / 25.6; 1 x 1000 18.4 / 18.8, 16.3 / 17.2, but
+// 10 x 1000 25 / 19.  (Under the default measure a box has ten times the eliminators: 24 x 3000 anchors 133 / 60.)
+NMS_HD bool nms_use_place_greedy(int n_max, int frames, int sort_chunk, long long walk_boxes)
+{
+    const long long total = (long long)frames * n_max;
+    if (n_max <= 256 || n_max > 2 * sort_chunk) return false;
+    if (n_max <= 1024) return frames == 1;
+    if (n_max <= 2048) return total <= 6000;
+    return n_max > sort_chunk || total < walk_boxes;
+}
+
 // Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.
 NMS_HD int nms_place_share(int n_max, int frames)
 {

@@ -225,7 +225,8 @@ int place_sort_launch(const float *boxes, const float *scores, const int32_t *co
     begin_launch();
 #define NMS_LAUNCH_SORT(E_, MULTI_)                                                                                     \
     place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, keep_out)
-    if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
+    if (n_max <= 4 * kSortThreads) NMS_LAUNCH_SORT(4, false);
+    else if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
     else if (n_max <= 16 * kSortThreads) NMS_LAUNCH_SORT(16, false);
     else NMS_LAUNCH_SORT(16, true);
 #undef NMS_LAUNCH_SORT
@@ -278,6 +279,29 @@ int greedy_small_launch(const float *boxes, const float *scores, const int32_t *
         greedy_small_kernel<128, EX, IOU, MODE, AUX><<<dim3((unsigned)frames), dim3(4 * 128), 0, stream>>>(boxes, scores, classes, counts, n_max, th, v, keep_out);
     else
         greedy_small_kernel<kGreedySmallBoxes, EX, IOU, MODE, AUX><<<dim3((unsigned)frames), dim3(4 * kGreedySmallBoxes), 0, stream>>>(boxes, scores, classes, counts, n_max, th, v, keep_out);
+    return launch_status();
+}
+
+int place_relation_launch(const int32_t *counts, int n_max, int frames, const PlaceTest &test, const PlaceTable &tab,
+                          const PlaceRelation &rel, uint8_t *keep_out, hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    const int tiles = n_pad / kTile;
+    begin_launch();
+    if ((long long)frames * tiles <= 128)  // a workgroup per compute unit, two victims per wavefront
+        place_relation_kernel<16, 2><<<dim3((unsigned)frames, (unsigned)tiles * 2), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 1, test, tab, rel);
+    else
+        place_relation_kernel<16, 4><<<dim3((unsigned)frames, (unsigned)tiles), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 0, test, tab, rel);
+    const int st = launch_status();
+    if (st != NMS_OK) return st;
+    begin_launch();
+#define NMS_LAUNCH_RESOLVE(R_) \
+    place_resolve_kernel<R_><<<dim3((unsigned)frames), dim3(kResolveWaves * 64), 0, stream>>>(counts, n_max, n_pad, tab.index, rel, keep_out)
+    if (tiles <= kResolveWaves) NMS_LAUNCH_RESOLVE(1);
+    else if (tiles <= 2 * kResolveWaves) NMS_LAUNCH_RESOLVE(2);
+    else if (tiles <= 4 * kResolveWaves) NMS_LAUNCH_RESOLVE(4);
+    else NMS_LAUNCH_RESOLVE(8);
+#undef NMS_LAUNCH_RESOLVE
     return launch_status();
 }
 
@@ -513,6 +537,30 @@ static PlaceTable place_table(const RunWorkspace &w, int n_pad, int frames, int3
     t.hull = w.ysc;
     t.tile = reinterpret_cast<uint2 *>(t.hull + tiles);
     return t;
+}
+
+// The greedy rule under IoU in order of place: table, relation, resolve.  Frames of 256 (kRelationWords tiles) to 2 * NMS_SORT_CHUNK boxes; words: the
+// mask's place, n_pad / 64 words per row.  The table as above, but the summary takes ysc (8 or 16 bytes per row), the tiles of the first
+// masks and the hulls what is left of it, or the place of the sort keys that frames beyond NMS_SORT_CHUNK boxes have.
+static int place_greedy_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
+                               const PlaceTest &test, uint8_t *keep_out, void *workspace, int32_t *label, unsigned long long *words,
+                               hipStream_t stream)
+{
+    const int n_pad = nms_padded_n(n_max);
+    const size_t rows = (size_t)frames * n_pad;
+    const RunWorkspace w = carve_workspace(workspace, n_max, frames);
+    PlaceTable tab = place_table(w, n_pad, frames, label);
+    PlaceRelation rel;
+    rel.S = (n_pad / kTile + 63) / 64;
+    rel.summary = reinterpret_cast<unsigned long long *>(w.ysc);
+    rel.at = rel.S == 1 ? reinterpret_cast<unsigned *>(rel.summary + rows) : reinterpret_cast<unsigned *>(w.keys);
+    rel.first = words;
+    rel.further = words + rows * kRelationWords;
+    tab.hull = reinterpret_cast<float4 *>(rel.at + rows);  // (rows is a multiple of 64)
+    tab.tile = reinterpret_cast<uint2 *>(tab.hull + rows / kTile);
+    const int st = place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
+    if (st != NMS_OK) return st;
+    return place_relation_launch(counts, n_max, frames, test, tab, rel, keep_out, stream);
 }
 
 // The paper's rule on long frames: table, scan.
@@ -875,6 +923,10 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         return aux ? NMS_SMALL_MODE(false, true) : NMS_SMALL_MODE(false, false);
 #undef NMS_SMALL_MODE
 #undef NMS_SMALL
+    }
+    if (opt.rule == NMS_RULE_GREEDY && !divide && iou && nms_use_place_greedy(n_max, frames, kChunk, kGreedyFusedBoxes)) {
+        const PlaceTest test = {boundary, opt.pixel_offset, opt.ties == NMS_TIES_IGNORE ? 1 : 0, opt.classes};
+        return place_greedy_launch(boxes, scores, counts, n_max, frames, test, keep_out, workspace, ranked_class, mask, s);
     }
     if (opt.rule == NMS_RULE_PAPER && !divide && (iou || opt.pixel_offset == 1.0f) &&
         nms_use_spatial_variant(n_max, frames, opt.classes != nullptr)) {

@@ -1,5 +1,6 @@
 """The paper's rule with IoU, strict compare, ignored ties and labels in order of place (spatial_frames_kernel, place_sort_kernel and
-place_scan_kernel with the variants), and the greedy rule on short frames (greedy_small_kernel), against the oracle, 0 differing
+place_scan_kernel with the variants), the greedy rule under IoU in order of
+place (place_relation_kernel, place_resolve_kernel) and on short frames (greedy_small_kernel), against the oracle, 0 differing
 bits: every table size, labels in and outside 0 .. 255 and in one bin, boxes without area, ties between copies, frame lengths around
 tiles, thresholds with and without a division-free form."""
 import itertools
@@ -83,4 +84,32 @@ def test_greedy_on_short_frames(nms, oracle, frames, n):
         opts = dict(rule="greedy", measure=measure, compare=compare, ties=ties, pixel_offset=1.0 if compare == "ge" else 0.0, labelled=labelled)
         data = batch(7 * n, frames, n, offset0=compare == "gt")
         for theta in (0.4, 0.0):
+            check(nms, oracle, data, theta, opts)
+
+
+@pytest.mark.parametrize("frames,n", [(1, 257), (1, 1000), (3, 2000), (2, 2049), (3, 4096), (2, 4097), (1, 8192), (1, 8193)])
+def test_greedy_iou(nms, oracle, frames, n):
+    print(f"case {frames} x {n}", flush=True)
+    for compare, ties, labelled in itertools.product(("ge", "gt"), ("index", "ignore"), (False, True)):
+        opts = dict(rule="greedy", measure="iou", compare=compare, ties=ties, pixel_offset=1.0 if compare == "ge" else 0.0, labelled=labelled)
+        check(nms, oracle, batch(5 * n, frames, n, offset0=compare == "gt"), 0.45, opts)
+
+
+def test_greedy_iou_chains_and_crowds(nms, oracle):
+    """Long chains of boxes that eliminate only the next one (many rounds), and boxes with eliminators in every tile (more masks per row
+    than are kept in registers)."""
+    opts = dict(rule="greedy", measure="iou", compare="gt", ties="index", pixel_offset=0.0, labelled=False)
+    n = 3000
+    step = np.arange(n, dtype=np.float32) * 4
+    chain = np.stack([step, np.zeros(n, np.float32), step + 10, np.full(n, 10, np.float32)], 1)
+    scores = (1.0 - np.arange(n) / n).astype(np.float32)
+    labels, counts = np.zeros((1, n), np.int32), np.array([n], np.int32)
+    perm = np.random.default_rng(1).permutation(n)
+    check(nms, oracle, (chain[None, perm], scores[None, perm], labels, counts), 0.3, opts)
+    rng = np.random.default_rng(2)
+    for n in (2500, 6000):
+        xy = rng.random((1, n, 2)).astype(np.float32) * 300
+        boxes = np.concatenate([xy, xy + 100 + 50 * rng.random((1, n, 2)).astype(np.float32)], -1)
+        data = (boxes, rng.random((1, n)).astype(np.float32), np.zeros((1, n), np.int32), np.array([n], np.int32))
+        for theta in (0.02, 0.3, 0.6):
             check(nms, oracle, data, theta, opts)
