@@ -494,9 +494,10 @@ def main():
                 structure["differing_keep_bits_vs_oracle"] = differing
                 structure["oracle_1_core_us_per_frame"] = round((time.perf_counter() - t0) * 1e6 / wo.frames, 1)
             del ws_go, keep_go
+            # these thresholds have a division-free form: beyond the direct form the configurations take the boxes in order of place
             route = {0: "direct (one launch)", 1: "all pairs (rank + fused pair-test kernel)",
-                     2: "two launches (best 2048 ranks, then the victims still alive)", 3: "early exit",
-                     4: "small frames (one launch, no sort: picked boxes, then the victims still alive against the frame)"}[nms.nms_route(wo.n, wo.frames)]
+                     2: "in order of place (two launches: table, then the victims against the tiles that reach them)", 3: "early exit",
+                     4: "in order of place (one launch: best of the cells around, then the tiles that reach a victim)"}[nms.nms_route(wo.n, wo.frames)]
             skips = nms.nms_route(wo.n, wo.frames) >= 2
             ms_pairs = ms_o  # the time in which every pair of the ranked triangle is evaluated
             if skips:

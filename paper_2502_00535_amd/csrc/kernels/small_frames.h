@@ -3,6 +3,8 @@
 
 // ----------------------------------------------------------------------------- small frames, one launch
 
+// (Thresholds with a division-free form come here for the smaller batches only and up to 1024 boxes: spatial_frames_kernel takes
+// the rest.)
 // A batch of some tens to hundreds of frames of at most a thousand boxes is too much arithmetic
 // for the direct form and too little for separate launches.  Here one workgroup does everything
 // for its frame, out of LDS, and nothing is sorted: Algorithm 1 asks of a pair only which of the two

@@ -225,8 +225,13 @@ int place_sort_launch(const float *boxes, const float *scores, const int32_t *co
     begin_launch();
 #define NMS_LAUNCH_SORT(E_, MULTI_)                                                                                     \
     place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, keep_out)
-    if (n_max <= 4 * kSortThreads) NMS_LAUNCH_SORT(4, false);
-    else if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
+    if constexpr (IOU) {  // frames of up to 4096 boxes come here under the greedy rule only
+        if (n_max <= 4 * kSortThreads) {
+            NMS_LAUNCH_SORT(4, false);
+            return launch_status();
+        }
+    }
+    if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
     else if (n_max <= 16 * kSortThreads) NMS_LAUNCH_SORT(16, false);
     else NMS_LAUNCH_SORT(16, true);
 #undef NMS_LAUNCH_SORT
@@ -259,12 +264,17 @@ int spatial_frames_launch(const float *boxes, const float *scores, const int32_t
 #define NMS_LAUNCH_PLACE(W_, E_, AXIS_)                                                                                \
     spatial_frames_kernel<W_, E_, AXIS_, IOU, LABELS><<<grid, dim3(W_ * 64), 0, stream>>>(                     \
         boxes, scores, counts, n_max, nms_spatial_frames_split(n_max, parts, W_), test, keep_out)
-    constexpr bool kVariant = IOU || LABELS;
-    if (kVariant && n_max <= 256) NMS_LAUNCH_PLACE(4, 1, 8);
-    else if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
-    else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
-    else if (!LABELS && n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
-    else NMS_LAUNCH_PLACE(16, 4, 32);
+    if constexpr (LABELS) {  // short frames come here with labels only; the bins of labels want the finer grid beyond 1024 boxes
+        if (n_max <= 256) NMS_LAUNCH_PLACE(4, 1, 8);
+        else if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+        else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
+        else NMS_LAUNCH_PLACE(16, 4, 32);
+    } else {
+        if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+        else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
+        else if (n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
+        else NMS_LAUNCH_PLACE(16, 4, 32);
+    }
 #undef NMS_LAUNCH_PLACE
     return launch_status();
 }
