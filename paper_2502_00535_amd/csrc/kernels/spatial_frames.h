@@ -135,18 +135,6 @@ struct PlaceTest {
     const int32_t *classes;  // null: no labels
 };
 
-// The float32 below which an intersection with a box eliminates nothing: the value that decides (outranking area), or, under
-// IoU, a bound that no union undercuts (c_T1 of map_tile_ex_kernel).
-template <bool IOU>
-__device__ __forceinline__ float place_threshold(float area, double boundary)
-{
-    if (!IOU) return nms_pair_threshold(area, boundary);
-    const double t = boundary * (double)area * (1.0 - 0x1p-21);
-    float t1 = (float)t;
-    if ((double)t1 > t) t1 = __uint_as_float(__float_as_uint(t1) - 1u);  // next float32 down (t > 0)
-    return t1 > 0.0f ? t1 : 0.0f;
-}
-
 // The tables of a frame.  P rows, AXIS cells per axis and size class.
 template <int P, int AXIS>
 struct PlaceShared {
@@ -290,7 +278,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
         if (e < n_f) {
             const unsigned row = sh.start[cell[q]] + within[q];
             sh.box[row] = b[q];
-            sh.T[row] = place_threshold<IOU>(((b[q].z - b[q].x) + off) * ((b[q].w - b[q].y) + off), test.boundary);
+            sh.T[row] = nms_place_threshold<IOU>(((b[q].z - b[q].x) + off) * ((b[q].w - b[q].y) + off), test.boundary);
             sh.upper[row] = upper[q];
             sh.meta[row] = (unsigned)e | (cell[q] << 16) | (LABELS ? (unsigned)(label[q] & 0xf0) << 24 : 0u);
             atomicMin(&sh.best[A + 1 + cell[q]], (upper[q] & ~4095u) | row);
@@ -319,17 +307,8 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             for (int i = 0; i < 4; ++i) {
                 const int row = t * kTile + i * 16 + (lane & 15);
                 const float4 v = sh.box[row];
-                float T = sh.T[row];
                 const unsigned u = sh.upper[row];
-                const bool there = row < n_f;
-                const bool odd = IOU && !(T > 0.0f);
-                const float far = odd ? -INFINITY : INFINITY;
-                if (odd) T = -INFINITY;
-                h.x = fminf(h.x, there && !odd ? v.x : far);
-                h.y = fminf(h.y, there && !odd ? v.y : far);
-                h.z = fminf(h.z, there && !odd ? -v.z : far);
-                h.w = fminf(h.w, there && !odd ? -v.w : far);
-                least = fminf(least, T);
+                nms_place_hull_add<IOU>(h, least, v, sh.T[row], row < n_f);
                 best = u < best ? u : best;
             }
             h.x = row_min(h.x), h.y = row_min(h.y), h.z = row_min(h.z), h.w = row_min(h.w);
@@ -341,11 +320,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             }
         }
     }
-    auto inter_with = [&](const float4 v, const float4 c) __attribute__((always_inline)) {
-        const float iw = (fminf(v.z, c.z) - fmaxf(v.x, c.x)) + off;  // one floor is enough where T > 0: see nms_pair.h
-        const float ih = fmaxf(0.0f, (fminf(v.w, c.w) - fmaxf(v.y, c.y)) + off);
-        return iw * ih;
-    };
+    auto inter_with = [&](const float4 v, const float4 c) __attribute__((always_inline)) { return nms_place_inter(v, c, off); };
     auto area_of = [&](const float4 v) __attribute__((always_inline)) { return ((v.z - v.x) + off) * ((v.w - v.y) + off); };
 
     // A lane's victim against the boxes named in the cells of a line around it: `below` classes smaller, dy lines on (at the border of the
@@ -468,7 +443,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
     const float4 th_hull = sh.hull[lane < tiles ? lane : 0];
     const uint2 th_tile = sh.tile[lane < tiles ? lane : 0];
     const unsigned th_bins = LABELS ? sh.bins[lane < tiles ? lane : 0] : 0u;
-    const float tile_T = lane < tiles ? __uint_as_float(th_tile.x) : INFINITY;
+    const float tile_T = __uint_as_float(th_tile.x);
     constexpr int G = kPlaceGroup;
     float4 g_box[G];
     float g_T[G], g_area[G];
@@ -500,8 +475,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             for (int u = 0; u < G; ++u) {
                 reach[u] = 0;
                 if (u < members) {
-                    const float inter = inter_with(g_box[u], th_hull);
-                    bool near = inter >= (IOU ? (tile_T < 0.0f ? tile_T : fmaxf(tile_T, g_T[u])) : tile_T) && th_tile.y <= g_upper[u];
+                    bool near = nms_place_reaches<IOU>(lane, tiles, g_box[u], g_T[u], g_upper[u], th_hull, tile_T, th_tile.y, off);
                     if (LABELS) near = near && ((th_bins >> ((g_meta[u] >> 16) / (unsigned)(A * A) & (kPlaceBins - 1))) & 1u) != 0;
                     reach[u] = __ballot(near);
                 }
@@ -533,8 +507,8 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
                                 near0 &= __ballot(((m0 ^ g_meta[u]) & kSame) == 0);
                                 near1 &= __ballot(((m1 ^ g_meta[u]) & kSame) == 0);
                                 if (wide) {
-                                    near0 &= __ballot(label_f[m0 & 0xffffu] == g_label[u]);
-                                    near1 &= __ballot(label_f[m1 & 0xffffu] == g_label[u]);
+                                    near0 &= __ballot(((near0 >> lane) & 1ull) != 0 && label_f[m0 & 0xffffu] == g_label[u]);
+                                    near1 &= __ballot(((near1 >> lane) & 1ull) != 0 && label_f[m1 & 0xffffu] == g_label[u]);
                                 }
                             }
                             const unsigned long long before0 = __ballot(u0 < g_upper[u]), before1 = __ballot(u1 < g_upper[u]);

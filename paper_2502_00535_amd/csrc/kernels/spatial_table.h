@@ -12,7 +12,7 @@
 // 16 x 16,384 42 / 206, 64 ragged frames of 8192 62 / 162, 128 x 5000 78 / 166.
 struct PlaceTable {
     float4 *box;         // [frames][n_pad]
-    float *T;            // [frames][n_pad]        smallest intersection that may eliminate (see place_threshold)
+    float *T;            // [frames][n_pad]        smallest intersection that may eliminate (see nms_place_threshold)
     unsigned *upper;     // [frames][n_pad]        upper half of the rank key
     unsigned *index;     // [frames][n_max]        input index
     int32_t *label;      // [frames][n_pad]        class labels, where the call has them
@@ -207,11 +207,13 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
     const int rows = (hi - lo + kTile - 1) / kTile * kTile;         // with the last tile's empty rows
     if (i < rows) {  // whole wavefronts
         const bool there = i < hi - lo;
-        const unsigned e = there ? sh.index[i] : 0u;
+        // (coordinates that are not finite: a box counted under one cell and placed under another would leave a place unwritten)
+        const unsigned written = there ? sh.index[i] : 0u;
+        const unsigned e = written < (unsigned)n_f ? written : 0u;
         const float score = score_f[e];
         const float4 v = there ? sh.box[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float area = ((v.z - v.x) + test.offset) * ((v.w - v.y) + test.offset);
-        const float T = there ? place_threshold<IOU>(area, test.boundary) : INFINITY;
+        const float T = there ? nms_place_threshold<IOU>(area, test.boundary) : INFINITY;
         const unsigned upper = there ? (unsigned)(nms_rank_key(score, e) >> 32) : ~0u;
         const size_t at = (size_t)f * n_pad + lo + i;
         tab.box[at] = v;
@@ -219,12 +221,11 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
         tab.upper[at] = upper;
         if (there) tab.index[(size_t)f * n_max + lo + i] = e;
         if (test.classes != nullptr) tab.label[at] = test.classes[(size_t)f * n_max + e];
-        // a box without area (no positive T) may eliminate what it does not touch: its tile reaches everything
-        const bool odd = there && !(T > 0.0f);
-        float4 h = make_float4(there ? v.x : INFINITY, there ? v.y : INFINITY, there ? -v.z : INFINITY, there ? -v.w : INFINITY);
-        if (odd) h = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        float4 h = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+        float T_hull = INFINITY;
+        nms_place_hull_add<true>(h, T_hull, v, T, there);
         const float hx = wave_min(h.x), hy = wave_min(h.y), hz = wave_min(h.z), hw = wave_min(h.w);
-        const float least = wave_min(odd ? -INFINITY : T);
+        const float least = wave_min(T_hull);
         unsigned best = row16_min(upper);  // in every lane of the row
         {
             const unsigned b0 = (unsigned)__builtin_amdgcn_readlane((int)best, 0), b1 = (unsigned)__builtin_amdgcn_readlane((int)best, 16);
@@ -242,13 +243,6 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
 
 // Value of another lane, wave-uniform.
 __device__ __forceinline__ float lane_value(float x, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); }
-
-__device__ __forceinline__ float place_inter(const float4 v, const float4 c, float off)
-{
-    const float iw = (fminf(v.z, c.z) - fmaxf(v.x, c.x)) + off;  // one floor is enough where T > 0: see nms_pair.h
-    const float ih = fmaxf(0.0f, (fminf(v.w, c.w) - fmaxf(v.y, c.y)) + off);
-    return iw * ih;
-}
 
 // Where the boxes of a frame lie (PlaceTable at frame f).
 struct PlaceFrame {
@@ -289,7 +283,7 @@ template <bool IOU>
 __device__ __forceinline__ unsigned long long place_eliminators(const PlaceFrame &p, const PlaceTest &test, const PlaceVictim &v, int r,
                                                                 const float4 c, float T, unsigned u)
 {
-    const float inter = place_inter(v.box, c, test.offset);
+    const float inter = nms_place_inter(v.box, c, test.offset);
     unsigned long long near = __ballot(inter >= (IOU ? fmaxf(T, v.T) : T)) & __ballot(u <= v.upper);
     if (near == 0) return 0;
     asm volatile("" ::: "memory");  // keeps this a branch
@@ -328,14 +322,12 @@ __device__ __forceinline__ void place_scan_group(const PlaceFrame &p, const Plac
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const float T = s + c * kTile + lane < p.tiles ? __uint_as_float(hi[c].x) : INFINITY;
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
                     reach[c][u] = 0;
-                    if (u < members && ((settled >> u) & 1u) == 0) {
-                        const float inter = place_inter(v[u].box, h[c], test.offset);
-                        reach[c][u] = __ballot(inter >= (IOU && T >= 0.0f ? fmaxf(T, v[u].T) : T)) & __ballot(hi[c].y <= v[u].upper);
-                    }
+                    if (u < members && ((settled >> u) & 1u) == 0)
+                        reach[c][u] = __ballot(nms_place_reaches<IOU>(s + c * kTile + lane, p.tiles, v[u].box, v[u].T, v[u].upper, h[c],
+                                                                      __uint_as_float(hi[c].x), hi[c].y, test.offset));
                 }
             }
         }
@@ -417,7 +409,7 @@ place_scan_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, Plac
         for (int i = 0; i < kTile / W; ++i) {
             const int k = wave + W * i;
             const float4 c = make_float4(lane_value(mine.x, k), lane_value(mine.y, k), lane_value(mine.z, k), lane_value(mine.w, k));
-            const float inter = place_inter(mine, c, test.offset);
+            const float inter = nms_place_inter(mine, c, test.offset);
             unsigned long long hit = __ballot(inter >= (IOU ? fmaxf(lane_value(mine_T, k), mine_T) : lane_value(mine_T, k)));
             hit &= __ballot((unsigned)__builtin_amdgcn_readlane((int)mine_upper, k) < mine_upper);  // (equal scores: below)
             if (labelled) hit &= __ballot(__builtin_amdgcn_readlane(mine_label, k) == mine_label);

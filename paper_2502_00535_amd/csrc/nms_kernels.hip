@@ -26,6 +26,7 @@
 
 #include "../../include/nms.h"
 #include "nms_pair.h"
+#include "nms_place.h"
 #include "nms_host_logic.h"
 
 // Scratch of nms_run_static_batched: one copy per GPU, held from the moment the library is
