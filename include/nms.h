@@ -238,8 +238,9 @@ int nms_run_greedy_fused_batched(const float *boxes, const float *scores, const 
  * smaller batches of shorter ones), else rank and the map step with the options and the row
  * reduction folded in; the greedy rule rank, mask (workspace) and sweep, on large batches the
  * mask-free walk, on frames of at most 192 boxes one launch, and under IoU in order of place on most
- * batches of frames beyond 2048 boxes and on single shorter ones.  With every option at its default the
- * call is nms_run_batched / nms_run_greedy_batched.
+ * batches of frames of 2049 to 8192 boxes (its time then depends on the data: most where thousands of
+ * candidates crowd around few objects).  With every option at its default the call is nms_run_batched /
+ * nms_run_greedy_batched.
  *   options    HOST pointer, read before the call returns; NULL = all defaults
  *   workspace  >= nms_ex_workspace_bytes(n_max, frames) bytes, 256-byte aligned
  */

@@ -42,7 +42,7 @@ constexpr int kSweepWaves = kSweepTiles / kSweepOwned;
 template <bool FIRST>
 __global__ void __launch_bounds__(kSweepWaves * 64)
 greedy_sweep_kernel(const unsigned long long *__restrict__ mask, const int32_t *__restrict__ order,
-                    const int32_t *__restrict__ counts, int n_max, int n_pad, int t0, uint8_t *__restrict__ keep_out)
+                    const int32_t *__restrict__ counts, int n_max, int n_pad, int t0, int fill, uint8_t *__restrict__ keep_out)
 {
     __shared__ unsigned long long kept_s[kSweepTiles];
     const int f = blockIdx.x;
@@ -54,7 +54,7 @@ greedy_sweep_kernel(const unsigned long long *__restrict__ mask, const int32_t *
     const unsigned long long *m = mask + (size_t)f * ((size_t)(n_pad / kTile) * n_pad);
     uint8_t *keep_f = keep_out + (size_t)f * n_max;
     const int32_t *order_f = order + (size_t)f * n_max;
-    if (FIRST)
+    if (FIRST && fill)
         for (int i = n_f + (int)threadIdx.x; i < n_max; i += blockDim.x) keep_f[i] = 0;  // slots beyond the count
     if (t0 >= t1) return;  // uniform
     const int steps = (t1 - t0 + kSweepOwned - 1) / kSweepOwned;  // wavefronts that own tiles of this frame

@@ -336,6 +336,7 @@ rank_chunk_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
     const int base = chunk * kSpan;
     int cnt = n_f - base;
     cnt = cnt < 0 ? 0 : (cnt > kSpan ? kSpan : cnt);
+    if (!STAGE && cnt == 0 && ytile == nullptr && keep_preset == nullptr) return;  // (uniform) no keys, nothing else to write
     const float *scores_f = scores + (size_t)f * n_max;
     const float *boxes_f = boxes + (size_t)f * n_max * 4;
     int e[4];

@@ -475,9 +475,9 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             for (int u = 0; u < G; ++u) {
                 reach[u] = 0;
                 if (u < members) {
-                    bool near = nms_place_reaches<IOU>(lane, tiles, g_box[u], g_T[u], g_upper[u], th_hull, tile_T, th_tile.y, off);
+                    bool near = nms_place_reaches<IOU>(g_box[u], g_T[u], g_upper[u], th_hull, tile_T, th_tile.y, off);
                     if (LABELS) near = near && ((th_bins >> ((g_meta[u] >> 16) / (unsigned)(A * A) & (kPlaceBins - 1))) & 1u) != 0;
-                    reach[u] = __ballot(near);
+                    reach[u] = __ballot(near) & nms_place_tile_lanes(0, tiles);
                 }
                 left |= reach[u];
             }

@@ -43,7 +43,7 @@ struct PlaceSortShared {
 template <int E, bool MULTI, bool IOU>
 __global__ void __launch_bounds__(kSortThreads)
 place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,
-                  int n_max, int n_pad, int share, PlaceTest test, PlaceTable tab, uint8_t *__restrict__ keep_out)
+                  int n_max, int n_pad, int share, PlaceTest test, PlaceTable tab, unsigned *__restrict__ crowded, uint8_t *__restrict__ keep_out)
 {
     __shared__ PlaceSortShared sh;
     constexpr int kSpan = kSortThreads * E;
@@ -208,8 +208,8 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
     if (i < rows) {  // whole wavefronts
         const bool there = i < hi - lo;
         // (coordinates that are not finite: a box counted under one cell and placed under another would leave a place unwritten)
-        const unsigned written = there ? sh.index[i] : 0u;
-        const unsigned e = written < (unsigned)n_f ? written : 0u;
+        const unsigned written = sh.index[i], last = there ? (unsigned)(n_f - 1) : 0u;
+        const unsigned e = written < last ? written : last;
         const float score = score_f[e];
         const float4 v = there ? sh.box[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float area = ((v.z - v.x) + test.offset) * ((v.w - v.y) + test.offset);
@@ -223,7 +223,7 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
         if (test.classes != nullptr) tab.label[at] = test.classes[(size_t)f * n_max + e];
         float4 h = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
         float T_hull = INFINITY;
-        nms_place_hull_add<true>(h, T_hull, v, T, there);
+        nms_place_hull_add<IOU>(h, T_hull, v, T, there);
         const float hx = wave_min(h.x), hy = wave_min(h.y), hz = wave_min(h.z), hw = wave_min(h.w);
         const float least = wave_min(T_hull);
         unsigned best = row16_min(upper);  // in every lane of the row
@@ -237,6 +237,7 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
             const size_t t = (size_t)f * (n_pad / kTile) + (lo + i) / kTile;
             tab.hull[t] = make_float4(hx, hy, -hz, -hw);
             tab.tile[t] = make_uint2(__float_as_uint(least), best);
+            if (crowded != nullptr && lo + i == 0) crowded[f] = 0u;  // (for the relation launch)
         }
     }
 }
@@ -300,11 +301,12 @@ __device__ __forceinline__ unsigned long long place_eliminators(const PlaceFrame
     return near;
 }
 
-// What a group of victims is tested against: the tiles that reach one of them, 256 tiles at a time, two tiles' boxes in flight together.
+// What a group of victims is tested against: the tiles that reach one of them, 128 tiles at a time, K tiles' boxes in flight together.
 // found(u, t, mask): victim u of the group has eliminators `mask` (not 0) in tile t; returns whether that settles it.
-template <bool IOU, class Found>
+// many(u, k): k tiles of the 128 at hand reach victim u; returns whether that settles it.
+template <bool IOU, int K, class Many, class Found>
 __device__ __forceinline__ void place_scan_group(const PlaceFrame &p, const PlaceTest &test, const PlaceVictim (&v)[kPlaceGroup], int members,
-                                                 int lane, Found found)
+                                                 int lane, Many many, Found found)
 {
     constexpr int G = kPlaceGroup, C = 2;
     unsigned settled = 0;
@@ -322,12 +324,23 @@ __device__ __forceinline__ void place_scan_group(const PlaceFrame &p, const Plac
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) {
+                const unsigned long long lanes = s + c * kTile < p.tiles ? nms_place_tile_lanes(s + c * kTile, p.tiles) : 0ull;
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
                     reach[c][u] = 0;
                     if (u < members && ((settled >> u) & 1u) == 0)
-                        reach[c][u] = __ballot(nms_place_reaches<IOU>(s + c * kTile + lane, p.tiles, v[u].box, v[u].T, v[u].upper, h[c],
-                                                                      __uint_as_float(hi[c].x), hi[c].y, test.offset));
+                        reach[c][u] = __ballot(nms_place_reaches<IOU>(v[u].box, v[u].T, v[u].upper, h[c], __uint_as_float(hi[c].x), hi[c].y, test.offset)) & lanes;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                int k = 0;
+#pragma unroll
+                for (int c = 0; c < C; ++c) k += __builtin_popcountll(reach[c][u]);
+                if (k != 0 && many(u, k)) {  // wave-uniform
+                    settled |= 1u << u;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) reach[c][u] = 0;
                 }
             }
         }
@@ -338,7 +351,6 @@ __device__ __forceinline__ void place_scan_group(const PlaceFrame &p, const Plac
             for (int u = 0; u < G; ++u) left |= reach[c][u];
 #pragma unroll 1
             while (left != 0) {
-                constexpr int K = 2;
                 int t[K];
                 float4 b[K];
                 float T[K];
@@ -448,10 +460,12 @@ place_scan_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, Plac
             v[u].row = t * kTile + at;
         }
         unsigned dead = 0;
-        place_scan_group<IOU>(p, test, v, members, lane, [&](int u, int, unsigned long long) __attribute__((always_inline)) {
-            dead |= 1u << u;
-            return true;
-        });
+        place_scan_group<IOU, 2>(
+            p, test, v, members, lane, [](int, int) __attribute__((always_inline)) { return false; },
+            [&](int u, int, unsigned long long) __attribute__((always_inline)) {
+                dead |= 1u << u;
+                return true;
+            });
         if (lane < members) {
             unsigned e = v[0].index;
 #pragma unroll
@@ -463,26 +477,32 @@ place_scan_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, Plac
 
 // ----------------------------------------------------------------------------- greedy rule in order of place
 
-// The sequential rule needs, for every box, the better-ranked boxes that would eliminate it.  Under IoU these are few
+// The sequential rule needs, for every box, the better-ranked boxes that would eliminate it.  Under IoU these are mostly few
 // (1.3 per box on anchors, 8 on clustered detections), and in order of place they lie in one to six tiles: a launch writes them
-// down per row, as lane masks with their tiles, and another settles the rows of a frame.  One frame of 4096 clustered boxes: table
-// 8 us, relation 7.6, resolve 10.4 (which one workgroup does: its loads and the rounds), 27.5 for the call against 36.0 with
-// ranks, mask and sweep.
+// down per row, as lane masks with their tiles, and another settles the rows of a frame.  Where thousands of candidates crowd
+// around few objects a row has them in dozens of tiles; such a crowded row keeps the first kRelationMasks masks only, so that the
+// relation stays bounded, and what then cannot be settled from masks is walked in rank order.
 //
-// Per row: the first kRelationWords masks and a byte each for their tiles (bit 7 of the last: there are more), the further
-// masks behind those of all rows, in the order of the tiles named in `summary` (a bit per tile, S words).
-constexpr int kRelationWords = 4;
+// A row's masks lie as nms_relation_block says (columns, so that the lanes of a tile read one together); a byte each for their tiles.
+// A victim that more than kCrowdedReach tiles reach and that kCrowdedTile of its own tile's boxes overlap far enough is crowded without a look at
+// them all: clusters are reached by six tiles, and what many tiles reach without such neighbours (boxes of very different sizes) has few eliminators.
+constexpr int kCrowdedReach = 20, kCrowdedTile = 16;
+constexpr int kSampleTiles = 16;
+constexpr unsigned kRowCrowded = 0x80u;   // of PlaceRelation::at[].x: the row has more masks than are kept
+constexpr unsigned kRowMore = 0x8000u;    // of the same: masks behind the first four
+constexpr unsigned kNoTile = 0x80u;       // of the bytes behind the first four: no mask
 
 struct PlaceRelation {
-    unsigned long long *first;    // [frames][n_pad][kRelationWords]; 0: none
-    unsigned long long *further;  // [frames][n_pad][n_pad / 64 - kRelationWords]
-    unsigned *at;                 // [frames][n_pad]
-    unsigned long long *summary;  // [frames][n_pad][S]
-    int S;
+    unsigned long long *words;  // [frames] blocks of n_pad / 64 * n_pad words
+    uint4 *at;                  // [frames][n_pad]
+    unsigned *crowded;          // [frames] crowded ones of the rows that are sampled: the first wavefront's in each of the first kSampleTiles tiles
+    int32_t *left;              // [frames] boxes of the frames that the rounds have left open (0: settled), frames beyond NMS_SORT_CHUNK boxes
 };
 
 // W wavefronts per tile of victims (M of them in a group), parts workgroups per tile.  The masks of a victim are collected in the lanes
-// of a register and stored together: a store per mask would have every load of the next tiles wait for it.
+// of a register and stored together: a store per mask would have every load of the next tiles wait for it.  In large batches (M = 4), whose
+// workgroups come one after the other, the tiles still to come are not related at all once half of the rows sampled
+// are crowded: the frame will be walked.  (A count of all crowded rows is 4096 atomics on one address, 45 us.)
 template <int W, int M>
 __global__ void __launch_bounds__(W * 64)
 place_relation_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, int parts_log2, PlaceTest test, PlaceTable tab, PlaceRelation rel)
@@ -498,13 +518,18 @@ place_relation_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, 
     const int T = n_pad / kTile;
     const int row = t * kTile + lane;
     const bool there = row < n_f;
+    const unsigned crowded_rows = __hip_atomic_load(rel.crowded + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const float4 mine = p.box[row];
     const float mine_T = p.T[row];
     const unsigned mine_upper = p.upper[row];
     const unsigned mine_index = p.index[there ? row : n_f - 1];
     const int mine_label = labelled ? p.label[row] : 0;
     const float mine_area = ((mine.z - mine.x) + test.offset) * ((mine.w - mine.y) + test.offset);
+    const bool skip = M == 4 && __builtin_amdgcn_readfirstlane((int)crowded_rows) > kSampleTiles * M / 2;
+    unsigned long long *first_f = rel.words + (size_t)f * T * n_pad;
+    unsigned long long *more_f = first_f + nms_relation_block(n_pad).more;
     constexpr int G = kPlaceGroup;
+    unsigned crowded_here = 0;
 #pragma unroll 1
     for (int i0 = (part * W + wave) * M; i0 < kTile; i0 += (W << parts_log2) * M) {
         const int r0 = t * kTile + i0;
@@ -522,157 +547,348 @@ place_relation_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, 
             v[u].label = __builtin_amdgcn_readlane(mine_label, at);
             v[u].row = t * kTile + at;
         }
-        unsigned long long sum[2][G] = {};
         int found[G] = {};
-        unsigned w_lo[G] = {}, w_hi[G] = {}, tiles_of[G] = {};
-        unsigned long long *further_f = rel.further + ((size_t)f * n_pad + r0) * (size_t)(T > kRelationWords ? T - kRelationWords : 0);
-        place_scan_group<true>(p, test, v, members, lane, [&](int u, int tile, unsigned long long m) __attribute__((always_inline)) {
-            if (tile < kTile) sum[0][u] |= 1ull << tile;
-            else sum[1][u] |= 1ull << (tile - kTile);
-            const int k = found[u]++;
-            if (k < kRelationWords) {
+        unsigned w_lo[G] = {}, w_hi[G] = {}, tile_of[G];
+#pragma unroll
+        for (int u = 0; u < G; ++u) tile_of[u] = lane < kRelationWords ? 0u : kNoTile;
+        unsigned crowded = skip ? (1u << G) - 1u : 0u;
+        if (!skip) {
+            // a victim that many tiles reach and that a quarter of its own tile would eliminate or be eliminated by: crowded, without a look at them all
+            auto many = [&](int u, int k) __attribute__((always_inline)) {
+                if (k <= kCrowdedReach) return false;
+                asm volatile("" ::: "memory");  // keeps this a branch
+                const float inter = nms_place_inter(v[u].box, mine, test.offset);
+                unsigned long long near = __ballot(inter >= fmaxf(mine_T, v[u].T)) & __ballot((double)inter >= test.boundary * (double)((v[u].area + mine_area) - inter));
+                if (labelled) near &= __ballot(mine_label == v[u].label);
+                if (__builtin_popcountll(near) < kCrowdedTile) return false;
+                crowded |= 1u << u;
+                return true;
+            };
+            place_scan_group<true, M == 4 ? 2 : 4>(p, test, v, members, lane, many, [&](int u, int tile, unsigned long long m) __attribute__((always_inline)) {
+                const int k = found[u]++;
+                if (k == kRelationMasks) {
+                    crowded |= 1u << u;
+                    return true;
+                }
                 const bool here = lane == k;
                 w_lo[u] = here ? (unsigned)m : w_lo[u];
                 w_hi[u] = here ? (unsigned)(m >> 32) : w_hi[u];
-                tiles_of[u] |= (unsigned)tile << (8 * k);
-            } else {
-                tiles_of[u] |= 0x80000000u;
-                if (lane == 0) further_f[(size_t)u * (T - kRelationWords) + k - kRelationWords] = m;
-            }
-            return false;
-        });
+                tile_of[u] = here ? (unsigned)tile : tile_of[u];
+                return false;
+            });
+        }
 #pragma unroll
-        for (int u = 0; u < M; ++u)
-            if (u < members && lane < kRelationWords)
-                rel.first[((size_t)f * n_pad + r0 + u) * kRelationWords + lane] = ((unsigned long long)w_hi[u] << 32) | w_lo[u];
-        if (lane < members) {
-            unsigned long long w0 = sum[0][0], w1 = sum[1][0];
-            unsigned at = tiles_of[0];
-#pragma unroll
-            for (int u = 1; u < M; ++u) {
-                w0 = lane == u ? sum[0][u] : w0;
-                w1 = lane == u ? sum[1][u] : w1;
-                at = lane == u ? tiles_of[u] : at;
+        for (int u = 0; u < M; ++u) {
+            if (u < members) {
+                const size_t r = (size_t)(r0 + u);
+                const unsigned long long w = ((unsigned long long)w_hi[u] << 32) | w_lo[u];
+                if (lane < kRelationWords)
+                    first_f[r * kRelationWords + lane] = w;
+                else if (lane < kRelationMasks && lane < found[u])
+                    more_f[(size_t)(lane - kRelationWords) * n_pad + r] = w;
+                // four bytes to a word, in the first lane of each four
+                unsigned at = tile_of[u] << (8 * (lane & 3));
+                at |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)at, 0xb1, 0xf, 0xf, true);  // quad_perm: neighbour
+                at |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)at, 0x4e, 0xf, 0xf, true);  // quad_perm: the other pair
+                if (lane == 0) {
+                    at |= found[u] > kRelationWords ? kRowMore : 0u;
+                    if (((crowded >> u) & 1u) != 0) {
+                        at |= kRowCrowded;
+                        ++crowded_here;
+                    }
+                }
+                if (lane < kRelationMasks && (lane & 3) == 0) reinterpret_cast<unsigned *>(rel.at + (size_t)f * n_pad + r)[lane >> 2] = at;
             }
-            const size_t r = (size_t)f * n_pad + r0 + lane;
-            rel.at[r] = at;
-            rel.summary[r * rel.S] = w0;
-            if (rel.S > 1) rel.summary[r * rel.S + 1] = w1;
         }
     }
+    if (M == 4 && t < kSampleTiles && wave == 0 && lane == 0 && crowded_here != 0)
+        __hip_atomic_fetch_add(rel.crowded + f, crowded_here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A row without eliminators is kept; of the others a row with a kept eliminator is out, a row none of whose eliminators is kept or
-// open is kept, until no row is open.  A workgroup per frame, R tiles of 64 rows per wavefront (frames of at most 1024 R boxes),
-// lane = row; the states of the tiles are words in LDS.  A wavefront looks at its open rows, again while that settles some;
-// the best-ranked open row of the frame has no open eliminator, so something is settled between any two barriers, and the rounds end.
+// A row without eliminators is kept; of the others a row with a kept eliminator is out, a row all of whose eliminators are out
+// is kept, until no row is open or none can be settled any more.  A workgroup per frame, lane = row, up to R neighbouring tiles
+// per wavefront (frames of at most 1024 R boxes): chains of eliminators run between neighbours, so that they run inside a wavefront,
+// and inside a tile in registers.  The states of the tiles are words in LDS that only ever gain bits: a word read
+// late leaves rows open longer and does no harm.  A round ends with a barrier; a round in which nothing was settled is the last one, so
+// there are at most as many rounds as rows.
+//
+// Crowded rows, whose masks are not all there, are not settled here.  What is left open in the end (and what the rounds have not
+// settled after kResolveRounds: long chains across wavefronts) is, WALK, put in rank order together with the kept rows that may touch it, and walked
+// as in greedy_fused_kernel, by the same workgroup; beyond NMS_SORT_CHUNK boxes the frame is left to the general kernels (rel.left).
+//
+// What bounds it is one workgroup's chain: loads 3 us, rounds 8 (four to five passes over the rows, issue), stores 1 (1 x 4096 clustered: table 8,
+// relation 6, resolve 12; the walk of one object's candidates 25 more: sort 12, ranked rows 3, walk 7).  With the masks in LDS instead of registers and the
+// tiles in a loop 16 instead of 12; with the state of three masks or more behind a branch 13.  Frames beyond NMS_SORT_CHUNK boxes spill 12 vector registers.
+// The whole call against rank, mask and sweep: nms_use_place_greedy.
 constexpr int kResolveWaves = 16;
+constexpr int kResolvePasses = 8;    // of a wavefront over its tiles in a round
+constexpr int kResolveRounds = 128;  // (in frames with crowded rows kCrowdedRounds: what waits for those settles one by one)
+constexpr int kCrowdedRounds = 4;
 
-template <int R>
+struct ResolveSort {  // rows in input order, then sorted
+    unsigned long long keys[NMS_SORT_CHUNK];
+    __align__(16) unsigned hist[kResolveWaves * 256];
+    __align__(16) unsigned wbase[kResolveWaves * 256];
+    __align__(16) unsigned tot[256];
+    unsigned long long match[kResolveWaves * 512];
+    unsigned long long bits[kTile];  // by input index: rows of the walk
+    unsigned before[kTile];          // of them before each word
+};
+
+template <int R, bool AUX, bool WALK>
 __global__ void __launch_bounds__(kResolveWaves * 64)
-place_resolve_kernel(const int32_t *__restrict__ counts, int n_max, int n_pad, const unsigned *__restrict__ index, PlaceRelation rel,
-                     uint8_t *__restrict__ keep_out)
+place_resolve_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts, int n_max, int n_pad,
+                     PlaceTest test, PlaceTable tab, PlaceRelation rel, uint8_t *__restrict__ keep_out)
 {
-    constexpr int kTiles = kResolveWaves * R, K = kRelationWords;
-    __shared__ unsigned long long open_s[kTiles], kept_s[kTiles];
+    constexpr int K = kRelationWords, kMore = kRelationMasks - kRelationWords;
+    static_assert(!WALK || R * kResolveWaves * kTile == NMS_SORT_CHUNK, "the walk takes frames of one chunk");
+    using Walk = WalkShared<kFusedWaves, NMS_SORT_CHUNK>;
+    // (the states by themselves: through a reference into the walk's bytes the compiler would reach them by flat loads)
+    struct States {
+        unsigned long long kept[kResolveWaves * R], out[kResolveWaves * R];
+    };
+    __shared__ States st_s;
+    __shared__ uint16_t index_s[kResolveWaves * 64 * R];  // of the lane's row i: there are no registers for it
+    __shared__ unsigned news_s[3];  // of a round: bit 0: something was settled, bit 1: something is open, bit 2: there are crowded rows
+    __shared__ __align__(16) unsigned char raw[WALK ? (sizeof(ResolveSort) > sizeof(Walk) ? sizeof(ResolveSort) : sizeof(Walk)) : 16];
     const int f = blockIdx.x;
     const int tid = (int)threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_f = frame_count(counts, f, n_max);
+    if (!WALK && tid == 0) rel.left[f] = 0;
     if (n_f == 0) return;
     const int T = n_pad / kTile;
+    const int tiles = (n_f + kTile - 1) / kTile;
+    const int per = (tiles + kResolveWaves - 1) / kResolveWaves;  // tiles of a wavefront, <= R
+    uint8_t *keep_f = keep_out + (size_t)f * n_max;
+    const unsigned *index_f = tab.index + (size_t)f * n_max;
+    const unsigned long long *first_f = rel.words + (size_t)f * T * n_pad;
+    const unsigned long long *more_f = first_f + nms_relation_block(n_pad).more;
+    const uint4 *at_f = rel.at + (size_t)f * n_pad;
 
-    unsigned long long word[R][K];
-    unsigned at[R], index_of[R];
-    unsigned long long open[R], kept[R];  // wave-uniform: the state of the tile
+    unsigned long long word[R][K], own[R];  // masks in other tiles, in the row's own
+    unsigned at[R];
+    unsigned long long open[R], kept[R], crowd[R];  // wave-uniform: the state of the tile; its crowded rows
+    auto row_of = [&](int i) __attribute__((always_inline)) { return (wave * per + i) * kTile + lane; };
+    auto index_of = [&](int i) __attribute__((always_inline)) { return (unsigned)index_s[i * kResolveWaves * 64 + tid]; };
+    auto has = [&](int i) __attribute__((always_inline)) { return i < per && row_of(i) < n_f; };
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        const int row = (wave + kResolveWaves * i) * kTile + lane;
-        const size_t r = (size_t)f * n_pad + (row < n_f ? row : 0);
-        const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(rel.first + r * K);
+        const size_t r = has(i) ? (size_t)row_of(i) : 0;
+        const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(first_f + r * K);
         const ulonglong2 a = w[0], b = w[1];
         word[i][0] = a.x, word[i][1] = a.y, word[i][2] = b.x, word[i][3] = b.y;
-        at[i] = rel.at[r];
-        index_of[i] = index[(size_t)f * n_max + (row < n_f ? row : 0)];
+        at[i] = reinterpret_cast<const unsigned *>(at_f + r)[0];
+        index_s[i * kResolveWaves * 64 + tid] = (uint16_t)index_f[r];
     }
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        const int t = wave + kResolveWaves * i;
-        const bool there = t * kTile + lane < n_f;
-        open[i] = __ballot(there && (word[i][0] | word[i][1] | word[i][2] | word[i][3]) != 0);
-        kept[i] = __ballot(there) & ~open[i];
-        if (lane == 0) {
-            open_s[t] = open[i];
-            kept_s[t] = kept[i];
+        const int t = wave * per + i;
+        const bool there = has(i);
+        const unsigned long long rows = __ballot(there);
+        crowd[i] = __ballot(there && (at[i] & kRowCrowded) != 0);
+        open[i] = __ballot(there && (word[i][0] | word[i][1] | word[i][2] | word[i][3]) != 0) | crowd[i];
+        kept[i] = rows & ~open[i];
+        own[i] = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool is_own = ((at[i] >> (8 * k)) & 127u) == (unsigned)t;
+            own[i] |= is_own ? word[i][k] : 0ull;
+            word[i][k] = is_own ? 0ull : word[i][k];
+        }
+        if (lane == 0 && i < per && t < tiles) {
+            st_s.kept[t] = kept[i];
+            st_s.out[t] = ~rows;
         }
     }
-    __syncthreads();
-    auto load = [&](const unsigned long long *p) __attribute__((always_inline)) {
-        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (tid < 3) news_s[tid] = 0u;
+    lds_barrier();
+    struct State {
+        unsigned long long kept, out;
     };
-    for (;;) {
-        bool any;
-        for (int pass = 0; pass < 8; ++pass) {  // (the bound only lets the others' results in through a barrier now and then)
+    auto state = [&](unsigned tile) __attribute__((always_inline)) {
+        return State{__hip_atomic_load(&st_s.kept[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP),
+                     __hip_atomic_load(&st_s.out[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)};
+    };
+    auto scalar = [&](unsigned long long x) __attribute__((always_inline)) {
+        return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)x);
+    };
+    bool open_left = false;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+        unsigned news = 0;
+#pragma unroll 1
+        for (int pass = 0; pass < kResolvePasses; ++pass) {  // (the bound lets the others' results in through a barrier now and then)
             bool settled = false;
-            any = false;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                if (open[i] == 0) continue;  // wave-uniform
-                const int t = wave + kResolveWaves * i;
-                const bool mine = (open[i] >> lane) & 1ull;
-                unsigned long long is_open = 0ull, is_out = 0ull;
-                if (mine) {
-                    // open is read before kept, and written after it: a row that is no longer open by then has its kept bit
+                if (scalar(open[i] & ~crowd[i]) == 0) continue;
+                const int t = wave * per + i;
+                const bool mine = ((open[i] & ~crowd[i]) >> lane) & 1ull;
+                unsigned long long is_out = 0, is_open = 0;
+                {
+                    unsigned tiles_of = at[i];
+                    asm volatile("" : "+v"(tiles_of));  // (addresses kept from pass to pass would take what registers there are)
+                    State st[K];
 #pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        if (word[i][k] != 0) is_open |= word[i][k] & load(&open_s[(at[i] >> (8 * k)) & 127u]);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    for (int k = 0; k < K; ++k) st[k] = state((tiles_of >> (8 * k)) & 127u);  // (no mask: tile 0, to no effect)
 #pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        if (word[i][k] != 0) is_out |= word[i][k] & load(&kept_s[(at[i] >> (8 * k)) & 127u]);
-                    if ((at[i] >> 31) != 0 && is_out == 0 && is_open == 0) {  // further masks
-                        const size_t r = (size_t)f * n_pad + t * kTile + lane;
-                        const unsigned long long *more = rel.further + r * (size_t)(T - K);
-                        int k = 0;
-                        for (int half = 0; half < rel.S; ++half) {
-                            unsigned long long s = rel.summary[r * rel.S + half];
-                            while (s != 0 && is_out == 0) {
-                                const int tt = __builtin_ctzll(s) + kTile * half;
-                                s &= s - 1;
-                                if (k >= K) {
-                                    const unsigned long long w = more[k - K];
-                                    is_open |= w & load(&open_s[tt]);
-                                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                                    is_out |= w & load(&kept_s[tt]);
-                                }
-                                ++k;
+                    for (int k = 0; k < K; ++k) {
+                        is_out |= word[i][k] & st[k].kept;
+                        is_open |= word[i][k] & ~(st[k].kept | st[k].out);
+                    }
+                }
+                // the further masks: once a round, and where the first ones hold nothing open
+                const bool look = mine && (at[i] & kRowMore) != 0 && is_out == 0 && (pass == 0 || is_open == 0);
+                if (__ballot(look) != 0) {
+                    asm volatile("" ::: "memory");  // keeps this a branch
+                    if (look) {
+                        unsigned r = (unsigned)(t * kTile + lane);
+                        asm volatile("" : "+v"(r));  // (nor these addresses)
+#pragma unroll 1
+                        for (int j = 0; j < kMore; j += 4) {
+                            const unsigned tiles_of = reinterpret_cast<const unsigned *>(at_f + r)[1 + j / 4];
+                            unsigned long long w[4];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                w[k] = ((tiles_of >> (8 * k)) & 0xffu) != kNoTile ? more_f[(size_t)(j + k) * n_pad + r] : 0ull;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const State st = state((tiles_of >> (8 * k)) & 127u);
+                                is_out |= w[k] & st.kept;
+                                is_open |= w[k] & ~(st.kept | st.out);
                             }
+                            if ((tiles_of >> 24) == kNoTile || is_out != 0) break;
                         }
                     }
                 }
-                const unsigned long long now_out = __ballot(mine && is_out != 0);
-                const unsigned long long now_kept = __ballot(mine && is_out == 0 && is_open == 0);
-                if ((now_out | now_kept) != 0) {
+                const unsigned long long active = open[i] & ~crowd[i];
+                const unsigned long long go_out = __ballot(is_out != 0) & active, may_stay = __ballot(is_open == 0) & active;
+                unsigned long long now_open = scalar(open[i]), now_kept = scalar(kept[i]);
+                for (;;) {  // the tile's own rows: at most 64 times
+                    const unsigned long long o = (go_out | __ballot((own[i] & now_kept) != 0)) & now_open & ~crowd[i];
+                    const unsigned long long k = __ballot((own[i] & (now_open | now_kept)) == 0) & may_stay & now_open & ~o;
+                    if ((o | k) == 0) break;
+                    now_kept |= k;
+                    now_open &= ~(o | k);
+                }
+                if (now_open != open[i]) {
                     settled = true;
-                    kept[i] |= now_kept;
-                    open[i] &= ~(now_out | now_kept);
+                    open[i] = now_open;
+                    kept[i] = now_kept;
                     if (lane == 0) {
-                        __hip_atomic_store(&kept_s[t], kept[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                        __hip_atomic_store(&open_s[t], open[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        const int in_tile = n_f - t * kTile;
+                        const unsigned long long rows = in_tile >= kTile ? ~0ull : (1ull << in_tile) - 1ull;
+                        __hip_atomic_store(&st_s.kept[t], now_kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_store(&st_s.out[t], ~(rows & (now_open | now_kept)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                 }
-                any = any || open[i] != 0;
             }
-            if (!settled) break;
+            if (__builtin_amdgcn_readfirstlane(settled ? 1 : 0) == 0) break;
+            news |= 1u;
         }
-        if (__syncthreads_or(any ? 1 : 0) == 0) break;
-    }
-    uint8_t *keep_f = keep_out + (size_t)f * n_max;
+        {
+            unsigned long long any = 0;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int row = (wave + kResolveWaves * i) * kTile + lane;
-        if (row < n_f) keep_f[index_of[i]] = (uint8_t)((kept[i] >> lane) & 1ull);
+            for (int i = 0; i < R; ++i) any |= open[i];
+            news |= any != 0 ? 2u : 0u;
+            unsigned long long any_crowd = 0;
+#pragma unroll
+            for (int i = 0; i < R; ++i) any_crowd |= crowd[i];
+            news |= any_crowd != 0 ? 4u : 0u;
+        }
+        if (tid == 0) news_s[(round + 1) % 3] = 0u;
+        if (lane == 0 && news != 0) atomicOr(&news_s[round % 3], news);
+        lds_barrier();
+        const unsigned all = (unsigned)__builtin_amdgcn_readfirstlane((int)news_s[round % 3]);
+        if ((all & 2u) == 0) break;
+        if ((all & 1u) == 0 || round + 1 >= ((all & 4u) != 0 ? kCrowdedRounds : kResolveRounds)) {
+            open_left = true;
+            break;
+        }
+    }
+    if (!open_left) {  // uniform
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if (has(i)) keep_f[index_of(i)] = (uint8_t)((kept[i] >> lane) & 1ull);
+        return;
+    }
+    if constexpr (!WALK) {
+        if (tid == 0) rel.left[f] = n_f;
+    } else {
+        // ---- the open rows, and the kept ones that reach a tile with open rows, in input order
+        ResolveSort &so = *reinterpret_cast<ResolveSort *>(raw);
+        const unsigned long long open_tiles = __ballot(lane < tiles && ~(st_s.kept[lane < tiles ? lane : 0] | st_s.out[lane < tiles ? lane : 0]) != 0);
+        lds_barrier();  // (the states are not read any more)
+        if (tid < kTile) so.bits[tid] = 0ull;
+        unsigned long long walked[R];
+        {
+            const PlaceFrame p = place_frame(tab, f, n_f, n_max, n_pad);
+            const float4 hull = p.hull[lane < tiles ? lane : 0];
+            const float least = __uint_as_float(p.tile[lane < tiles ? lane : 0].x);
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                walked[i] = open[i];
+                if (kept[i] == 0) continue;  // wave-uniform
+                const float4 mine = p.box[has(i) ? row_of(i) : 0];
+                const float mine_T = p.T[has(i) ? row_of(i) : 0];
+                for (unsigned long long todo = kept[i]; todo != 0; todo &= todo - 1) {
+                    const int k = __builtin_ctzll(todo);
+                    const float4 c = make_float4(lane_value(mine.x, k), lane_value(mine.y, k), lane_value(mine.z, k), lane_value(mine.w, k));
+                    if ((__ballot(nms_place_reaches<true>(c, lane_value(mine_T, k), ~0u, hull, least, 0u, test.offset)) & open_tiles) != 0)
+                        walked[i] |= todo & (0ull - todo);
+                }
+            }
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if ((walked[i] >> lane) & 1ull) __hip_atomic_fetch_or(&so.bits[index_of(i) / 64u], 1ull << (index_of(i) % 64u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        lds_barrier();
+        const unsigned in_word = (unsigned)__builtin_popcountll(so.bits[lane]);
+        const unsigned upto = wave_inclusive_sum(in_word);
+        const int m = __builtin_amdgcn_readlane((int)upto, 63);
+        if (wave == 0) so.before[lane] = upto - in_word;
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if ((walked[i] >> lane) & 1ull) {
+                const unsigned long long below = so.bits[index_of(i) / 64u] & ((1ull << (index_of(i) % 64u)) - 1ull);
+                so.keys[so.before[index_of(i) / 64u] + (unsigned)__builtin_popcountll(below)] = nms_rank_key(scores[(size_t)f * n_max + index_of(i)], index_of(i));
+            }
+        }
+        lds_barrier();
+
+        // ---- in rank order, the ranked rows into the frame's block
+        unsigned key[4], idx[4];
+        int e[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            e[q] = wave * 256 + q * 64 + lane;
+            const unsigned long long v = e[q] < m ? so.keys[e[q]] : kSentinel;
+            key[q] = (unsigned)(v >> 32);
+            idx[q] = (unsigned)v;
+        }
+        radix_rank_large<kResolveWaves>(key, idx, e, m, so.keys, so.hist, so.tot, so.wbase, so.match);
+        float4 *sorted_f = reinterpret_cast<float4 *>(rel.words + (size_t)f * T * n_pad + nms_relation_block(n_pad).ranked);
+        int32_t *order_f = reinterpret_cast<int32_t *>(sorted_f + n_pad);
+        float *score_f = reinterpret_cast<float *>(order_f + n_pad);
+        int32_t *label_f = reinterpret_cast<int32_t *>(score_f + n_pad);
+        for (int r = tid; r < m; r += kResolveWaves * 64) {
+            const unsigned from = (unsigned)so.keys[r];
+            sorted_f[r] = reinterpret_cast<const float4 *>(boxes)[(size_t)f * n_max + from];
+            order_f[r] = (int32_t)from;
+            if (AUX) score_f[r] = scores[(size_t)f * n_max + from];
+            if (AUX && test.classes != nullptr) label_f[r] = test.classes[(size_t)f * n_max + from];
+        }
+        __syncthreads();
+        const FusedVariant v = {nullptr, nullptr, test.boundary, test.offset, (test.ties_ignore ? kExTiesIgnore : 0) | (test.classes != nullptr ? kExClasses : 0)};
+        walk_frame<true, true, kExBoundary, AUX>(*reinterpret_cast<Walk *>(raw), reinterpret_cast<const float *>(sorted_f), order_f, score_f, label_f,
+                                                 m, n_max, n_pad, NmsThetaConst{}, v, keep_f);
+#pragma unroll
+        for (int i = 0; i < R; ++i)  // (behind the barriers after the walk's zero fill)
+            if ((kept[i] >> lane) & 1ull) keep_f[index_of(i)] = 1;
     }
 }

@@ -17,6 +17,7 @@ gather_ranked_kernel(const int32_t *__restrict__ order, const float *__restrict_
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n_pad) return;
     const int n_f = frame_count(counts, f, n_max);
+    if (n_f == 0) return;  // (nothing reads the rows of an empty frame)
     const bool real = r < n_f;
     const int idx = real ? order[(size_t)f * n_max + r] : 0;
     ranked_score[(size_t)f * n_pad + r] = real ? scores[(size_t)f * n_max + idx] : -INFINITY;

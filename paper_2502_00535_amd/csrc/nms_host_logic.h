@@ -300,17 +300,33 @@ NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool labelled)
 }
 
 // The greedy rule under IoU in order of place (place_relation_kernel, place_resolve_kernel) against rank, mask and sweep; from walk_boxes boxes in
-// frames of up to sort_chunk on the walk and the class kernel take them.  Whole call, us, place / before, clustered, then sparse anchors:
-// 1 x 4096 27.5 / 36.0, 24.1 / 35.4; 4 x 4096 33.9 / 49.0, 28.3 / 47.4; 31 x 4096 89 / 136, 72 / 121; 20 x 3000 53 / 73, 43 / 64; 1 x 8000 41 / 87;
-// 6 x 8000 57 / 136; 3 x 2000 22.9 / 24.0, 19.0 / 23.0, but 8 x 2000 29.7 / 26.8, 22.4 / 25.6; 1 x 1000 18.4 / 18.8, 16.3 / 17.2, but
-// 10 x 1000 25 / 19.  (Under the default measure a box has ten times the eliminators: 24 x 3000 anchors 133 / 60.)
+// frames of up to sort_chunk on the walk and the class kernel take them.  Whole call, us, place / rank, mask and sweep, clustered, then sparse anchors:
+// 1 x 4096 27.3 / 36.0, 26.9 / 35.6; 4 x 4096 36 / 50, 33 / 48; 31 x 4096 91 / 134, 86 / 121; 20 x 3000 55 / 71, with 20 labels 49 / 74; 1 x 2049
+// 22.5 / 23.5; clustered 1 x 8000 61 / 89, 6 x 8000 90 / 142, 60 x 8000 334 / 725.  Shorter frames gain nothing, and at a lower threshold lose: 2 x 2048 at
+// 0.3 34 / 23, 3 x 1500 26 / 22.  Where thousands of candidates crowd around few objects: one object 1 x 4096 54 / 39, 31 x 4096 78 / 192, 1 x 8000 133 / 96; four
+// 83 / 38, 198 / 192, 147 / 96; sixteen 41 / 38, 172 / 190, 184 / 96.  A chain of 4096 eliminators in place order 270 / 187, in random order 939 / 187.
+// (Under the default measure a box has ten times the eliminators: 24 x 3000 anchors 133 / 60.)  Against the walk the line has not been drawn anew.
 NMS_HD bool nms_use_place_greedy(int n_max, int frames, int sort_chunk, long long walk_boxes)
 {
     const long long total = (long long)frames * n_max;
-    if (n_max <= 256 || n_max > 2 * sort_chunk) return false;
-    if (n_max <= 1024) return frames == 1;
-    if (n_max <= 2048) return total <= 6000;
+    if (n_max <= 2048 || n_max > 2 * sort_chunk) return false;
     return n_max > sort_chunk || total < walk_boxes;
+}
+
+// A frame's block of the relation, in 64-bit words; its place is the mask's, n_pad / 64 * n_pad words.  A row's first kRelationWords masks
+// lie side by side, the others in a column each; behind them the ranked rows of the walk (box, input index, score, label).
+constexpr int kRelationWords = 4;
+constexpr int kRelationMasks = 16;
+struct NmsRelationBlock {
+    size_t more, ranked, end;
+};
+NMS_HD NmsRelationBlock nms_relation_block(int n_pad)
+{
+    NmsRelationBlock b;
+    b.more = (size_t)kRelationWords * n_pad;
+    b.ranked = (size_t)kRelationMasks * n_pad;
+    b.end = b.ranked + (size_t)n_pad * (16 + 3 * 4) / 8;
+    return b;
 }
 
 // Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.

@@ -218,14 +218,14 @@ int map_launch(const float *sorted5, const int32_t *counts, int n_max, int frame
 
 template <bool IOU>
 int place_sort_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
-                             const PlaceTest &test, const PlaceTable &tab, uint8_t *keep_out, hipStream_t stream)
+                      const PlaceTest &test, const PlaceTable &tab, unsigned *crowded, uint8_t *keep_out, hipStream_t stream)
 {
     const int n_pad = nms_padded_n(n_max);
     const int share = nms_place_share(n_max, frames);
     const dim3 grid((unsigned)frames, (unsigned)((n_max + share - 1) / share)), block(kSortThreads);
     begin_launch();
 #define NMS_LAUNCH_SORT(E_, MULTI_)                                                                                     \
-    place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, keep_out)
+    place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, crowded, keep_out)
     if constexpr (IOU) {  // frames of up to 4096 boxes come here under the greedy rule only
         if (n_max <= 4 * kSortThreads) {
             NMS_LAUNCH_SORT(4, false);
@@ -293,25 +293,27 @@ int greedy_small_launch(const float *boxes, const float *scores, const int32_t *
     return launch_status();
 }
 
-int place_relation_launch(const int32_t *counts, int n_max, int frames, const PlaceTest &test, const PlaceTable &tab,
-                          const PlaceRelation &rel, uint8_t *keep_out, hipStream_t stream)
+int place_relation_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames, const PlaceTest &test,
+                          const PlaceTable &tab, const PlaceRelation &rel, uint8_t *keep_out, hipStream_t stream)
 {
     const int n_pad = nms_padded_n(n_max);
     const int tiles = n_pad / kTile;
     begin_launch();
-    if ((long long)frames * tiles <= 128)  // a workgroup per compute unit, two victims per wavefront
+    if ((long long)frames * tiles <= 64)  // a workgroup per compute unit, a victim per wavefront
+        place_relation_kernel<16, 1><<<dim3((unsigned)frames, (unsigned)tiles * 4), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 2, test, tab, rel);
+    else if ((long long)frames * tiles <= 128)
         place_relation_kernel<16, 2><<<dim3((unsigned)frames, (unsigned)tiles * 2), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 1, test, tab, rel);
     else
         place_relation_kernel<16, 4><<<dim3((unsigned)frames, (unsigned)tiles), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 0, test, tab, rel);
     const int st = launch_status();
     if (st != NMS_OK) return st;
     begin_launch();
-#define NMS_LAUNCH_RESOLVE(R_) \
-    place_resolve_kernel<R_><<<dim3((unsigned)frames), dim3(kResolveWaves * 64), 0, stream>>>(counts, n_max, n_pad, tab.index, rel, keep_out)
-    if (tiles <= kResolveWaves) NMS_LAUNCH_RESOLVE(1);
-    else if (tiles <= 2 * kResolveWaves) NMS_LAUNCH_RESOLVE(2);
-    else if (tiles <= 4 * kResolveWaves) NMS_LAUNCH_RESOLVE(4);
-    else NMS_LAUNCH_RESOLVE(8);
+#define NMS_LAUNCH_RESOLVE(R_, AUX_, WALK_)                                                                             \
+    place_resolve_kernel<R_, AUX_, WALK_><<<dim3((unsigned)frames), dim3(kResolveWaves * 64), 0, stream>>>(             \
+        boxes, scores, counts, n_max, n_pad, test, tab, rel, keep_out)
+    if (n_max > kChunk) NMS_LAUNCH_RESOLVE(8, false, false);
+    else if (test.classes != nullptr || test.ties_ignore) NMS_LAUNCH_RESOLVE(4, true, true);
+    else NMS_LAUNCH_RESOLVE(4, false, true);
 #undef NMS_LAUNCH_RESOLVE
     return launch_status();
 }
@@ -550,28 +552,28 @@ static PlaceTable place_table(const RunWorkspace &w, int n_pad, int frames, int3
     return t;
 }
 
-// The greedy rule under IoU in order of place: table, relation, resolve.  Frames of 256 (kRelationWords tiles) to 2 * NMS_SORT_CHUNK boxes; words: the
-// mask's place, n_pad / 64 words per row.  The table as above, but the summary takes ysc (8 or 16 bytes per row), the tiles of the first
-// masks and the hulls what is left of it, or the place of the sort keys that frames beyond NMS_SORT_CHUNK boxes have.
+// The greedy rule under IoU in order of place: table, relation, resolve; frames of 2049 to 2 * NMS_SORT_CHUNK boxes.  The masks lie in
+// the mask's place, the tiles of a row's masks in ysc's, the counts of crowded rows and of what is left open in ytile's, the
+// tiles' hulls in that of the ranked scores (ranked).  left: beyond NMS_SORT_CHUNK boxes the counts of the frames that are still to be done, 0 for the others.
 static int place_greedy_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
-                               const PlaceTest &test, uint8_t *keep_out, void *workspace, int32_t *label, unsigned long long *words,
-                               hipStream_t stream)
+                               const PlaceTest &test, uint8_t *keep_out, void *workspace, int32_t *label, unsigned long long *words, float *ranked,
+                               const int32_t **left, hipStream_t stream)
 {
     const int n_pad = nms_padded_n(n_max);
     const size_t rows = (size_t)frames * n_pad;
     const RunWorkspace w = carve_workspace(workspace, n_max, frames);
     PlaceTable tab = place_table(w, n_pad, frames, label);
-    PlaceRelation rel;
-    rel.S = (n_pad / kTile + 63) / 64;
-    rel.summary = reinterpret_cast<unsigned long long *>(w.ysc);
-    rel.at = rel.S == 1 ? reinterpret_cast<unsigned *>(rel.summary + rows) : reinterpret_cast<unsigned *>(w.keys);
-    rel.first = words;
-    rel.further = words + rows * kRelationWords;
-    tab.hull = reinterpret_cast<float4 *>(rel.at + rows);  // (rows is a multiple of 64)
+    tab.hull = reinterpret_cast<float4 *>(ranked);
     tab.tile = reinterpret_cast<uint2 *>(tab.hull + rows / kTile);
-    const int st = place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
+    PlaceRelation rel;
+    rel.words = words;
+    rel.at = reinterpret_cast<uint4 *>(w.ysc);
+    rel.crowded = w.ytile;
+    rel.left = reinterpret_cast<int32_t *>(w.ytile + frames);
+    *left = rel.left;
+    const int st = place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, rel.crowded, keep_out, stream);
     if (st != NMS_OK) return st;
-    return place_relation_launch(counts, n_max, frames, test, tab, rel, keep_out, stream);
+    return place_relation_launch(boxes, scores, counts, n_max, frames, test, tab, rel, keep_out, stream);
 }
 
 // The paper's rule on long frames: table, scan.
@@ -580,8 +582,8 @@ static int place_paper_launch(bool iou, const float *boxes, const float *scores,
 {
     const RunWorkspace w = carve_workspace(workspace, n_max, frames);
     const PlaceTable tab = place_table(w, nms_padded_n(n_max), frames, label);
-    const int st = iou ? place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream)
-                       : place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, keep_out, stream);
+    const int st = iou ? place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream)
+                       : place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream);
     if (st != NMS_OK) return st;
     return iou ? place_scan_launch<true>(counts, n_max, frames, test, tab, keep_out, stream)
                : place_scan_launch<false>(counts, n_max, frames, test, tab, keep_out, stream);
@@ -683,24 +685,19 @@ int nms_run_direct_batched(const float *boxes, const float *scores, const int32_
                       nullptr);
 }
 
-int nms_reduce_greedy_batched(const uint64_t *mask, const int32_t *order, const int32_t *counts, int n_max,
-                              int frames, uint8_t *keep_out, void *stream)
+// fill: keep_out entries at or beyond a frame's count are written 0
+static int greedy_sweep_launch(const unsigned long long *m, const int32_t *order, const int32_t *counts, int n_max, int frames, int fill,
+                               uint8_t *keep_out, hipStream_t s)
 {
-    int st;
-    if (!sizes_ok(n_max, frames, &st)) return st;
-    if (n_max == 0 || frames == 0) return NMS_OK;
-    if (!mask || !order || !keep_out) return NMS_ERR_INVALID_ARG;
     const int n_pad = nms_padded_n(n_max);
     const int T = n_pad / kTile;
-    const unsigned long long *m = reinterpret_cast<const unsigned long long *>(mask);
-    hipStream_t s = static_cast<hipStream_t>(stream);
     for (int t0 = 0; t0 < T; t0 += kSweepTiles) {
         begin_launch();
         if (t0 == 0)
-            greedy_sweep_kernel<true><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
+            greedy_sweep_kernel<true><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, fill, keep_out);
         else
-            greedy_sweep_kernel<false><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, keep_out);
-        st = launch_status();
+            greedy_sweep_kernel<false><<<dim3(frames), dim3(kSweepWaves * 64), 0, s>>>(m, order, counts, n_max, n_pad, t0, fill, keep_out);
+        int st = launch_status();
         if (st != NMS_OK) return st;
         const int later = T - (t0 + kSweepTiles);  // tile rows after this block
         if (later <= 0) break;
@@ -714,6 +711,17 @@ int nms_reduce_greedy_batched(const uint64_t *mask, const int32_t *order, const 
         if (st != NMS_OK) return st;
     }
     return NMS_OK;
+}
+
+int nms_reduce_greedy_batched(const uint64_t *mask, const int32_t *order, const int32_t *counts, int n_max,
+                              int frames, uint8_t *keep_out, void *stream)
+{
+    int st;
+    if (!sizes_ok(n_max, frames, &st)) return st;
+    if (n_max == 0 || frames == 0) return NMS_OK;
+    if (!mask || !order || !keep_out) return NMS_ERR_INVALID_ARG;
+    return greedy_sweep_launch(reinterpret_cast<const unsigned long long *>(mask), order, counts, n_max, frames, 1, keep_out,
+                               static_cast<hipStream_t>(stream));
 }
 
 int nms_reduce_greedy(const uint64_t *mask, const int32_t *order, int n, uint8_t *keep_out, void *stream)
@@ -922,6 +930,7 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     const int mode = !divide ? kExBoundary : (opt.compare == NMS_COMPARE_GT ? kExDivideGt : kExDivideGe);
     const bool iou = opt.measure == NMS_MEASURE_IOU;
     const bool aux = flags != 0;
+    int fill = 1;
     if (opt.rule == NMS_RULE_GREEDY && n_max <= kGreedySmallBoxes) {
         const NmsThetaConst th = nms_make_theta_const(threshold);
         const FusedVariant v = {nullptr, nullptr, boundary, opt.pixel_offset, flags};
@@ -937,7 +946,11 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     }
     if (opt.rule == NMS_RULE_GREEDY && !divide && iou && nms_use_place_greedy(n_max, frames, kChunk, kGreedyFusedBoxes)) {
         const PlaceTest test = {boundary, opt.pixel_offset, opt.ties == NMS_TIES_IGNORE ? 1 : 0, opt.classes};
-        return place_greedy_launch(boxes, scores, counts, n_max, frames, test, keep_out, workspace, ranked_class, mask, s);
+        const int32_t *left = nullptr;
+        st = place_greedy_launch(boxes, scores, counts, n_max, frames, test, keep_out, workspace, ranked_class, mask, ranked_score, &left, s);
+        if (st != NMS_OK || n_max <= kChunk) return st;
+        counts = left;  // what follows is for the frames that are left; the others have no boxes any more
+        fill = 0;
     }
     if (opt.rule == NMS_RULE_PAPER && !divide && (iou || opt.pixel_offset == 1.0f) &&
         nms_use_spatial_variant(n_max, frames, opt.classes != nullptr)) {
@@ -1056,8 +1069,7 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
     st = launch_status();
     if (st != NMS_OK) return st;
     if (fold) return NMS_OK;
-    return nms_reduce_greedy_batched(reinterpret_cast<const uint64_t *>(mask), w.order, counts, n_max, frames,
-                                     keep_out, stream);
+    return greedy_sweep_launch(mask, w.order, counts, n_max, frames, fill, keep_out, s);
 }
 
 int nms_map_matrix(const float *boxes, const float *scores, int n, int capacity, float threshold,

@@ -54,13 +54,19 @@ NMS_HD void nms_place_hull_add(B &h, float &least, const B &v, float T, bool the
     least = fminf(least, odd ? -INFINITY : (there ? T : INFINITY));
 }
 
-// Can tile t, one of `tiles`, hold a box that is ranked before the victim and eliminates it?  hull, tile_T, best: the tile's (of a t
-// that is no tile: anything); best, v_upper: upper halves of rank keys.  Whether t is a tile at all is asked by itself: an
-// intersection with an infinite box, or one whose area overflows, reaches every T.
+// Can a tile hold a box that is ranked before the victim and eliminates it?  hull, tile_T, best: the tile's; best, v_upper: upper
+// halves of rank keys.
 template <bool IOU, class B>
-NMS_HD bool nms_place_reaches(int t, int tiles, const B &v, float v_T, uint32_t v_upper, const B &hull, float tile_T, uint32_t best, float off)
+NMS_HD bool nms_place_reaches(const B &v, float v_T, uint32_t v_upper, const B &hull, float tile_T, uint32_t best, float off)
 {
     const float inter = nms_place_inter(v, hull, off);
     const float least = IOU ? (tile_T < 0.0f ? tile_T : fmaxf(tile_T, v_T)) : tile_T;
-    return (t < tiles) & (inter >= least) & (best <= v_upper);
+    return (inter >= least) & (best <= v_upper);
+}
+
+// Which of the 64 lanes stand for a tile when they look at the tiles first, first + 1, .. (first < tiles).  No T can say that: an
+// intersection with an infinite box, or one whose area overflows, reaches infinity too.
+NMS_HD unsigned long long nms_place_tile_lanes(int first, int tiles)
+{
+    return tiles - first >= 64 ? ~0ull : (1ull << (tiles - first)) - 1ull;
 }

@@ -96,6 +96,28 @@ int main(int argc, char **argv)
         while (scanf("%d %d", &n, &frames) == 2) printf("%d %d\n", nms_class_bin_limit(n), nms_class_waves(n, frames));
         return 0;
     }
+    if (!strcmp(argv[1], "relation")) {
+        // every batch that the greedy rule takes in order of place: what it keeps fits the parts of the workspace that it takes (the masks' place,
+        // ysc for the tiles of the masks, ytile for two counts per frame, the ranked scores for the tiles' hulls), tiles fit seven bits
+        long long taken = 0, bad = 0;
+        for (int n_max = 1; n_max <= 9000; ++n_max) {
+            for (int frames : {1, 2, 7, 31, 64, 1000, 65535}) {
+                if (!nms_use_place_greedy(n_max, frames, 4096, 32ll * 4096)) continue;
+                ++taken;
+                const int n_pad = (n_max + 63) / 64 * 64, T = n_pad / 64;
+                const NmsRelationBlock b = nms_relation_block(n_pad);
+                const bool rows_fit = n_max > 4096 || b.end <= (size_t)T * n_pad;  // (the walk takes frames of one chunk)
+                const bool masks_fit = b.more == 4u * n_pad && b.ranked == b.more + 12u * n_pad && b.ranked <= (size_t)T * n_pad && b.ranked % 2 == 0;
+                const bool ok = n_max > 2048 && n_max <= 8192 && rows_fit && masks_fit && (16 + 8) * T <= 4 * n_pad && 2 <= T && T <= 128;
+                if (!ok) {
+                    if (!bad) printf("first_bad %d %d\n", n_max, frames);
+                    ++bad;
+                }
+            }
+        }
+        printf("taken %lld bad %lld\n", taken, bad);
+        return 0;
+    }
     if (!strcmp(argv[1], "layout")) {
         int n_max, frames, chunk;
         while (scanf("%d %d %d", &n_max, &frames, &chunk) == 3) {

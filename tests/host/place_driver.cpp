@@ -67,8 +67,9 @@ static void reach(std::mt19937 &rng, long &words, long &outside)
                 for (int lane = 0; lane < kTile; ++lane) {
                     const int t = s + lane;
                     const Tile &c = tile[t < tiles ? t : tiles - 1];
-                    if (nms_place_reaches<IOU>(t, tiles, box[v], T[v], upper[v], c.hull, c.T, c.best, off)) word |= 1ull << lane;
+                    if (nms_place_reaches<IOU>(box[v], T[v], upper[v], c.hull, c.T, c.best, off)) word |= 1ull << lane;
                 }
+                word &= nms_place_tile_lanes(s, tiles);
                 ++words;
                 if (tiles - s < kTile && (word >> (tiles - s)) != 0) ++outside;
             }

@@ -120,6 +120,13 @@ def test_workspace_layout_matches_the_size_helper(driver):
         assert end - stage == (0 if n <= 4096 else -(-(f * (n_pad // 64) * 32 * 8) // 256) * 256)
 
 
+def test_relation_of_the_greedy_rule_fits_the_workspace(driver):
+    """Every batch that takes the greedy rule in order of place: masks, ranked rows, tiles and counts lie inside the parts they borrow."""
+    out = run(driver, "relation").strip().split("\n")
+    taken, bad = int(out[-1].split()[1]), int(out[-1].split()[3])
+    assert bad == 0 and taken > 20000, out
+
+
 def real_key(score, index):
     s = float(score)
     if s == float("inf"):
