@@ -265,13 +265,16 @@ int spatial_frames_launch(const float *boxes, const float *scores, const int32_t
 #define NMS_LAUNCH_PLACE(W_, E_, AXIS_)                                                                                \
     spatial_frames_kernel<W_, E_, AXIS_, IOU, LABELS><<<grid, dim3(W_ * 64), 0, stream>>>(                     \
         boxes, scores, counts, n_max, nms_spatial_frames_split(n_max, parts, W_), test, keep_out)
-    if constexpr (LABELS) {  // short frames come here with labels only; the bins of labels want the finer grid beyond 1024 boxes
-        if (n_max <= 256) NMS_LAUNCH_PLACE(4, 1, 8);
-        else if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+    // Sixteen wavefronts also for frames that fewer would hold, while every frame has a compute unit: the second stage is four victims per
+    // wavefront at a time.  us, four / eight / sixteen wavefronts, 20 labels, sparse anchors, then clustered: 1 x 64 11.8 / 8.2 / 7.3, 10.4 / 7.9 / 7.0; 46 x 256
+    // 12.8 / 9.2 / 8.2, 12.8 / 9.3 / 8.2; 187 x 64 12.1 / - / 7.8; more frames 400 x 30 8.8 / - / 12.1, 1000 x 12 7.5 / - / 20.  Without labels, eight / sixteen: 12 x 500
+    // 10.7 / 9.7.  The bins of labels want the finer grid beyond 1024 boxes.
+    if constexpr (LABELS) {
+        if (n_max <= 256 && frames > 256) NMS_LAUNCH_PLACE(4, 1, 8);
         else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
         else NMS_LAUNCH_PLACE(16, 4, 32);
     } else {
-        if (n_max <= 512) NMS_LAUNCH_PLACE(8, 1, 16);
+        if (n_max <= 512 && frames > 256) NMS_LAUNCH_PLACE(8, 1, 16);
         else if (n_max <= 1024) NMS_LAUNCH_PLACE(16, 1, 16);
         else if (n_max <= 2048) NMS_LAUNCH_PLACE(16, 2, 16);
         else NMS_LAUNCH_PLACE(16, 4, 32);
