@@ -245,7 +245,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
     unsigned cell[E], within[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) {
-        cell[q] = LABELS ? (unsigned)(label[q] & (kPlaceBins - 1)) * (unsigned)(A * A) + place_spot<A>(b[q], grid) : place_cell<A>(b[q], grid);
+        cell[q] = LABELS ? nms_place_bin(label[q]) * (unsigned)(A * A) + place_spot<A>(b[q], grid) : place_cell<A>(b[q], grid);
         within[q] = 0;
         if (q * kThreads + tid < n_f) {
             within[q] = atomicAdd(&sh.start[cell[q]], 1u);
@@ -282,7 +282,7 @@ spatial_frames_kernel(const float *__restrict__ boxes, const float *__restrict__
             sh.upper[row] = upper[q];
             sh.meta[row] = (unsigned)e | (cell[q] << 16) | (LABELS ? (unsigned)(label[q] & 0xf0) << 24 : 0u);
             atomicMin(&sh.best[A + 1 + cell[q]], (upper[q] & ~4095u) | row);
-            if (LABELS) atomicOr(&sh.bins[row / kTile], 1u << (label[q] & (kPlaceBins - 1)));
+            if (LABELS) atomicOr(&sh.bins[row / kTile], 1u << nms_place_bin(label[q]));
             if (parts > 1) sh.row[e] = (uint16_t)row;
         }
     }

@@ -2,6 +2,7 @@
 //   place_driver reach        frames of 1 to 128 tiles with boxes of every size, infinite ones and such whose area overflows among them:
 //                             reach words as the kernels form them (64 lanes at a time, lanes behind the last tile read the last one);
 //                             prints "words <n> outside <n>": bits of lanes that are no tile
+//   place_driver bins         labels -8 .. 511 and their bins
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -85,6 +86,10 @@ int main(int argc, char **argv)
         reach<false>(rng, words, outside);
         reach<true>(rng, words, outside);
         std::printf("words %ld outside %ld\n", words, outside);
+        return 0;
+    }
+    if (argc > 1 && std::strcmp(argv[1], "bins") == 0) {
+        for (int label = -8; label < 512; ++label) std::printf("%d %u\n", label, nms_place_bin(label));
         return 0;
     }
     return 2;

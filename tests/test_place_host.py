@@ -20,3 +20,14 @@ def test_no_tile_behind_the_last_is_reached(driver):
     have to be left out by their number (rows behind the table, and words behind a row's place, were read and written)."""
     out = subprocess.run([driver, "reach"], capture_output=True, text=True, check=True).stdout.split()
     assert int(out[1]) > 100000 and int(out[3]) == 0, out
+
+
+def test_labels_are_told_apart_and_spread(driver):
+    """Bin and bits 4 to 7 name a label from 0 to 255; sixteen labels in steps of 1, 16 or 17 take more than half of the bins
+    between them where the steps allow it (one bin for all is a grid without classes)."""
+    out = subprocess.run([driver, "bins"], capture_output=True, text=True, check=True).stdout.split("\n")
+    bins = {int(a): int(b) for a, b in (line.split() for line in out if line)}
+    assert all(0 <= b < 16 for b in bins.values())
+    assert len({(bins[n], n & 0xf0) for n in range(256)}) == 256
+    assert len({bins[n] for n in range(16)}) == 16 and len({bins[16 * n] for n in range(16)}) == 16
+    assert len({bins[20 * n] for n in range(16)}) > 8
