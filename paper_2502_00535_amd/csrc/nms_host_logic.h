@@ -257,16 +257,18 @@ NMS_HD bool nms_use_small_frames(int n_max, int frames)
 // Frames of up to 4096 boxes, for thresholds with a division-free form, whatever nms_route_for names for the
 // rest.  Its tables cost some 7 us whatever the batch; the line is where it passes the direct form and the
 // sort-free kernels on clustered detections (much eliminated) and on sparse anchors (little eliminated).  Whole
-// call, us, place / before: 16 x 1024 7.5 / 7.0 and 8.8 / 9.3, 32 x 1024 7.7 / 8.3 and 11.5 / 13.8, 64 x 600 8.0 / 9.9 and
-// 11.7 / 16.5, 16 x 600 6.8 / 5.9; 4 x 1300 8.5 / 7.0, 8 x 1300 7.8 / 9.6 and 9.1 / 9.6, 4 x 2048 8.4 / 9.6, 8 x 2048 8.5 / 9.1;
-// 1 x 4096 10.2 / 8.9, 2 x 4096 11.0 / 14.5, 2 x 3000 10.5 / 12.5.  Shorter frames gain on clustered detections only
-// (1000 x 300 14 / 34, but anchors 35 / 34) until there are many of some 500 boxes (512 x 512 13 / 19 and 35 / 41).
+// call, us, place / before: 28 x 1000 7.4 / 8.0 and 10.2 / 12.8, 31 x 900 (before) 8.2 and 12.7, 44 x 640 7.0 / 10.2 and 9.9 / 16.0, 16 x 1024
+// 7.5 / 7.0, 16 x 600 6.8 / 5.9; 8 x 1025 7.5 / 7.4 and 9.1 / 7.4, 9 x 1025 7.5 / 8.7 and 9.0 / 8.6, 6 x 1350 7.4 / 7.3 and 8.7 / 7.3, 7 x 1350
+// 7.5 / 9.6 and 8.7 / 9.6, 5 x 1600 7.7 / 8.2 and 9.3 / 8.2, 5 x 1650 7.7 / 10.6 and 8.9 / 10.6, 4 x 2048 8.1 / 9.5 and 9.1 / 9.6; 2 x 2049
+// 9.2 / 6.8 and 10.3 / 6.8, 2 x 2240 9.2 / 9.3 and 9.9 / 9.3, 2 x 2300 9.3 / 10.9 and 10.2 / 11.0, 3 x 2176 9.4 / 9.6 and 10.2 / 9.6, 4 x 2049 9.4 / 10.8 and
+// 10.2 / 10.7; 1 x 4096 10.2 / 8.9, 2 x 4096 11.0 / 14.5.  Shorter frames gain on clustered detections only
+// (1000 x 300 14 / 34, but anchors 35 / 34) until there are many of some 500 boxes (512 x 512 11.3 / 18.7 and 32 / 41).
 NMS_HD bool nms_use_spatial_frames(int n_max, int frames, int sort_chunk)
 {
     const long long total = (long long)frames * n_max;
     if (n_max > sort_chunk) return false;
-    if (n_max > 2048) return frames >= 2;
-    if (n_max > 1024) return total >= 8000;
+    if (n_max > 2048) return frames >= (n_max >= 2300 ? 2 : 4);
+    if (n_max > 1024) return total >= (n_max >= 1640 ? 8000 : 9000);
     if (n_max > 512) return total >= 28000;
     return n_max > 448 && frames >= 512;
 }
@@ -287,14 +289,17 @@ NMS_HD int nms_spatial_frames_split(int n_max, int parts, int W)
 }
 
 // The same for the paper's rule with IoU, labels, a strict compare or ignored ties, against rank and map step.  Whole call, us, place / before,
-// sparse anchors, then clustered with 20 labels: 1 x 1000 9.4 / 11.4, 9.0 / 15.5; 60 x 1000 19.0 / 23.7, 17.5 / 30.3; 200 x 700 35 / 29, 28 / 39;
-// 100 x 2000 59 / 74, 46 / 104; 20 x 4096 31 / 71, 26 / 94; 10 x 500 10.4 / 10.6, 10.0 / 13.4; 60 x 300 13.4 / 11.5, 12.0 / 14.4;
-// 60 x 200 13.2 / 12.6, 12.9 / 15.2.  Longer frames: 5 x 7000 crowd 19 / 60.
-NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool labelled)
+// sparse anchors, then clustered.  IoU without labels: 1 x 600 9.3 / 11.6, 7.3 / 14.4; 8 x 500 9.7 / 10.5, 7.4 / 13.5; 60 x 1000 19.6 / 23.9, 9.3 / 28.9; 80 x 1000 24.4 / 25.8,
+// 10.3 / 32; 100 x 520 19.4 / 20.9, 9.1 / 23.4; 95 x 800 27 / 24.8, 10.8 / 30; 97 x 1024 31.9 / 28.2, 12 / 35; 130 x 520 28.5 / 22.3, 10.7 / 27: what is left of a frame that little is
+// eliminated from is one compute unit's work, of two frames of three beyond 85 frames.  Longer frames keep it although such batches lose: 100 x 1500 45 / 49, 16 / 60;
+// 20 x 4096 28 / 71; 200 x 1025 49 / 50, 16.5 / 61, but 150 x 1100 53 / 44, 18 / 54 and 300 x 1100 100 / 82, 30 / 110.  20 labels: 1 x 64 7.3 / 8.8, 7.0 / 11.8; 46 x 256 8.2 / 11.5, 8.2 / 13.6;
+// 97 x 1024 30.8 / 33.9, 27 / 38; 100 x 2000 60 / 95, 46 / 102; one label 46 x 256 8.6 / 12.3, 7.0 / 16.5, 20 x 4096 60 / 94, 21 / 106; labels beyond 255, which are looked up in memory where
+// boxes hit, 60 x 1000 22 / 28, 20 x 4096 36 / 88.  Strict compare: 8 x 500 8.0 / 8.7, 97 x 1024 19.8 / 26.7.  Longer frames: 5 x 7000 crowd 19 / 60.
+NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool iou, bool labelled)
 {
     const long long total = (long long)frames * n_max;
     if (n_max > 1024) return true;
-    if (n_max > 512) return total <= 100000;
+    if (n_max > 512) return total <= (!iou || labelled ? 100000 : (frames <= 85 ? 87040 : 70000)) && (!iou || labelled || frames <= 128);
     if (n_max > 256) return total <= 6000;
     return labelled && total <= 12000;
 }

@@ -956,7 +956,7 @@ int nms_run_ex_batched(const float *boxes, const float *scores, const int32_t *c
         fill = 0;
     }
     if (opt.rule == NMS_RULE_PAPER && !divide && (iou || opt.pixel_offset == 1.0f) &&
-        nms_use_spatial_variant(n_max, frames, opt.classes != nullptr)) {
+        nms_use_spatial_variant(n_max, frames, iou, opt.classes != nullptr)) {
         const PlaceTest test = {boundary, opt.pixel_offset, opt.ties == NMS_TIES_IGNORE ? 1 : 0, opt.classes};
         if (n_max > kChunk) return place_paper_launch(iou, boxes, scores, counts, n_max, frames, test, keep_out, workspace, ranked_class, s);
         if (iou)

@@ -96,6 +96,41 @@ int main(int argc, char **argv)
         while (scanf("%d %d", &n, &frames) == 2) printf("%d %d\n", nms_class_bin_limit(n), nms_class_waves(n, frames));
         return 0;
     }
+    if (!strcmp(argv[1], "place")) {
+        // whether a batch is put in order of place, for every "n_max frames" on stdin: default call; IoU; IoU with labels; strict compare
+        int n, frames;
+        while (scanf("%d %d", &n, &frames) == 2)
+            printf("%d %d %d %d\n", nms_use_spatial_frames(n, frames, 4096), nms_use_spatial_variant(n, frames, true, false),
+                   nms_use_spatial_variant(n, frames, true, true), nms_use_spatial_variant(n, frames, false, false));
+        return 0;
+    }
+    if (!strcmp(argv[1], "place_shapes")) {
+        // every batch shape of the kernels in order of place: workgroups per frame, wavefronts per tile in the first stage, places per workgroup
+        long long seen = 0, bad = 0;
+        for (int n_max = 1; n_max <= 65536; n_max += n_max < 4200 ? 1 : 61) {
+            for (int frames = 1; frames <= 65535; frames = frames < 300 ? frames + 1 : frames * 3 / 2 + 1) {
+                ++seen;
+                const int tiles = (n_max + 63) / 64;
+                bool ok = true;
+                if (n_max <= 4096) {
+                    const int parts = nms_spatial_frames_parts(n_max, frames);
+                    ok = parts >= 1 && parts <= tiles && ((long long)frames * parts <= 256 || parts == 1);
+                    for (int W : {4, 8, 16}) {
+                        const int split = nms_spatial_frames_split(n_max, parts, W), share = (tiles + parts - 1) / parts;
+                        ok = ok && split >= 0 && split <= 2 && (split == 0 || (share << split) <= W);  // a wavefront has one tile then
+                    }
+                }
+                const int share = nms_place_share(n_max, frames);
+                ok = ok && share % 64 == 0 && share >= 64 && share <= 1024 && (n_max + share - 1) / share <= 65535;
+                if (!ok) {
+                    if (!bad) printf("first_bad %d %d\n", n_max, frames);
+                    ++bad;
+                }
+            }
+        }
+        printf("seen %lld bad %lld\n", seen, bad);
+        return 0;
+    }
     if (!strcmp(argv[1], "relation")) {
         // every batch that the greedy rule takes in order of place: what it keeps fits the parts of the workspace that it takes (the masks' place,
         // ysc for the tiles of the masks, ytile for two counts per frame, the ranked scores for the tiles' hulls), tiles fit seven bits

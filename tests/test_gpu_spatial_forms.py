@@ -27,6 +27,17 @@ def test_short_frames(nms, oracle, frames, n):
             check(nms, oracle, data, 0.45, dict(rule="paper", measure=measure, compare="gt", ties="index", pixel_offset=1.0, labelled=labelled))
 
 
+@pytest.mark.parametrize("frames,n", [(2, 2300), (2, 4096), (4, 2049), (9, 1025), (6, 1640), (7, 1350)])
+def test_shapes_at_the_lines(nms, oracle, frames, n):
+    """The smallest batches of frames of their length that are put in order of place (up to 64 workgroups per frame)."""
+    from test_gpu_spatial_frames import check as check_default
+
+    print(f"case {frames} x {n}", flush=True)
+    boxes, scores, _, counts = batch(n, frames, n)
+    check_default(nms, oracle, boxes, scores, 0.45)
+    check_default(nms, oracle, boxes, scores, 0.3, counts)
+
+
 @pytest.mark.parametrize("frames,n", [(3, 250), (3, 1000), (3, 2500)])
 def test_labels_by_their_bits(nms, oracle, frames, n):
     """The bin of a label comes from eight bits of it: labels equal in four of them, in all eight, and with the sign bit."""

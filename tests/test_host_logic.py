@@ -120,6 +120,28 @@ def test_workspace_layout_matches_the_size_helper(driver):
         assert end - stage == (0 if n <= 4096 else -(-(f * (n_pad // 64) * 32 * 8) // 256) * 256)
 
 
+def test_place_routes_where_they_are_quicker(driver):
+    """The quicker kernels at shapes either side of the lines (clustered detections and sparse anchors both, by 3 % or more on one of them)."""
+    quicker = [  # (default call, IoU, IoU with labels, strict compare; None: not measured)
+        ((1, None, None, None), [(1025, 12), (1025, 16), (1150, 8), (1350, 7), (1600, 6), (1650, 5), (2048, 4), (1900, 5), (2300, 2), (2600, 2), (3000, 2), (2300, 3), (2049, 4),
+                                 (4096, 2), (1000, 28), (640, 44), (520, 54), (512, 512)]),
+        ((0, None, None, None), [(1025, 8), (1350, 6), (1600, 5), (2049, 2), (2100, 2), (2240, 2), (2049, 3), (2176, 3), (1024, 16), (600, 16), (4096, 1), (300, 1000)]),
+        ((None, 1, 1, 1), [(600, 1), (500, 8), (1000, 60), (1000, 80), (800, 75), (520, 100), (1025, 97), (1500, 100), (2048, 200), (4096, 20)]),
+        ((None, 0, 1, 1), [(1024, 97), (800, 95), (1000, 90), (520, 130), (520, 160), (600, 130)]),
+        ((None, 0, 1, 0), [(64, 1), (256, 46), (12, 1000), (100, 100)])]
+    shapes = [shape for _, some in quicker for shape in some]
+    got = [tuple(map(int, line.split())) for line in run(driver, "place", stdin="\n".join(f"{n} {f}" for n, f in shapes)).strip().split("\n")]
+    want = [row for row, some in quicker for _ in some]
+    assert [(shape, tuple(w if w is None else g for g, w in zip(row, wanted))) for shape, row, wanted in zip(shapes, got, want)] == list(zip(shapes, want))
+
+
+def test_shares_of_the_kernels_in_order_of_place_fit(driver):
+    """Every batch shape: a wavefront of the first stage has one tile where several share one, a workgroup's places fit its LDS."""
+    out = run(driver, "place_shapes").strip().split("\n")
+    seen, bad = int(out[-1].split()[1]), int(out[-1].split()[3])
+    assert bad == 0 and seen > 1000000, out
+
+
 def test_relation_of_the_greedy_rule_fits_the_workspace(driver):
     """Every batch that takes the greedy rule in order of place: masks, ranked rows, tiles and counts lie inside the parts they borrow."""
     out = run(driver, "relation").strip().split("\n")
