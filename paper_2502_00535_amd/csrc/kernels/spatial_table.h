@@ -39,8 +39,8 @@ struct PlaceSortShared {
 // them) and writes the places [lo, lo + share) of the table, share a multiple of 64.  Cells, their first places and the order
 // inside the two cells that a share may cut depend on the input alone (numbered by wavefront, chunk, register, lane), so the
 // workgroups agree without exchanging anything.  E: boxes per thread and chunk of 1024 E; MULTI: several chunks, read again in
-// each pass.
-template <int E, bool MULTI, bool IOU>
+// each pass.  GREEDY: for the relation launch.
+template <int E, bool MULTI, bool IOU, bool GREEDY>
 __global__ void __launch_bounds__(kSortThreads)
 place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ scores, const int32_t *__restrict__ counts,
                   int n_max, int n_pad, int share, PlaceTest test, PlaceTable tab, unsigned *__restrict__ crowded, uint8_t *__restrict__ keep_out)
@@ -82,6 +82,9 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
         sh.start[i * kSortThreads + tid] = 0u;
     }
     if (tid == 0) sh.start[kSortCells] = ~0u;
+    // (coordinates that are not finite: a box counted under one cell and placed under another would leave a place unwritten)
+    static_assert(kSortShare == kSortThreads, "a place per thread");
+    sh.index[tid] = 0u;
     lds_barrier();
     PlaceGrid grid;
     {
@@ -207,9 +210,7 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
     const int rows = (hi - lo + kTile - 1) / kTile * kTile;         // with the last tile's empty rows
     if (i < rows) {  // whole wavefronts
         const bool there = i < hi - lo;
-        // (coordinates that are not finite: a box counted under one cell and placed under another would leave a place unwritten)
-        const unsigned written = sh.index[i], last = there ? (unsigned)(n_f - 1) : 0u;
-        const unsigned e = written < last ? written : last;
+        const unsigned e = there ? sh.index[i] : 0u;
         const float score = score_f[e];
         const float4 v = there ? sh.box[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float area = ((v.z - v.x) + test.offset) * ((v.w - v.y) + test.offset);
@@ -237,7 +238,7 @@ place_sort_kernel(const float *__restrict__ boxes, const float *__restrict__ sco
             const size_t t = (size_t)f * (n_pad / kTile) + (lo + i) / kTile;
             tab.hull[t] = make_float4(hx, hy, -hz, -hw);
             tab.tile[t] = make_uint2(__float_as_uint(least), best);
-            if (crowded != nullptr && lo + i == 0) crowded[f] = 0u;  // (for the relation launch)
+            if (GREEDY && lo + i == 0) crowded[f] = 0u;  // (for the relation launch; where it is not wanted even the branch costs 2 %)
         }
     }
 }

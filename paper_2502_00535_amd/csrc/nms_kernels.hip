@@ -216,7 +216,7 @@ int map_launch(const float *sorted5, const int32_t *counts, int n_max, int frame
     return launch_status();
 }
 
-template <bool IOU>
+template <bool IOU, bool GREEDY>
 int place_sort_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
                       const PlaceTest &test, const PlaceTable &tab, unsigned *crowded, uint8_t *keep_out, hipStream_t stream)
 {
@@ -225,16 +225,15 @@ int place_sort_launch(const float *boxes, const float *scores, const int32_t *co
     const dim3 grid((unsigned)frames, (unsigned)((n_max + share - 1) / share)), block(kSortThreads);
     begin_launch();
 #define NMS_LAUNCH_SORT(E_, MULTI_)                                                                                     \
-    place_sort_kernel<E_, MULTI_, IOU><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, crowded, keep_out)
-    if constexpr (IOU) {  // frames of up to 4096 boxes come here under the greedy rule only
-        if (n_max <= 4 * kSortThreads) {
-            NMS_LAUNCH_SORT(4, false);
-            return launch_status();
-        }
+    place_sort_kernel<E_, MULTI_, IOU, GREEDY><<<grid, block, 0, stream>>>(boxes, scores, counts, n_max, n_pad, share, test, tab, crowded, keep_out)
+    if constexpr (GREEDY) {  // frames of 2049 to 8192 boxes
+        if (n_max <= 4 * kSortThreads) NMS_LAUNCH_SORT(4, false);
+        else NMS_LAUNCH_SORT(8, false);
+    } else {
+        if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
+        else if (n_max <= 16 * kSortThreads) NMS_LAUNCH_SORT(16, false);
+        else NMS_LAUNCH_SORT(16, true);
     }
-    if (n_max <= 8 * kSortThreads) NMS_LAUNCH_SORT(8, false);
-    else if (n_max <= 16 * kSortThreads) NMS_LAUNCH_SORT(16, false);
-    else NMS_LAUNCH_SORT(16, true);
 #undef NMS_LAUNCH_SORT
     return launch_status();
 }
@@ -574,7 +573,7 @@ static int place_greedy_launch(const float *boxes, const float *scores, const in
     rel.crowded = w.ytile;
     rel.left = reinterpret_cast<int32_t *>(w.ytile + frames);
     *left = rel.left;
-    const int st = place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, rel.crowded, keep_out, stream);
+    const int st = place_sort_launch<true, true>(boxes, scores, counts, n_max, frames, test, tab, rel.crowded, keep_out, stream);
     if (st != NMS_OK) return st;
     return place_relation_launch(boxes, scores, counts, n_max, frames, test, tab, rel, keep_out, stream);
 }
@@ -585,8 +584,8 @@ static int place_paper_launch(bool iou, const float *boxes, const float *scores,
 {
     const RunWorkspace w = carve_workspace(workspace, n_max, frames);
     const PlaceTable tab = place_table(w, nms_padded_n(n_max), frames, label);
-    const int st = iou ? place_sort_launch<true>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream)
-                       : place_sort_launch<false>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream);
+    const int st = iou ? place_sort_launch<true, false>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream)
+                       : place_sort_launch<false, false>(boxes, scores, counts, n_max, frames, test, tab, nullptr, keep_out, stream);
     if (st != NMS_OK) return st;
     return iou ? place_scan_launch<true>(counts, n_max, frames, test, tab, keep_out, stream)
                : place_scan_launch<false>(counts, n_max, frames, test, tab, keep_out, stream);
