@@ -5,6 +5,7 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
+#include "../../include/nms.h"
 
 typedef int (*run_batched_fn)(const float *, const float *, const int32_t *, int, int, float, uint8_t *, void *, size_t, void *);
 
@@ -78,12 +79,12 @@ static PyObject *run(PyObject *self, PyObject *const *a, Py_ssize_t n)
         PyErr_SetString(PyExc_TypeError, "run takes ten arguments");
         return NULL;
     }
-    /* whole numbers and a float, as they are; sizes whose products the library would refuse are left to the other path */
+    /* whole numbers and a float, as they are; sizes that the library would refuse are left to the other path, so that no product overflows */
     if (!PyLong_CheckExact(a[4]) || !PyLong_CheckExact(a[5]) || !PyFloat_CheckExact(a[6]) || raw_stream == NULL) Py_RETURN_NONE;
     n_max = PyLong_AsLongLong(a[4]);
     frames = PyLong_AsLongLong(a[5]);
     threshold = PyFloat_AS_DOUBLE(a[6]);
-    if (PyErr_Occurred() || n_max < 0 || frames < 0 || n_max > 0x7fffffff || frames > 0x7fffffff) goto other;
+    if (PyErr_Occurred() || n_max < 0 || frames < 0 || n_max > NMS_MAX_N || frames > NMS_MAX_FRAMES) goto other;
     if (!address(a[1], dtype_f32, 4 * n_max * frames, &boxes) || !address(a[2], dtype_f32, n_max * frames, &scores) ||
         (a[3] != Py_None && !address(a[3], dtype_i32, frames, &counts)) || !address(a[7], dtype_u8, n_max * frames, &keep) ||
         !address(a[8], NULL, 0, &ws) || !as_i64(PyObject_GetAttr(a[8], n_nbytes), &bytes) || !stream_handle(a[9], &stream))

@@ -26,6 +26,49 @@ def test_what_is_not_in_order_is_named():
             call("boxes", *args[1:])
 
 
+class Claimed(torch.Tensor):
+    """A tensor that says of itself what the native path asks for (no GPU, nothing is read): `count` elements on one."""
+    count = 1
+    is_cuda = True
+
+    def numel(self):
+        return self.count
+
+
+def claimed(dtype, count):
+    t = torch.zeros(1, dtype=dtype).as_subclass(Claimed)
+    t.count = count
+    return t
+
+
+def test_sizes_are_bounded_before_they_are_multiplied():
+    """The boxes' element count is 4 n_max frames: near 2^31 each, that product passes 2^63 (it once wrapped to a negative number, which
+    no tensor is too small for).  Sizes the library refuses are left to the other path; what fits goes through."""
+    import ctypes
+
+    import paper_2502_00535_amd.binding as nms
+
+    calls = []
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 3, ctypes.c_int, ctypes.c_int, ctypes.c_float, *[ctypes.c_void_p] * 2,
+                             ctypes.c_size_t, ctypes.c_void_p)
+    fn = proto(lambda *a: calls.append(a[3:6]) or 0)
+    address = ctypes.cast(fn, ctypes.c_void_p).value
+
+    class Stream:
+        cuda_stream = 0
+
+    def run(n, f, boxes):
+        many = 2 ** 62 + 2 ** 61
+        return nms._marshal.run(address, claimed(torch.float32, boxes), claimed(torch.float32, many), None, n, f, 0.5,
+                                claimed(torch.uint8, many), claimed(torch.uint8, many), Stream())
+
+    assert run(8, 2, 64) == 0 and run(8, 2, 63) is None
+    assert run(65536, 65535, 4 * 65536 * 65535) == 0 and run(65536, 65535, 4 * 65536 * 65535 - 1) is None
+    for n, f in ((2 ** 31 - 1, 2 ** 31 - 1), (2 ** 31 - 1, 2 ** 30 + 1), (65537, 1), (1, 65536)):
+        assert run(n, f, 1) is None, (n, f)
+    assert [c[:2] for c in calls] == [(8, 2), (65536, 65535)]
+
+
 @pytest.mark.gpu
 def test_the_two_paths_agree():
     import paper_2502_00535_amd.binding as nms
