@@ -2,7 +2,8 @@
 "Work-Efficient Parallel Non-Maximum Suppression Kernels").
 
 The computation lives in ``libnms_mi355x.so`` (HIP, gfx950) behind the C ABI of
-``include/nms.h``; :mod:`paper_2502_00535_amd.binding` is a thin ctypes binding with
+``include/nms.h``; :mod:`paper_2502_00535_amd.binding` is a binding (ctypes, the whole-path
+calls through a small C module where that is built) with
 the same entry-point names that marshals torch tensors (device memory) and the
 current HIP stream.  There is no CPU fallback: touching any entry point without the
 built library raises ImportError.  ``python -m paper_2502_00535_amd.build`` compiles it.

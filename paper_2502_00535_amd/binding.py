@@ -216,9 +216,17 @@ def _stream(stream):
     return _raw_stream(_current_device())
 
 
-from . import _marshal  # noqa: E402  (built with the library)
+try:
+    from . import _marshal  # noqa: E402  (built with the library)
+except ImportError:  # another Python than the one it was built for, or no C compiler there: the calls are marshalled below then
+    _marshal = None
 
-_marshal.setup(torch.Tensor, torch.float32, torch.int32, torch.uint8, _current_device, _raw_stream)
+if _marshal is not None:
+    _marshal.setup(torch.Tensor, torch.float32, torch.int32, torch.uint8, _current_device, _raw_stream)
+    _native = _marshal.run
+else:
+    def _native(*args):
+        return None
 
 
 def _address(name):
@@ -315,7 +323,7 @@ def nms_reduce_batched(mask, order, counts, n_max, frames, keep_out, stream=None
 
 
 def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
-    status = _marshal.run(_RUN_BATCHED, boxes, scores, None, n, 1, threshold, keep_out, workspace, stream)  # what nms_run_ws calls
+    status = _native(_RUN_BATCHED, boxes, scores, None, n, 1, threshold, keep_out, workspace, stream)  # what nms_run_ws calls
     if status == NMS_OK:
         return
     if status is not None:
@@ -328,7 +336,7 @@ def nms_run_ws(boxes, scores, n, threshold, keep_out, workspace, stream=None):
 
 
 def nms_run_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    status = _marshal.run(_RUN_BATCHED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    status = _native(_RUN_BATCHED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
     if status == NMS_OK:
         return
     if status is not None:
@@ -372,7 +380,7 @@ class RunPlan:
 
 
 def nms_run_ranked_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    status = _marshal.run(_RUN_RANKED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    status = _native(_RUN_RANKED, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
     if status == NMS_OK:
         return
     if status is not None:
@@ -423,7 +431,7 @@ def nms_greedy_workspace_bytes(n_max: int, frames: int) -> int:
 
 
 def nms_run_greedy_batched(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream=None):
-    status = _marshal.run(_RUN_GREEDY, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
+    status = _native(_RUN_GREEDY, boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, stream)
     if status == NMS_OK:
         return
     if status is not None:

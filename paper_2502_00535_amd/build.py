@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sysconfig
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = [os.path.join(_HERE, "csrc", "nms_kernels.hip")]
@@ -31,26 +32,39 @@ HIPCC_FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIBRARY) or not os.path.exists(MARSHAL):
+    if not os.path.exists(LIBRARY):
         return True
     built = os.path.getmtime(LIBRARY)
-    return any(os.path.getmtime(p) > built for p in SOURCES + HEADERS) or os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL)
+    if any(os.path.getmtime(p) > built for p in SOURCES + HEADERS):
+        return True
+    return os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL)
 
 
 def build_marshal() -> str:
     """The binding's native marshalling (CPython's C API, no device code); returns the path of the module."""
     tmp = MARSHAL + f".tmp{os.getpid()}"
-    cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], MARSHAL_SOURCE, "-o", tmp]
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], MARSHAL_SOURCE, "-o", tmp]
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
-        raise RuntimeError("gcc failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
+        raise RuntimeError("the C compiler failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
     os.replace(tmp, MARSHAL)
     return MARSHAL
 
 
+def build_marshal_if_possible() -> str | None:
+    """The same where there is a C compiler and this Python's headers; without them the binding marshals every call in Python."""
+    try:
+        return build_marshal()
+    except (OSError, RuntimeError) as e:
+        if os.path.exists(MARSHAL):  # of an earlier state of its source
+            os.remove(MARSHAL)
+        warnings.warn(f"native marshalling not built, calls on small frames take 2 us longer: {e}")
+        return None
+
+
 def build_library(verbose: bool = False) -> str:
-    """Always compiles (the binding's marshalling module as well); returns the path of the shared object."""
-    build_marshal()
+    """Always compiles (the binding's marshalling module as well, where that can be done); returns the path of the shared object."""
+    build_marshal_if_possible()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIBRARY + f".tmp{os.getpid()}"
     cmd = [hipcc, *HIPCC_FLAGS, *SOURCES, "-o", tmp]

@@ -1,4 +1,6 @@
 """The native marshalling leaves every argument that is not in order to the Python path, which names it; no GPU needed."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -24,6 +26,51 @@ def test_what_is_not_in_order_is_named():
             call(*args)
         with pytest.raises(TypeError, match="boxes: expected a torch tensor"):
             call("boxes", *args[1:])
+
+
+def test_without_the_native_module():
+    """A Python that the module was not built for, or a machine without a C compiler: the package imports, and every call is
+    marshalled (and refused) as before."""
+    import subprocess
+    import sys
+
+    code = """
+import sys
+sys.modules["paper_2502_00535_amd._marshal"] = None
+import torch
+import paper_2502_00535_amd.binding as nms
+assert nms._marshal is None
+boxes, scores, keep = torch.zeros(1, 8, 4), torch.zeros(1, 8), torch.zeros(1, 8, dtype=torch.uint8)
+for call, args in ((nms.nms_run_ws, (boxes, scores, 8, 0.5, keep, None)), (nms.nms_run_batched, (boxes, scores, None, 8, 1, 0.5, keep, None)),
+                   (nms.nms_run_ranked_batched, (boxes, scores, None, 8, 1, 0.5, keep, None)),
+                   (nms.nms_run_greedy_batched, (boxes, scores, None, 8, 1, 0.5, keep, None))):
+    try:
+        call(*args)
+    except ValueError as e:
+        assert "boxes: tensor must live on the GPU" in str(e)
+    else:
+        raise AssertionError(call)
+    try:
+        call("boxes", *args[1:])
+    except TypeError as e:
+        assert "boxes: expected a torch tensor" in str(e)
+    else:
+        raise AssertionError(call)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    proc = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
+    assert proc.returncode == 0, proc.stderr[-2000:]
+
+
+def test_library_builds_without_a_c_compiler(monkeypatch, tmp_path):
+    from paper_2502_00535_amd import build
+
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    monkeypatch.setenv("CC", "/nonexistent/cc")
+    (tmp_path / "_marshal.so").write_bytes(b"of an earlier state")
+    with pytest.warns(UserWarning, match="native marshalling not built"):
+        assert build.build_marshal_if_possible() is None
+    assert not (tmp_path / "_marshal.so").exists()
 
 
 class Claimed(torch.Tensor):
