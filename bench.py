@@ -274,7 +274,7 @@ def main():
 
     # ------------------------------------------------------------------ headline workload
     # Every pair of the ranked triangle is evaluated: the explicit all-pairs route.  (nms_run_batched
-    # itself routes a batch of this size to the early-exit kernels, which return the same keep vector
+    # itself puts the boxes of a batch of this size in order of place, which returns the same keep vector
     # from a fraction of the pair tests; that is reported in frames/s under extra.automatic_route.)
     all_pairs_entry = "nms_run_ranked_batched" if w.frames * w.n * w.n > (3 << 24) or w.n > 4096 else "nms_run_batched"
     headline = nms.RunPlan(d["boxes"], d["scores"], None, w.n, w.frames, w.theta, d["keep"], d["ws"], entry=all_pairs_entry)
@@ -494,11 +494,13 @@ def main():
                 structure["differing_keep_bits_vs_oracle"] = differing
                 structure["oracle_1_core_us_per_frame"] = round((time.perf_counter() - t0) * 1e6 / wo.frames, 1)
             del ws_go, keep_go
-            # these thresholds have a division-free form: beyond the direct form the configurations take the boxes in order of place
-            route = {0: "direct (one launch)", 1: "all pairs (rank + fused pair-test kernel)",
-                     2: "in order of place (two launches: table, then the victims against the tiles that reach them)", 3: "early exit",
-                     4: "in order of place (one launch: best of the cells around, then the tiles that reach a victim)"}[nms.nms_route(wo.n, wo.frames)]
-            skips = nms.nms_route(wo.n, wo.frames) >= 2
+            kernels = nms.nms_route_at(wo.n, wo.frames, float(wo.theta))
+            route = {nms.NMS_ROUTE_DIRECT: "direct (one launch)", nms.NMS_ROUTE_ALL_PAIRS: "all pairs (rank + fused pair-test kernel)",
+                     nms.NMS_ROUTE_TWO_LAUNCH: "two launches (best 2048 ranks, then the victims still alive)", nms.NMS_ROUTE_EARLY_EXIT: "early exit",
+                     nms.NMS_ROUTE_SMALL_FRAMES: "small frames (one launch, no sort: picked boxes, then the victims still alive against the frame)",
+                     nms.NMS_ROUTE_PLACE_FRAMES: "in order of place (one launch: best of the cells around, then the tiles that reach a victim)",
+                     nms.NMS_ROUTE_PLACE_TABLE: "in order of place (two launches: table, then the victims against the tiles that reach them)"}[kernels]
+            skips = kernels not in (nms.NMS_ROUTE_DIRECT, nms.NMS_ROUTE_ALL_PAIRS)
             ms_pairs = ms_o  # the time in which every pair of the ranked triangle is evaluated
             if skips:
                 # the automatic route skips tests of decided victims here: time the all-pairs route beside it

@@ -90,12 +90,16 @@ int nms_padded_n(int n);                                  /* n rounded up to a m
 size_t nms_mask_words(int n);                             /* ceil(n/64) * nms_padded_n(n) */
 size_t nms_sort_workspace_bytes(int n_max, int frames);   /* scratch of nms_sort*: 0 when n_max <= NMS_SORT_CHUNK */
 size_t nms_workspace_bytes(int n_max, int frames);        /* scratch of nms_run_ws / nms_run_batched */
-/* Which kernels nms_run_batched launches for a batch shape: one of NMS_ROUTE_*; -1 on invalid sizes. */
+/* Which kernels nms_run_batched launches for a batch shape at a threshold: one of NMS_ROUTE_*; -1 on invalid sizes or a NaN threshold. */
 #define NMS_ROUTE_DIRECT 0
 #define NMS_ROUTE_ALL_PAIRS 1
 #define NMS_ROUTE_TWO_LAUNCH 2
 #define NMS_ROUTE_EARLY_EXIT 3
 #define NMS_ROUTE_SMALL_FRAMES 4
+#define NMS_ROUTE_PLACE_FRAMES 5
+#define NMS_ROUTE_PLACE_TABLE 6
+int nms_route_at(int n_max, int frames, float threshold);
+/* The same for thresholds that take the literal division (outside [2^-40, 2^20]); 0 .. 4, -1 on invalid sizes. */
 int nms_route(int n_max, int frames);
 
 /*
@@ -140,17 +144,18 @@ int nms_reduce_batched(const uint64_t *mask, const int32_t *order, const int32_t
 /*
  * The whole path in one call.  No mask is written to memory: the row AND is folded
  * into the pair tests, and the result is the same keep vector as steps 1-3 give.
- * The call picks its route by size (nms_route() names it); every route returns the same bits.
- * Batches of frames of 449 to 4096 boxes whose threshold lies in [2^-40, 2^20] (two frames beyond
- * 2048 boxes, some 8000 boxes in frames beyond 1024, some 28,000 in shorter ones) are put in order
- * of place instead of rank and pairs of boxes that lie apart are left out, in one launch, and so
- * are frames of more than 4096 boxes, in two; the route that nms_route() names is theirs for
- * other thresholds.
+ * The call picks its route by size and threshold (nms_route_at() names it); every route returns the same bits.
+ *   NMS_ROUTE_PLACE_FRAMES  thresholds in [2^-40, 2^20], batches of frames of 449 to 4096 boxes: two frames of
+ *                         2300 boxes or more, four of 2049 or more, 9000 boxes in frames beyond 1024 (8000 from 1640 on),
+ *                         28,000 in frames beyond 512, 512 frames of 449 to 512.  One launch: the boxes in order of place
+ *                         instead of rank, pairs of boxes that lie apart are left out.
+ *   NMS_ROUTE_PLACE_TABLE the same thresholds, frames of more than NMS_SORT_CHUNK boxes: the same in two launches.
+ * Other thresholds, and what these leave:
  *   NMS_ROUTE_DIRECT      small work (up to about 2^25 pair slots = frames * n_max^2): one launch.
  *   NMS_ROUTE_SMALL_FRAMES  batches of ten or more frames of 513 to 1024 boxes (of 128 or more
  *                         frames from 449 boxes on), and 2 to about 40
  *                         frames of 1025 to 4096 boxes (which batch sizes depends on the frame
- *                         length; nms_route() tells): one launch without a sort, every victim
+ *                         length; nms_route_at() tells): one launch without a sort, every victim
  *                         against the two best-ranked of every sixteen input boxes, then the
  *                         victims still alive against the whole frame; rank order enters as a
  *                         compare of the two boxes' (score, index) keys.

@@ -23,10 +23,11 @@ NMS_ERR_TOO_LARGE = -2
 NMS_ERR_WORKSPACE = -3
 NMS_ERR_LAUNCH = -4
 NMS_ROUTE_DIRECT, NMS_ROUTE_ALL_PAIRS, NMS_ROUTE_TWO_LAUNCH, NMS_ROUTE_EARLY_EXIT, NMS_ROUTE_SMALL_FRAMES = 0, 1, 2, 3, 4
+NMS_ROUTE_PLACE_FRAMES, NMS_ROUTE_PLACE_TABLE = 5, 6
 
 EXPORTS = (
     "nms_status_string", "nms_version", "nms_last_launch_error", "nms_padded_n", "nms_mask_words",
-    "nms_sort_workspace_bytes", "nms_workspace_bytes", "nms_route",
+    "nms_sort_workspace_bytes", "nms_workspace_bytes", "nms_route", "nms_route_at",
     "nms_sort", "nms_sort_batched", "nms_overlap_mask", "nms_overlap_mask_batched",
     "nms_reduce", "nms_reduce_batched", "nms_run_ws", "nms_run_batched", "nms_run_ranked_batched", "nms_run_direct_batched",
     "nms_run_batched_profiled", "nms_reduce_greedy", "nms_reduce_greedy_batched",
@@ -83,6 +84,8 @@ def _load() -> ctypes.CDLL:
     L.nms_workspace_bytes.argtypes = [i32, i32]
     L.nms_route.restype = i32
     L.nms_route.argtypes = [i32, i32]
+    L.nms_route_at.restype = i32
+    L.nms_route_at.argtypes = [i32, i32, f32]
     L.nms_sort.restype = i32
     L.nms_sort.argtypes = [vp, vp, i32, vp, vp, vp, sz, vp]
     L.nms_sort_batched.restype = i32
@@ -269,6 +272,10 @@ def nms_workspace_bytes(n_max: int, frames: int) -> int:
 
 def nms_route(n_max: int, frames: int) -> int:
     return int(lib.nms_route(int(n_max), int(frames)))
+
+
+def nms_route_at(n_max: int, frames: int, threshold: float) -> int:
+    return int(lib.nms_route_at(int(n_max), int(frames), float(threshold)))
 
 
 def nms_host_pair_test(victim, outranking, threshold: float) -> int:

@@ -142,13 +142,15 @@ NMS_HD int nms_class_waves(int n_max, int frames)
 }
 
 // ---- which kernels a whole-path call runs ------------------------------------------------------
-// All four routes return the same keep vector (the paper's rule, section "Algorithm Correctness");
-// they differ in what they launch.  Values of nms_route() in the C ABI.
+// All routes return the same keep vector (the paper's rule, section "Algorithm Correctness");
+// they differ in what they launch.  Values of nms_route() and nms_route_at() in the C ABI.
 constexpr int kNmsRouteDirect = 0;     // one launch, full n x n pair set with the score test inside (no rank step)
 constexpr int kNmsRouteAllPairs = 1;   // rank, then every pair of the ranked triangle
 constexpr int kNmsRouteTwoLaunch = 2;  // rank, every victim against the best 2048 ranks, then the live victims only
 constexpr int kNmsRouteEarlyExit = 3;  // rank, then stages that drop a victim once it has an eliminator
 constexpr int kNmsRouteSmallFrames = 4;  // frames of at most 1024 boxes, or a few of up to 4096: two such stages in one launch, no sort
+constexpr int kNmsRoutePlaceFrames = 5;  // boxes in order of place, one launch
+constexpr int kNmsRoutePlaceTable = 6;   // the same for frames beyond sort_chunk boxes: a table launch and a scan launch
 
 // Frames small enough that launch latency, not arithmetic, decides: one launch of the
 // direct form instead of rank + map.  (Twice the pairs and two more compares per pair:
@@ -342,7 +344,11 @@ NMS_HD int nms_place_share(int n_max, int frames)
     return share < 1024 ? share : 1024;
 }
 
-// The route of the automatic whole-path call for a batch shape (1 <= n_max, 1 <= frames).
+// The route of the automatic whole-path call for a batch shape (1 <= n_max, 1 <= frames) where the threshold takes the literal division.  Its
+// lines were drawn with division-free thresholds, before those took the boxes in order of place from some batch size on.  With the
+// literal form, whole call, us, this route / all pairs, at 2^-41 (every overlap eliminates), then at 2^22 (nothing does): 64 x 1024 clustered 13 / 32, 48 / 31;
+// 8 x 2048 8.5 / 25, 26 / 25; 16 x 4096 34 / 91, 184 / 91; 64 x 2048 46 / 86, 118 / 85; 256 x 4096 anchors 111 / 1079, 1218 / 1075; 1 x 16384 crowd 51 / 87, 117 / 87;
+// 16 x 16384 264 / 1109, 1250 / 1103; at 0 10 / 31 to 94 / 1076.
 NMS_HD int nms_route_for(int n_max, int frames, int sort_chunk)
 {
     if (nms_use_small_frames(n_max, frames)) return kNmsRouteSmallFrames;
@@ -350,4 +356,12 @@ NMS_HD int nms_route_for(int n_max, int frames, int sort_chunk)
     if (nms_use_early_exit(n_max, frames, sort_chunk)) return kNmsRouteEarlyExit;
     if (nms_use_two_launches(n_max, frames, sort_chunk)) return kNmsRouteTwoLaunch;
     return kNmsRouteAllPairs;
+}
+
+// The same at a threshold: division_free as in NmsThetaConst::fast.
+NMS_HD int nms_route_with(int n_max, int frames, int sort_chunk, bool division_free)
+{
+    if (division_free && nms_use_spatial_frames(n_max, frames, sort_chunk)) return kNmsRoutePlaceFrames;
+    if (division_free && n_max > sort_chunk) return kNmsRoutePlaceTable;
+    return nms_route_for(n_max, frames, sort_chunk);
 }

@@ -372,7 +372,8 @@ size_t nms_workspace_bytes(int n_max, int frames)
 
 static_assert(kNmsRouteDirect == NMS_ROUTE_DIRECT && kNmsRouteAllPairs == NMS_ROUTE_ALL_PAIRS &&
                   kNmsRouteTwoLaunch == NMS_ROUTE_TWO_LAUNCH && kNmsRouteEarlyExit == NMS_ROUTE_EARLY_EXIT &&
-                  kNmsRouteSmallFrames == NMS_ROUTE_SMALL_FRAMES,
+                  kNmsRouteSmallFrames == NMS_ROUTE_SMALL_FRAMES && kNmsRoutePlaceFrames == NMS_ROUTE_PLACE_FRAMES &&
+                  kNmsRoutePlaceTable == NMS_ROUTE_PLACE_TABLE,
               "route numbers of the header and of the host logic");
 
 int nms_route(int n_max, int frames)
@@ -380,6 +381,13 @@ int nms_route(int n_max, int frames)
     int st;
     if (!sizes_ok(n_max, frames, &st) || n_max == 0 || frames == 0) return -1;
     return nms_route_for(n_max, frames, kChunk);
+}
+
+int nms_route_at(int n_max, int frames, float threshold)
+{
+    int st;
+    if (!sizes_ok(n_max, frames, &st) || n_max == 0 || frames == 0 || is_nan(threshold)) return -1;
+    return nms_route_with(n_max, frames, kChunk, nms_make_theta_const(threshold).fast != 0);
 }
 
 int nms_sort_batched(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
@@ -595,7 +603,7 @@ static int place_paper_launch(bool iou, const float *boxes, const float *scores,
 static int early_exit_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames,
                              float threshold, uint8_t *keep_out, void *workspace, hipStream_t s);
 
-// kRouteAuto: one launch for small frames, direct, all pairs, two launches or early exit by size (nms_route_for).  kRouteAllPairs: direct or ranked by size
+// kRouteAuto: by size and threshold (nms_route_with).  kRouteAllPairs: direct or ranked by size
 // (every pair of the ranked triangle is evaluated).
 enum Route { kRouteAuto = 0, kRouteRanked = 1, kRouteDirect = 2, kRouteAllPairs = 3 };
 
@@ -608,27 +616,21 @@ static int run_routed(Route route, const float *boxes, const float *scores, cons
     if (is_nan(threshold)) return NMS_ERR_INVALID_ARG;
     if (n_max == 0 || frames == 0) return NMS_OK;
     if (!boxes || !scores || !keep_out) return NMS_ERR_INVALID_ARG;
-    const bool by_size = route == kRouteAuto || route == kRouteAllPairs;
-    const bool small = route == kRouteAuto && nms_use_small_frames(n_max, frames);
-    const bool direct = route == kRouteDirect || (by_size && !small && nms_use_direct_form(n_max, frames));
+    const NmsThetaConst th = nms_make_theta_const(threshold);
+    const int kernels = route == kRouteAuto ? nms_route_with(n_max, frames, kChunk, th.fast != 0) : -1;
+    const bool direct = route == kRouteDirect || kernels == kNmsRouteDirect || (route == kRouteAllPairs && nms_use_direct_form(n_max, frames));
     if (route != kRouteDirect) {  // the automatic route validates the workspace whichever way it goes
         const size_t need = nms_workspace_bytes(n_max, frames);
         if (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255)) return NMS_ERR_WORKSPACE;
     }
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (route == kRouteAuto && nms_use_spatial_frames(n_max, frames, kChunk)) {
-        const NmsThetaConst th = nms_make_theta_const(threshold);
-        if (th.fast) return spatial_frames_launch<false, false>(boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, s);
-    }
-    if (route == kRouteAuto && n_max > kChunk) {
-        const NmsThetaConst th = nms_make_theta_const(threshold);
-        if (th.fast) return place_paper_launch(false, boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, workspace, nullptr, s);
-    }
-    if (small)
-        return small_frames_launch(boxes, scores, counts, n_max, frames, nms_make_theta_const(threshold), keep_out, s);
-    if (route == kRouteAuto && !direct && nms_use_early_exit(n_max, frames, kChunk))
-        return early_exit_launch(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, s);
+    if (kernels == kNmsRoutePlaceFrames)
+        return spatial_frames_launch<false, false>(boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, s);
+    if (kernels == kNmsRoutePlaceTable)
+        return place_paper_launch(false, boxes, scores, counts, n_max, frames, {th.m, 1.0f, 0, nullptr}, keep_out, workspace, nullptr, s);
+    if (kernels == kNmsRouteSmallFrames) return small_frames_launch(boxes, scores, counts, n_max, frames, th, keep_out, s);
+    if (kernels == kNmsRouteEarlyExit) return early_exit_launch(boxes, scores, counts, n_max, frames, threshold, keep_out, workspace, s);
     auto mark = [&](int i) {
         if (!events || !events[i]) return true;
         const hipError_t e = hipEventRecord(static_cast<hipEvent_t>(events[i]), s);
@@ -644,8 +646,7 @@ static int run_routed(Route route, const float *boxes, const float *scores, cons
     }
 
     const RunWorkspace w = carve_workspace(workspace, n_max, frames);
-    const NmsThetaConst th = nms_make_theta_const(threshold);
-    const bool staged = route == kRouteAuto && nms_use_two_launches(n_max, frames, kChunk);
+    const bool staged = kernels == kNmsRouteTwoLaunch;
     st = rank_launch(boxes, scores, counts, n_max, frames, w.order, w.sorted5, w.keys, keep_out, w.ysc, w.ytile, s,
                      th.fast ? w.tsc : nullptr, th.m);
     if (st != NMS_OK) return st;

@@ -66,8 +66,20 @@ def test_size_helpers(nms):
     assert nms.nms_workspace_bytes(-1, 1) == 0 and nms.nms_workspace_bytes(1, 70000) == 0
 
 
+def test_route_at_a_threshold(nms):
+    """nms_route_at: the shapes that are put in order of place where the threshold has a division-free form; nms_route's answer elsewhere."""
+    place = {(1024, 1): 0, (4096, 1): 0, (1024, 64): 5, (16384, 1): 6, (4096, 256): 5, (1000, 12): 4, (1024, 16): 4, (2049, 2): 0, (2300, 2): 5, (4097, 1): 6,
+             (65536, 1): 6, (500, 511): 4, (500, 512): 5, (300, 1000): 1, (8192, 40): 6}
+    for (n, f), want in place.items():
+        for theta in (0.5, 2.0 ** -40, 2.0 ** 20, 1.5):
+            assert nms.nms_route_at(n, f, theta) == want, (n, f, theta)
+        for theta in (0.0, -1.0, 2.0 ** -41, 2.0 ** 21, float("inf")):
+            assert nms.nms_route_at(n, f, theta) == nms.nms_route(n, f), (n, f, theta)
+    assert nms.nms_route_at(4096, 4, float("nan")) == -1 and nms.nms_route_at(0, 1, 0.5) == -1 and nms.nms_route_at(70000, 1, 0.5) == -1
+
+
 def test_route_by_size():
-    """nms_route: which kernels the automatic call launches, for the five benchmark shapes and at
+    """nms_route: which kernels the automatic call launches at thresholds that take the literal division, for the five benchmark shapes and at
     each border of the size rules."""
     import paper_2502_00535_amd.binding as nms
 
