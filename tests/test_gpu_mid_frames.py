@@ -1,9 +1,10 @@
-"""The sort-free one-launch route on small batches of frames of 1025 to 4096 boxes (two or four input
-elements per thread, a frame shared out among up to 64 workgroups) against the oracle's plain double
+"""Small batches of frames of 1025 to 4096 boxes through nms_run_batched: at thresholds that take the literal division the sort-free
+one-launch route (mid_frames_kernel: two or four input
+elements per thread, a frame shared out among up to 64 workgroups), at division-free ones spatial_frames_kernel.  Every scene is run at the
+threshold that the test names and at 2^-41, where mid_frames_kernel is what runs; against the oracle's plain double
 loop, 0 differing bits: shares of one, two and three to five tiles of victims (the first stage takes
 a different form for each), frame lengths around the register and tile sizes, ragged batches, long
-lists for the second stage, y coordinates outside the scaled form's range, thresholds that take the
-literal division, equal scores and scores of every kind."""
+lists for the second stage, y coordinates outside the scaled form's range, equal scores and scores of every kind."""
 import numpy as np
 import pytest
 
@@ -23,14 +24,23 @@ def nms():
     return binding
 
 
+LITERAL = 2.0 ** -41  # takes the literal division; boxes that overlap at all eliminate, disjoint ones do not
+
+
 def check(nms, oracle, boxes, scores, theta, counts=None):
+    """At theta and at LITERAL; returns theta's survivors."""
     F, n = scores.shape
-    assert nms.nms_route(n, F) == nms.NMS_ROUTE_SMALL_FRAMES, f"{F} x {n} is not a shape of the one-launch route"
-    want = oracle_keep_frames(oracle, boxes, scores, np.float32(theta), counts)
+    assert nms.nms_route_at(n, F, LITERAL) == nms.NMS_ROUTE_SMALL_FRAMES, f"{F} x {n} is not a shape of the one-launch route"
+    assert nms.nms_route_at(n, F, float(theta)) == (nms.NMS_ROUTE_PLACE_FRAMES if 2.0 ** -40 <= theta <= 2.0 ** 20 and (n >= 2300 or F >= 4)
+                                                    else nms.NMS_ROUTE_SMALL_FRAMES)
     dev = DeviceFrames(nms, boxes, scores, counts)
-    got = dev.fused(float(theta))
-    assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits"
-    return want
+    survivors = None
+    for t in dict.fromkeys((float(theta), LITERAL)):
+        want = oracle_keep_frames(oracle, boxes, scores, np.float32(t), counts)
+        got = dev.fused(t)
+        assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits at {t}"
+        survivors = want if survivors is None else survivors
+    return survivors
 
 
 def clustered(seed, F, n):
@@ -114,7 +124,7 @@ def test_y_ranges_and_literal_division(nms, oracle):
             shifted[f, idx, 1] += 20000.0
             shifted[f, idx, 3] += 20000.0
         check(nms, oracle, shifted, scores, 0.4)
-        for theta in (0.0, 2.0 ** -41, 1.5):
+        for theta in (0.0, 2.0 ** -41, 1.5, 2.0 ** 21):
             check(nms, oracle, boxes, scores, theta)
         check(nms, oracle, shifted, scores, 0.0)
 

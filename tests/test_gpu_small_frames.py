@@ -1,4 +1,6 @@
-"""The one-launch route that nms_run_batched takes for batches of frames of 257 to 1024 boxes (no
+"""Batches of frames of 257 to 1024 boxes through nms_run_batched: the sort-free one-launch route (small_frames_kernel and
+tiny_frames_kernel) for the smaller ones and at thresholds that take the literal division, else spatial_frames_kernel.  Every scene is run at
+the threshold that the test names and at 2^-41, where the sort-free route is what runs; the scenes are built for it (no
 sort: every victim against the two best-ranked of every sixteen input elements, the victims still
 alive against the whole frame, rank order as a compare of the two boxes' keys; a frame shared out
 among 1 to 16 workgroups) against the oracle's plain double loop, 0 differing bits, on what the
@@ -6,8 +8,10 @@ route itself can meet: every number of workgroups per frame, frame lengths aroun
 stage sizes, ragged batches incl. empty frames and frames shorter than a tile, nothing / everything /
 all but a few victims alive after the first stage (short and long lists for the second, at the
 length where its form changes), eliminators that the first stage does not hold, equal scores,
-y coordinates outside the scaled form's range, thresholds that take the literal division, scores
+y coordinates outside the scaled form's range, scores
 of every kind."""
+import itertools
+
 import numpy as np
 import pytest
 
@@ -30,19 +34,26 @@ def nms():
     return binding
 
 
+LITERAL = 2.0 ** -41  # takes the literal division; boxes that overlap at all eliminate, disjoint ones do not
+
+
 def check(nms, oracle, boxes, scores, theta, counts=None):
-    """nms_run_batched (which routes these shapes to the one launch) and the explicit all-pairs route."""
+    """nms_run_batched and the explicit all-pairs route at theta and at LITERAL; returns theta's survivors."""
     F, n = scores.shape
-    assert nms.nms_route(n, F) == nms.NMS_ROUTE_SMALL_FRAMES, f"{F} x {n} is not a shape of the one-launch route"
-    want = oracle_keep_frames(oracle, boxes, scores, np.float32(theta), counts)
+    assert nms.nms_route_at(n, F, LITERAL) == nms.NMS_ROUTE_SMALL_FRAMES, f"{F} x {n} is not a shape of the one-launch route"
+    assert nms.nms_route_at(n, F, float(theta)) in (nms.NMS_ROUTE_SMALL_FRAMES, nms.NMS_ROUTE_PLACE_FRAMES)
     dev = DeviceFrames(nms, boxes, scores, counts)
-    got = dev.fused(float(theta))
-    assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits"
-    dev.keep.fill_(77)
-    nms.nms_run_ranked_batched(dev.boxes, dev.scores, dev.counts, n, F, float(theta), dev.keep, dev.run_ws)
-    dev.torch.cuda.synchronize()
-    assert np.array_equal(dev.keep.cpu().numpy(), want)
-    return want
+    survivors = None
+    for t in dict.fromkeys((float(theta), LITERAL)):
+        want = oracle_keep_frames(oracle, boxes, scores, np.float32(t), counts)
+        got = dev.fused(t)
+        assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits at {t}"
+        dev.keep.fill_(77)
+        nms.nms_run_ranked_batched(dev.boxes, dev.scores, dev.counts, n, F, t, dev.keep, dev.run_ws)
+        dev.torch.cuda.synchronize()
+        assert np.array_equal(dev.keep.cpu().numpy(), want)
+        survivors = want if survivors is None else survivors
+    return survivors
 
 
 def lattice(n, rng=None, pitch=40.0, size=30.0):
@@ -305,12 +316,12 @@ def test_frames_of_at_most_512_boxes(nms, oracle, frames, n):
 def test_route_can_be_captured_in_a_hip_graph(nms, oracle):
     """The route enqueues one kernel and nothing else, so it may be captured; replays with new inputs in the same
     buffers and eager work in between must give the oracle's keep vectors (frames of 1000, 500 and 3000 boxes: the three
-    kernels of the route)."""
+    kernels of the route, at 2^-41; at 0.45 the last is spatial_frames_kernel)."""
     import torch
 
     dev = torch.device("cuda:0")
-    for F, n in ((24, 1000), (130, 500), (5, 3000)):
-        assert nms.nms_route(n, F) == nms.NMS_ROUTE_SMALL_FRAMES
+    for (F, n), theta in itertools.product(((24, 1000), (130, 500), (5, 3000)), (LITERAL, 0.45)):
+        assert nms.nms_route_at(n, F, theta) == (nms.NMS_ROUTE_SMALL_FRAMES if theta == LITERAL or n < 3000 else nms.NMS_ROUTE_PLACE_FRAMES)
         boxes = torch.zeros((F, n, 4), dtype=torch.float32, device=dev)
         scores = torch.zeros((F, n), dtype=torch.float32, device=dev)
         keep = torch.zeros((F, n), dtype=torch.uint8, device=dev)
@@ -319,10 +330,10 @@ def test_route_can_be_captured_in_a_hip_graph(nms, oracle):
         side.wait_stream(torch.cuda.current_stream())
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.stream(side):
-            nms.nms_run_batched(boxes, scores, None, n, F, 0.45, keep, ws)
+            nms.nms_run_batched(boxes, scores, None, n, F, theta, keep, ws)
             side.synchronize()
             with torch.cuda.graph(graph, stream=side):
-                nms.nms_run_batched(boxes, scores, None, n, F, 0.45, keep, ws)
+                nms.nms_run_batched(boxes, scores, None, n, F, theta, keep, ws)
         torch.cuda.synchronize()
         for rep in range(3):
             b, s = batch(31000 + 1000 * rep + n, F, n, extent=900, max_side=120, integer=(rep % 2 == 0), score_levels=100)
@@ -332,5 +343,5 @@ def test_route_can_be_captured_in_a_hip_graph(nms, oracle):
             (boxes.sum() + scores.sum()).item()
             graph.replay()
             torch.cuda.synchronize()
-            want = oracle_keep_frames(oracle, b, s, np.float32(0.45))
+            want = oracle_keep_frames(oracle, b, s, np.float32(theta))
             assert np.array_equal(keep.cpu().numpy(), want), f"{F} x {n}, replay {rep}"

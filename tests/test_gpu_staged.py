@@ -1,11 +1,13 @@
-"""The two-launch route that nms_run_batched takes for a few frames of more than 4096 boxes
-(first launch: every victim against the best 2048 ranks; second launch: the victims still alive,
+"""Frames of more than 4096 boxes, a few of them, through nms_run_batched: at thresholds that take the literal division the
+two-launch route (staged_first_kernel, staged_second_kernel), at division-free ones the boxes in order of place
+(place_sort_kernel, place_scan_kernel).  Every scene is run at the threshold that the test names and at 2^-41, where the two-launch
+route is what runs; the scenes are built for it (first launch: every victim against the best 2048 ranks; second launch: the victims still alive,
 64 consecutive live ones per wavefront, against the rest) against the oracle's plain double loop,
 0 differing bits, on what the route itself can meet: nothing alive after the first launch,
 everything alive, exactly one live victim, live counts on and next to multiples of 64, eliminators
 that sit only behind rank 2048 (in the tile of their victim's own run, at run and tile borders),
 ragged batches whose frames end before, at and behind rank 2048, y coordinates outside the scaled
-form's range, thresholds that take the literal division, scores of every kind."""
+form's range, scores of every kind."""
 import numpy as np
 import pytest
 
@@ -28,19 +30,26 @@ def nms():
     return binding
 
 
+LITERAL = 2.0 ** -41  # takes the literal division; boxes that overlap at all eliminate, disjoint ones do not
+
+
 def check(nms, oracle, boxes, scores, theta, counts=None):
-    """nms_run_batched (which routes these sizes to the two launches) and the explicit all-pairs route."""
+    """nms_run_batched and the explicit all-pairs route at theta and at LITERAL; returns theta's survivors."""
     F, n = scores.shape
-    assert nms.nms_route(n, F) == nms.NMS_ROUTE_TWO_LAUNCH, "not a size of the two-launch route"
-    want = oracle_keep_frames(oracle, boxes, scores, np.float32(theta), counts)
+    assert nms.nms_route_at(n, F, LITERAL) == nms.NMS_ROUTE_TWO_LAUNCH, "not a size of the two-launch route"
+    assert nms.nms_route_at(n, F, float(theta)) == (nms.NMS_ROUTE_PLACE_TABLE if 2.0 ** -40 <= theta <= 2.0 ** 20 else nms.NMS_ROUTE_TWO_LAUNCH)
     dev = DeviceFrames(nms, boxes, scores, counts)
-    got = dev.fused(float(theta))
-    assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits"
-    dev.keep.fill_(77)
-    nms.nms_run_ranked_batched(dev.boxes, dev.scores, dev.counts, n, F, float(theta), dev.keep, dev.run_ws)
-    dev.torch.cuda.synchronize()
-    assert np.array_equal(dev.keep.cpu().numpy(), want)
-    return want
+    survivors = None
+    for t in dict.fromkeys((float(theta), LITERAL)):
+        want = oracle_keep_frames(oracle, boxes, scores, np.float32(t), counts)
+        got = dev.fused(t)
+        assert np.array_equal(got, want), f"{(got != want).sum()} differing keep bits at {t}"
+        dev.keep.fill_(77)
+        nms.nms_run_ranked_batched(dev.boxes, dev.scores, dev.counts, n, F, t, dev.keep, dev.run_ws)
+        dev.torch.cuda.synchronize()
+        assert np.array_equal(dev.keep.cpu().numpy(), want)
+        survivors = want if survivors is None else survivors
+    return survivors
 
 
 def lattice(n, rng=None, pitch=40.0, size=30.0):
@@ -152,7 +161,7 @@ def test_y_ranges_and_literal_division(nms, oracle):
         shifted[idx, 1] += 20000.0
         shifted[idx, 3] += 20000.0
     check(nms, oracle, shifted[None], scores[None], 0.4)
-    for theta in (0.0, 2.0 ** -41, 1.5):
+    for theta in (0.0, 2.0 ** -41, 1.5, 2.0 ** 21):
         check(nms, oracle, boxes[None], scores[None], theta)
     check(nms, oracle, shifted[None], scores[None], 0.0)
 
