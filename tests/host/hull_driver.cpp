@@ -1,4 +1,4 @@
-// Host check of what the kernels in order of place rely on: a box that eliminates a victim passes the same test against any box
+// Host check that the pair test is monotone in the victim's box: a box that eliminates a victim passes the same test against any box
 // around the victim.  Reads lines "theta cx1 cy1 cx2 cy2 k" followed by k victims; prints "violations <n> hits <n>".
 #include <cstdio>
 #include <vector>

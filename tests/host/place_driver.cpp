@@ -3,6 +3,8 @@
 //                             reach words as the kernels form them (64 lanes at a time, lanes behind the last tile read the last one);
 //                             prints "words <n> outside <n>": bits of lanes that are no tile
 //   place_driver bins         labels -8 .. 511 and their bins
+//   place_driver tiles        random tiles of outranking boxes and victims: a pair that eliminates, by the definition (float32, IEEE division), in a tile that does not
+//                             reach the victim is a violation; a box under its own T that eliminates is one too.  Prints, per form, "form violations hits reached of"
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -78,6 +80,87 @@ static void reach(std::mt19937 &rng, long &words, long &outside)
     }
 }
 
+// The definition: the outranking box c eliminates v, compare >= or > (gt).
+static bool eliminates(const Box &v, const Box &c, bool iou, bool gt, float off, float theta)
+{
+    volatile float iw = std::max(0.0f, (std::min(v.z, c.z) - std::max(v.x, c.x)) + off);
+    volatile float ih = std::max(0.0f, (std::min(v.w, c.w) - std::max(v.y, c.y)) + off);
+    volatile float inter = iw * ih;
+    volatile float wc = (c.z - c.x) + off, hc = (c.w - c.y) + off, wv = (v.z - v.x) + off, hv = (v.w - v.y) + off;
+    volatile float ac = wc * hc, av = wv * hv;
+    volatile float sum = av + ac;
+    volatile float denom = iou ? sum - inter : (float)ac;
+    volatile float q = inter / denom;
+    return gt ? q > theta : !(q < theta);
+}
+
+// The rounding boundary of the division next to theta, below it for >=, above it for >.
+static double boundary_of(float theta, bool gt)
+{
+    uint32_t b;
+    std::memcpy(&b, &theta, sizeof b);
+    b = gt ? b + 1u : b - 1u;
+    float other;
+    std::memcpy(&other, &b, sizeof other);
+    return 0.5 * ((double)theta + (double)other);
+}
+
+template <bool IOU>
+static void tiles_form(std::mt19937 &rng, bool gt, float off, const char *name)
+{
+    std::uniform_real_distribution<float> u(0.0f, 1.0f);
+    const float thetas[] = {0.3f, 0.45f, 0.5f, 0.7f, 1.0f, 0x1p-40f, 0.01f, 1.3f, 0x1p20f, 0.25f};
+    long violations = 0, hits = 0, reached = 0, asked = 0;
+    for (int round = 0; round < 6000; ++round) {
+        const float theta = thetas[rng() % 10];
+        const double boundary = boundary_of(theta, gt);
+        const float scale = std::ldexp(1.0f, (int)(rng() % 40) - 10), size = std::ldexp(1.0f, (int)(rng() % 14) - 6);
+        const bool grid = rng() % 2, steered = rng() % 2, flat = IOU && off == 0.0f && rng() % 4 == 0;
+        const float cx = scale * (u(rng) - 0.5f), cy = scale * (u(rng) - 0.5f);
+        auto box = [&](float spread) {
+            float x = cx + spread * (u(rng) - 0.5f), y = cy + spread * (u(rng) - 0.5f), w = size * u(rng), h = size * u(rng);
+            if (grid) x = std::floor(x), y = std::floor(y), w = std::floor(w), h = std::floor(h);
+            if (off == 0.0f && !flat) w += size * 0.01f + 0x1p-20f * scale, h += size * 0.01f + 0x1p-20f * scale;  // extents above 0
+            Box b = {x, y, x + w, y + h};
+            if (flat && rng() % 3 == 0) b.z = b.x;  // no area
+            return b;
+        };
+        const int n = 1 + (int)(rng() % kTile);
+        std::vector<Box> box_c(n);
+        std::vector<float> T(n);
+        std::vector<uint32_t> upper(n);
+        for (int i = 0; i < n; ++i) {
+            box_c[i] = box(size * 3.0f);
+            T[i] = nms_place_threshold<IOU>(((box_c[i].z - box_c[i].x) + off) * ((box_c[i].w - box_c[i].y) + off), boundary);
+            upper[i] = (uint32_t)rng() % 16;
+        }
+        const Tile t = make_tile<IOU>(box_c, T, upper, n, 0);
+        for (int k = 0; k < 12; ++k) {
+            Box v = box(size * 3.0f);
+            if (steered) {  // a victim that just reaches, or is, a box of the tile
+                const Box &c = box_c[rng() % n];
+                const float w = c.z - c.x, h = c.w - c.y;
+                v = {c.x + w * (rng() % 3 == 0 ? 0.0f : theta < 1.0f ? 1.0f - theta : 0.0f), c.y, c.z, c.w + (rng() % 4 == 0 ? h : 0.0f)};
+                if (!(v.z >= v.x)) v = c;
+            }
+            const uint32_t v_upper = (uint32_t)rng() % 16;
+            const float v_T = nms_place_threshold<IOU>(((v.z - v.x) + off) * ((v.w - v.y) + off), boundary);
+            const bool reach = nms_place_reaches<IOU>(v, v_T, v_upper, t.hull, t.T, t.best, off);
+            reached += reach;
+            ++asked;
+            for (int i = 0; i < n; ++i) {
+                if (upper[i] > v_upper || !eliminates(v, box_c[i], IOU, gt, off, theta)) continue;
+                ++hits;
+                const float inter = nms_place_inter(v, box_c[i], off);
+                const bool first_test = inter >= (IOU ? std::max(T[i], v_T) : T[i]);
+                const bool no_area = IOU && !(T[i] > 0.0f && v_T > 0.0f);  // (decided by the tile's reach alone: 0 / 0)
+                if (!reach || (!first_test && !no_area)) ++violations;
+            }
+        }
+    }
+    std::printf("%s %ld %ld %ld %ld\n", name, violations, hits, reached, asked);
+}
+
 int main(int argc, char **argv)
 {
     std::mt19937 rng(7);
@@ -86,6 +169,15 @@ int main(int argc, char **argv)
         reach<false>(rng, words, outside);
         reach<true>(rng, words, outside);
         std::printf("words %ld outside %ld\n", words, outside);
+        return 0;
+    }
+    if (argc > 1 && std::strcmp(argv[1], "tiles") == 0) {
+        tiles_form<false>(rng, false, 1.0f, "area_ge");
+        tiles_form<false>(rng, true, 1.0f, "area_gt");
+        tiles_form<true>(rng, false, 1.0f, "iou_ge_1");
+        tiles_form<true>(rng, true, 1.0f, "iou_gt_1");
+        tiles_form<true>(rng, false, 0.0f, "iou_ge_0");
+        tiles_form<true>(rng, true, 0.0f, "iou_gt_0");
         return 0;
     }
     if (argc > 1 && std::strcmp(argv[1], "bins") == 0) {

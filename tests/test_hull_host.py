@@ -1,5 +1,6 @@
-"""A victim's hull stands in for it when pairs are left out: no pair that eliminates may be lost, whatever the rounding
-(coordinates of very different sizes, thresholds at both ends of the division-free range, boxes that just touch)."""
+"""The pair test is monotone in the victim's box: a hull around several victims is eliminated where one of them is, whatever the
+rounding (coordinates of very different sizes, thresholds at both ends of the division-free range, boxes that just touch).  What the kernels
+in order of place rest on, tiles of outranking boxes with their hull and least T, is in test_place_host.py."""
 import os
 import subprocess
 

@@ -31,3 +31,14 @@ def test_labels_are_told_apart_and_spread(driver):
     assert len({(bins[n], n & 0xf0) for n in range(256)}) == 256
     assert len({bins[n] for n in range(16)}) == 16 and len({bins[16 * n] for n in range(16)}) == 16
     assert len({bins[20 * n] for n in range(16)}) > 8
+
+
+def test_no_eliminator_lies_in_a_tile_that_does_not_reach_the_victim(driver):
+    """The hull, the least T and the reach predicate of the kernels against the definition (float32, IEEE division), both measures, both
+    compares, pixel offsets 1 and 0, boxes without area, tiles that are not full, thresholds at both ends of the division-free range,
+    coordinates of very different sizes, boxes that just touch."""
+    out = subprocess.run([driver, "tiles"], capture_output=True, text=True, check=True).stdout.strip().split("\n")
+    assert len(out) == 6
+    for line in out:
+        form, violations, hits, reached, asked = line.split()
+        assert int(violations) == 0 and int(hits) > 50000 and 5000 < int(asked) - int(reached), line
