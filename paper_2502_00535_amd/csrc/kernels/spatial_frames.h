@@ -86,30 +86,23 @@ __device__ __forceinline__ unsigned place_cell(const float4 b, const PlaceGrid &
     const unsigned cls = t < 0.5f ? 0u : (t < 2.0f ? 1u : (t < 8.0f ? 2u : 3u));
     return cls * (unsigned)(AXIS * AXIS) + place_spot<AXIS>(b, g);
 }
-// The cells of a class in the order of a Hilbert curve: neighbours on the curve are neighbours in the picture.
+// The cells of a class in the order of Hilbert's curve (D. Hilbert, Mathematische Annalen 38, 1891): neighbours on the curve are neighbours in
+// the picture.  From his construction: the curve of twice the side is four copies of the one before, the first mirrored
+// in the diagonal, the next two as they are, the last mirrored in the other diagonal.
 template <int AXIS>
 struct HilbertCells {
     uint16_t at[AXIS * AXIS];
     constexpr HilbertCells() : at()
     {
-        for (unsigned i = 0; i < (unsigned)(AXIS * AXIS); ++i) {
-            unsigned d = i, x = 0, y = 0;
-            for (unsigned s = 1; s < (unsigned)AXIS; s <<= 1) {
-                const unsigned rx = 1u & (d >> 1), ry = 1u & (d ^ rx);
-                if (ry == 0) {
-                    if (rx == 1) {
-                        x = s - 1u - x;
-                        y = s - 1u - y;
-                    }
-                    const unsigned t = x;
-                    x = y;
-                    y = t;
-                }
-                x += s * rx;
-                y += s * ry;
-                d >>= 2;
+        for (unsigned side = 1; side < (unsigned)AXIS; side *= 2) {
+            const unsigned cells = side * side;
+            for (unsigned i = 0; i < cells; ++i) {
+                const unsigned x = at[i] % AXIS, y = at[i] / AXIS;
+                at[i] = (uint16_t)(x * AXIS + y);
+                at[cells + i] = (uint16_t)((y + side) * AXIS + x);
+                at[2 * cells + i] = (uint16_t)((y + side) * AXIS + (x + side));
+                at[3 * cells + i] = (uint16_t)((side - 1 - x) * AXIS + (2 * side - 1 - y));
             }
-            at[i] = (uint16_t)(y * AXIS + x);
         }
     }
 };
