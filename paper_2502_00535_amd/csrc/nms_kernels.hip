@@ -238,6 +238,9 @@ int place_sort_launch(const float *boxes, const float *scores, const int32_t *co
     return launch_status();
 }
 
+// Wavefronts per tile of victims: sixteen while the workgroups leave compute units idle, four beyond.  Whole call, us, sixteen / four: 66 tiles in all
+// (1 x 4200) 13.6 / 14.3; 256 (1 x 16,384) 20.1 / 21.5; 384 (3 x 8192) 17.4 / 16.9; 469 (1 x 30,000) 43.1 / 43.3; 512 (2 x 16,384) 23.8 / 23.1; 632 (8 x 5000
+// clustered) 19.6 / 18.5; 1024 (4 x 16,384) 29.6 / 25.9; 8192 (64 x 8192) 102 / 64.  From 384 to 512 tiles either is ahead by 3 %.
 template <bool IOU>
 int place_scan_launch(const int32_t *counts, int n_max, int frames, const PlaceTest &test, const PlaceTable &tab, uint8_t *keep_out,
                       hipStream_t stream)
@@ -295,6 +298,10 @@ int greedy_small_launch(const float *boxes, const float *scores, const int32_t *
     return launch_status();
 }
 
+// Victims of a wavefront of place_relation_kernel: fewer leave fewer compute units idle, more read a tile's rows less often.  Whole call under the
+// greedy rule with IoU, us, 1 / 2 / 4 victims: 64 tiles in all (1 x 4096 clustered) 26.9 / 28.6 / 33.3; 125 (1 x 8000) 61.5 / 60.3 / 65.6; 128 (2 x 4096)
+// 30.9 / 30.1 / 35.0, anchors 29.6 / 28.2; 2 / 4 victims: 256 (4 x 4096) 35.0 / 36.3; 282 (6 x 3000) 34.9 / 38.4; 375 (3 x 8000) 72 / 76; 384 (6 x 4096) 39.7 / 43.3;
+// 512 (8 x 4096) 43.9 / 43.8; 1984 (31 x 4096) 93.1 / 91.2.
 int place_relation_launch(const float *boxes, const float *scores, const int32_t *counts, int n_max, int frames, const PlaceTest &test,
                           const PlaceTable &tab, const PlaceRelation &rel, uint8_t *keep_out, hipStream_t stream)
 {
@@ -303,7 +310,7 @@ int place_relation_launch(const float *boxes, const float *scores, const int32_t
     begin_launch();
     if ((long long)frames * tiles <= 64)  // a workgroup per compute unit, a victim per wavefront
         place_relation_kernel<16, 1><<<dim3((unsigned)frames, (unsigned)tiles * 4), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 2, test, tab, rel);
-    else if ((long long)frames * tiles <= 128)
+    else if ((long long)frames * tiles <= 384)
         place_relation_kernel<16, 2><<<dim3((unsigned)frames, (unsigned)tiles * 2), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 1, test, tab, rel);
     else
         place_relation_kernel<16, 4><<<dim3((unsigned)frames, (unsigned)tiles), dim3(16 * 64), 0, stream>>>(counts, n_max, n_pad, 0, test, tab, rel);

@@ -71,7 +71,7 @@ def test_crowded_frames(nms, oracle, frames, n):
             assert np.array_equal(got, want), f"{(got != want).sum(axis=1)} differing keep bits per frame: {opts} {theta}"
 
 
-@pytest.mark.parametrize("frames,n,objects", [(31, 4096, 1), (31, 4096, 6), (6, 4096, 40), (40, 5000, 1)])
+@pytest.mark.parametrize("frames,n,objects", [(31, 4096, 1), (31, 4096, 6), (6, 4096, 40), (7, 4096, 40), (40, 5000, 1)])
 def test_batches_of_crowded_frames(nms, oracle, frames, n, objects):
     """More workgroups than fit at once: later tiles of a frame are not related once many of its rows are crowded."""
     print(f"case {frames} x {n} x {objects}", flush=True)
