@@ -308,7 +308,7 @@ NMS_HD bool nms_use_spatial_variant(int n_max, int frames, bool iou, bool labell
 
 // The greedy rule under IoU in order of place (place_relation_kernel, place_resolve_kernel) against rank, mask and sweep; from walk_boxes boxes in
 // frames of up to sort_chunk on the walk and the class kernel take them.  Whole call, us, place / rank, mask and sweep, clustered, then sparse anchors:
-// 1 x 4096 27.3 / 36.0, 26.9 / 35.6; 4 x 4096 36 / 50, 33 / 48; 31 x 4096 91 / 134, 86 / 121; 20 x 3000 55 / 71, with 20 labels 49 / 74; 1 x 2049
+// 1 x 4096 27.3 / 36.0, 26.9 / 35.6; 4 x 4096 35 / 50, 32 / 48; 31 x 4096 91 / 134, 86 / 121; 20 x 3000 55 / 71, with 20 labels 49 / 74; 1 x 2049
 // 22.5 / 23.5; clustered 1 x 8000 61 / 89, 6 x 8000 90 / 142, 60 x 8000 334 / 725.  Shorter frames gain nothing, and at a lower threshold lose: 2 x 2048 at
 // 0.3 34 / 23, 3 x 1500 26 / 22.  Where thousands of candidates crowd around few objects: one object 1 x 4096 54 / 39, 31 x 4096 78 / 192, 1 x 8000 133 / 96; four
 // 83 / 38, 198 / 192, 147 / 96; sixteen 41 / 38, 172 / 190, 184 / 96.  A chain of 4096 eliminators in place order 270 / 187, in random order 939 / 187.
@@ -336,7 +336,9 @@ NMS_HD NmsRelationBlock nms_relation_block(int n_pad)
     return b;
 }
 
-// Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.
+// Places per workgroup of place_sort_kernel: a multiple of 64, at most 1024; a workgroup per compute unit where the batch allows.  Twice and four times
+// the share (half and a quarter of the workgroups, whole call, us, share / twice / four times): 1 x 16,384 20.4 / 20.5 / 21.2; 2 x 16,384 24.2 / 24.4 / 25.1; 16 x 5000
+// 20.9 / 21.0 / 21.3; 8 x 5000 18.6 / 18.6 / 18.8; 1 x 4200 and 64 x 8192 alike; only 1 x 30,000 takes 44.1 / 41.6 / 42.0 (every workgroup reads the whole frame again).
 NMS_HD int nms_place_share(int n_max, int frames)
 {
     const int parts = 256 / (frames < 256 ? frames : 256);
