@@ -27,8 +27,8 @@
 // The order of boxes inside a cell and the boxes of stage 1 are whatever the atomics make them; no result
 // depends on them.
 //
-// What bounds it: on large batches VALU issue and LDS bandwidth of stage 2 (of 93 k cycles at 256 x 4096 anchors 17 k are
-// the tables, 20 k stage 1, 55 k stage 2); on small ones the chain of seven barriers (256 x 1024: 18 k cycles).
+// What bounds it: on large batches VALU issue (by counters 74 k of 97 k cycles at 256 x 4096 anchors; the LDS is indexed in 34 k, 8 k of
+// them bank conflicts; 17 k are the tables, 20 k stage 1, 55 k stage 2); on small ones the chain of seven barriers (256 x 1024: 18 k cycles).
 // Measured, whole call, us, against the kernels that took these batches before (rank order, early exit):
 // 256 x 4096 anchors 45.5 / 145, clustered 33.0 / 99; 48 ragged frames of 1777 boxes 10.0 / 29.3; 64 x 1024 8.5 / 11.7;
 // 512 x 1024 anchors 45 / 133.
